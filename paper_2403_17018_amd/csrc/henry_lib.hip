@@ -2006,22 +2006,37 @@ static int mlmc_estimate_impl(henry_ctx* ctx, int L, const int* m, const henry_g
     fail(HENRY_EINVAL, "estimator workspace of %zu doubles exceeds the %zu available", need, work_doubles);
   }
   hipStream_t st = ctx->stream;
-  // scalar estimator: per level mean and unbiased variance of Y_l (two-pass, fixed order)
-  for (int l = 0; l <= L; ++l)
-    hipLaunchKernelGGL(k_level_moments, dim3(1), dim3(256), 0, st, m[l], g_fine[l], l > 0 ? g_coarse[l] : nullptr,
-                       work + 2 * l);
-  if (fields) {
-    const int nxL = grids[L].nx, nyL = grids[L].ny, ncL = nxL * nyL;
+  // mean and unbiased variance of Y_l on every level and of every cell of the fields, two-pass in
+  // a fixed order
+  MomentSegs sg{};
+  long long blocks = 0;
+  auto add = [&](const double* f, const double* g, long long rows, int ml, size_t mean_off, size_t var_off) {
+    const int k = sg.nseg++;
+    sg.first[k] = (int)blocks;
+    sg.rows[k] = (int)rows;
+    sg.m[k] = ml;
+    sg.lanes[k] = moment_lanes(ml);
+    sg.f[k] = f;
+    sg.g[k] = g;
+    sg.mean[k] = (long long)mean_off;
+    sg.var[k] = (long long)var_off;
+    const int per = 256 / sg.lanes[k];
+    blocks += (rows + per - 1) / per;
+  };
+  for (int l = 0; l <= L; ++l) add(g_fine[l], l > 0 ? g_coarse[l] : nullptr, 1, m[l], 2 * l, 2 * l + 1);
+  if (fields)
     for (int l = 0; l <= L; ++l) {
-      const int nc = grids[l].nx * grids[l].ny;
-      double* t = work + off[l];
-      hipLaunchKernelGGL(k_cell_moments, dim3((nc + 255) / 256), dim3(256), 0, st, nc, m[l], c_fine[l], t, t + nc);
+      const long long nc = (long long)grids[l].nx * grids[l].ny;
+      add(c_fine[l], nullptr, nc, m[l], off[l], off[l] + nc);
       if (l > 0) {
-        const int ncc = grids[l - 1].nx * grids[l - 1].ny;
-        hipLaunchKernelGGL(k_cell_moments, dim3((ncc + 255) / 256), dim3(256), 0, st, ncc, m[l], c_coarse[l],
-                           t + 2 * nc, t + 2 * nc + ncc);
+        const long long ncc = (long long)grids[l - 1].nx * grids[l - 1].ny;
+        add(c_coarse[l], nullptr, ncc, m[l], off[l] + 2 * nc, off[l] + 2 * nc + ncc);
       }
     }
+  if (blocks > 0x7fffffffLL) fail(HENRY_EUNSUPPORTED, "too many cells for the estimator");
+  hipLaunchKernelGGL(k_moments, dim3((unsigned)blocks), dim3(256), 0, st, sg, work);
+  if (fields) {
+    const int nxL = grids[L].nx, nyL = grids[L].ny, ncL = nxL * nyL;
     FieldLevels fl{};
     fl.L = L;
     for (int l = 0; l <= L; ++l) {

@@ -1,0 +1,50 @@
+"""The sizes where a launch rule changes its shape: each kernel against the oracle or a plain
+64-bit result at the edges and remainders of its tiles."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from henry_inputs import draw_theta
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    import paper_2403_17018_amd as P
+    h = P.Henry(0)
+    yield h
+    h.close()
+
+
+def _cu(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+@pytest.mark.parametrize("m", [(1, 2), (3, 15), (16, 17), (33, 64), (65, 255), (256, 1023), (1024, 1025), (4096, 4099)])
+def test_moments_at_every_row_width(hx, m):
+    """Rows of m samples are shared by 1 .. 64 threads or a block, with remainders: level and
+    cell moments against numpy.  Bound: a sum of m terms in any order is off by at most
+    (m - 1) eps of the sum of magnitudes; mean and squared deviations take a few such sums."""
+    import paper_2403_17018_amd as P
+    rng = np.random.default_rng(5)
+    grids = [P.grid(6, 3, 1), P.grid(12, 6, 1)]
+    gf = [rng.normal(3.0, 1.0, k) for k in m]
+    gc = [None, rng.normal(2.5, 1.0, m[1])]
+    cf = [rng.uniform(size=(g.ny, g.nx, k)) for g, k in zip(grids, m)]
+    cc = [None, rng.uniform(size=(3, 6, m[1]))]
+    cu = lambda a: None if a is None else _cu(a)
+    out = hx.mlmc_estimate(grids, [cu(a) for a in gf], [cu(a) for a in gc], [cu(a) for a in cf], [cu(a) for a in cc])
+    Y = [gf[0], gf[1] - gc[1]]
+    var = lambda a: a.var(axis=-1, ddof=1) if a.shape[-1] > 1 else np.zeros(a.shape[:-1])
+    eps = 2.3e-16 * (max(m) + 10)
+    assert abs(out["mean"] - sum(y.mean() for y in Y)) <= 8 * eps * sum(np.abs(y).mean() for y in Y)
+    for v, y in zip(out["V"], Y):
+        assert abs(v - var(y)) <= 8 * eps * (np.abs(y) ** 2).mean() * len(y) / max(1, len(y) - 1)
+    up = lambda a: a.repeat(2, 0).repeat(2, 1)
+    mean = up(cf[0].mean(-1)) + cf[1].mean(-1) - up(cc[1].mean(-1))
+    vf = up(var(cf[0])) + var(cf[1]) - up(var(cc[1]))
+    assert np.abs(out["mean_field"].cpu().numpy() - mean).max() <= 8 * eps * 3
+    assert np.abs(out["var_field"].cpu().numpy() - vf).max() <= 8 * eps * 3 * 2
