@@ -230,6 +230,10 @@ static dim3 grid_cells(const Map& m, int ncell) {
   const long long nb = (long long)m.nsb * ((ncell + m.CY - 1) / m.CY);
   return dim3((unsigned)nb);
 }
+static dim3 grid_fields(const Map& m, int ncell) {
+  const int per = FIELDS_CPT * m.CY;
+  return dim3((unsigned)((long long)m.nsb * ((ncell + per - 1) / per)));
+}
 static dim3 grid_red(const Map& m) { return dim3((unsigned)((long long)m.nsb * m.ncb)); }
 static dim3 block_of(const Map& m) { return dim3(m.SX, m.CY); }
 // the assembly's tiles: one workgroup per (sample block, ASM_TX x ASM_TY cells)
@@ -757,7 +761,7 @@ struct Solver {
 
   void fields(const double* theta) {
     const Map& m = P.m;
-    hipLaunchKernelGGL(k_fields, grid_cells(m, P.G.ncell), block_of(m), 0, st, m, P.G, phys, kl, fp, theta,
+    hipLaunchKernelGGL(k_fields, grid_fields(m, P.G.ncell), block_of(m), fields_lds(m.CY), st, m, P.G, phys, kl, fp, theta,
                        P.phi.as<double>(), P.K.as<double>(), P.uin.as<double>());
     for (int k = 1; k < P.nlev; ++k) {
       MGLevel& F = *P.lv[k - 1];
@@ -1909,7 +1913,7 @@ int henry_sample_fields(henry_ctx* ctx, const henry_problem* prob, henry_grid gr
     const Phys P = make_phys(*prob, grid.nx, grid.ny, grid.nsteps);
     const KLModes kl = make_kl(*prob);
     const FieldParams fp = make_fp(*prob);
-    hipLaunchKernelGGL(k_fields, grid_cells(m, G.ncell), block_of(m), 0, ctx->stream, m, G, P, kl, fp, theta, phi, K,
+    hipLaunchKernelGGL(k_fields, grid_fields(m, G.ncell), block_of(m), fields_lds(m.CY), ctx->stream, m, G, P, kl, fp, theta, phi, K,
                        q_in);
     HIPCHK(hipGetLastError());
     return HENRY_OK;
@@ -2215,7 +2219,7 @@ int henry_assemble(henry_ctx* ctx, const henry_problem* prob, henry_grid grid, i
     double* phi = ctx->kws.as<double>();
     double* K = phi + N;
     double* uin = K + N;
-    hipLaunchKernelGGL(k_fields, grid_cells(m, G.ncell), block_of(m), 0, ctx->stream, m, G, P, make_kl(*prob),
+    hipLaunchKernelGGL(k_fields, grid_fields(m, G.ncell), block_of(m), fields_lds(m.CY), ctx->stream, m, G, P, make_kl(*prob),
                        make_fp(*prob), theta, phi, K, uin);
     hipLaunchKernelGGL((k_assemble<true, double, false, true>), asm_grid(m, G), asm_block(m), asm_lds(m.SX), ctx->stream, m,
                        G, P, p, c, c_old, (const double*)phi, (const double*)K, (const double*)uin, R, J,
@@ -2627,7 +2631,7 @@ struct VCSolver {
   }
 
   void fields(const double* theta) {
-    hipLaunchKernelGGL(k_fields, grid_cells(me, ne), block_of(me), 0, st, me, E, P, make_kl(pr), make_fp(pr), theta,
+    hipLaunchKernelGGL(k_fields, grid_fields(me, ne), block_of(me), fields_lds(me.CY), st, me, E, P, make_kl(pr), make_fp(pr), theta,
                        phi.as<double>(), K.as<double>(), uin.as<double>());
     const double* pf = phi.as<double>();
     const double* kf = K.as<double>();

@@ -48,3 +48,37 @@ def test_moments_at_every_row_width(hx, m):
     vf = up(var(cf[0])) + var(cf[1]) - up(var(cc[1]))
     assert np.abs(out["mean_field"].cpu().numpy() - mean).max() <= 8 * eps * 3
     assert np.abs(out["var_field"].cpu().numpy() - vf).max() <= 8 * eps * 3 * 2
+
+
+@pytest.mark.parametrize("S", [1, 3, 16, 37, 64, 130])
+@pytest.mark.parametrize("model", ["kl", "paper"])
+@pytest.mark.parametrize("nx,ny", [(6, 3), (34, 17), (64, 32)])
+def test_fields_at_block_edges(hx, S, model, nx, ny):
+    """Cells per block 4 * (256 / min(S, 64)), with remainders: phi, K and u_in against the
+    oracle.  Bound: 8 + 8 products and sums, and exp's argument (about 21) carried to K."""
+    import paper_2403_17018_amd as P
+    from oracle import henry as H
+    th = draw_theta(31, S, level=1)
+    prob, pro = (P.paper_problem(), H.paper_problem()) if model == "paper" else (P.problem(), H.Problem())
+    phi, K, u = (t.cpu().numpy() for t in hx.sample_fields(_cu(th), P.grid(nx, ny, 4), prob))
+    for s in range(S):
+        a, b, c = H.sample_fields(pro, H.Grid(nx, ny, 4), th[s])
+        assert np.abs(phi[..., s].ravel() - np.ravel(a)).max() <= 1e-13
+        assert (np.abs(K[..., s].ravel() - np.ravel(b)) <= 1e-12 * np.abs(np.ravel(b))).all()
+        assert abs(u[s] - c) <= 1e-15 * abs(c)
+
+
+@pytest.mark.parametrize("n_phi,n_logK", [(0, 0), (2, 0), (0, 3), (4, 5)])
+def test_fields_with_fewer_modes(hx, n_phi, n_logK):
+    """Modes beyond the problem's counts contribute nothing: equal to the full set with their
+    coefficients at zero, up to the sign of a zero."""
+    import paper_2403_17018_amd as P
+    th = draw_theta(32, 5)
+    z = th.copy()
+    z[:, n_phi:4] = 0.0
+    z[:, 4 + n_logK:12] = 0.0
+    g = P.grid(20, 10, 1)
+    a = hx.sample_fields(_cu(th), g, P.problem(n_kl_phi=n_phi, n_kl_logK=n_logK))
+    b = hx.sample_fields(_cu(z), g, P.problem())
+    for u, v in zip(a, b):
+        assert torch.equal(u, v)
