@@ -428,8 +428,9 @@ enum henry_prof_class {
                                  nine-point SpMV, units vertex-samples) */
   HENRY_PROF_RESTRICT = 3,    /* fine-grid fused residual + restriction */
   HENRY_PROF_PROLONG = 4,     /* prolongation + correction onto the fine grid */
-  HENRY_PROF_BAND_FACTOR = 5, /* coarse banded LU factorisation */
-  HENRY_PROF_BAND_SOLVE = 6,  /* coarse banded triangular solves */
+  HENRY_PROF_BAND_FACTOR = 5, /* coarsest grid's banded LU factorisation or explicit inverse */
+  HENRY_PROF_BAND_SOLVE = 6,  /* coarsest grid's banded triangular solves, or the cycle's coarse grids
+                                 taken together with it in one launch */
   HENRY_PROF_DENSE_FACTOR = 7,/* dense coarse LU: the pivoted factorisation (units: samples) */
   HENRY_PROF_DENSE_SOLVE = 8, /* dense coarse triangular solves (units: samples) */
   HENRY_PROF_HOST_SYNC = 9,   /* the solver's host round trips (control reads): launches = their

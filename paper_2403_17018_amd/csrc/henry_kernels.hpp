@@ -276,6 +276,42 @@ __device__ __forceinline__ void face_flux(const Phys& P, bool north, double pL, 
   o.cup = cup;
 }
 
+// The left and right sides' terms of cell (i, j): added to its residual and centre block.
+__device__ __forceinline__ void boundary_terms(const Phys& P, int nx, int i, int j, double pP, double cP, double phP,
+                                               double KP, double u_in, double& Rp, double& Rc, double (&D)[4]) {
+  const double rP = P.rho0 + P.drho * cP;
+  const double wb = P.hy / P.hx;
+  // left boundary: prescribed inflow at c_left, diffusive Dirichlet c_left
+  if (i == 0) {
+    const double F = -(P.rho0 + P.drho * P.c_left) * u_in * P.uin_fac * P.hy;
+    Rp += F;
+    Rc += F * P.c_left + 2.0 * rP * phP * P.Dm * (cP - P.c_left) * wb;
+    D[3] += 2.0 * phP * P.Dm * wb * (P.drho * (cP - P.c_left) + rP);
+  }
+  // right boundary: hydrostatic seawater pressure; inflow carries rho1 and c = 1
+  if (i == nx - 1) {
+    const double y = -P.Ly + (j + 0.5) * P.hy;
+    const double pb = -P.rho1 * P.g * y;
+    const double u = -(KP / P.mu) * (pb - pP) / (0.5 * P.hx);
+    const bool inflow = u < 0.0;
+    const double rb = inflow ? P.rho1 : rP;
+    const double F = rb * u * P.hy;
+    const double cb = inflow ? 1.0 : cP;
+    Rp += F;
+    Rc += F * cb;
+    const double dFdp = rb * P.hy * (2.0 * KP / (P.mu * P.hx));
+    const double dFdc = inflow ? 0.0 : P.drho * u * P.hy;
+    D[0] += dFdp;
+    D[1] += dFdc;
+    D[2] += cb * dFdp;
+    D[3] += cb * dFdc + (inflow ? 0.0 : F);
+    if (P.right_dir) {
+      Rc += 2.0 * rP * phP * P.Dm * (cP - 1.0) * wb;
+      D[3] += 2.0 * phP * P.Dm * wb * (P.drho * (cP - 1.0) + rP);
+    }
+  }
+}
+
 // Thread map of the assembly: a workgroup takes ASM_TX x ASM_TY cells (a tile) of one sample
 // block, blockDim = (SX, ASM_TY * ASM_TX) (one row of threads per cell); the grid enumerates
 // (sample block, tile) pairs.  The tile's p, c, phi, K and those of its one-cell halo (the
@@ -416,36 +452,7 @@ __global__ void __launch_bounds__(1024) k_assemble(Map m, Grid2 G, Phys P, const
   } else {
     put(4, 0.0, 0.0, 0.0, 0.0);
   }
-  const double wb = P.hy / P.hx;
-  // left boundary: prescribed inflow at c_left, diffusive Dirichlet c_left
-  if (i == 0) {
-    const double F = -(P.rho0 + P.drho * P.c_left) * u_in * P.uin_fac * P.hy;
-    Rp += F;
-    Rc += F * P.c_left + 2.0 * rP * phP * P.Dm * (cP - P.c_left) * wb;
-    D[3] += 2.0 * phP * P.Dm * wb * (P.drho * (cP - P.c_left) + rP);
-  }
-  // right boundary: hydrostatic seawater pressure; inflow carries rho1 and c = 1
-  if (i == G.nx - 1) {
-    const double y = -P.Ly + (j + 0.5) * P.hy;
-    const double pb = -P.rho1 * P.g * y;
-    const double u = -(KP / P.mu) * (pb - pP) / (0.5 * P.hx);
-    const bool inflow = u < 0.0;
-    const double rb = inflow ? P.rho1 : rP;
-    const double F = rb * u * P.hy;
-    const double cb = inflow ? 1.0 : cP;
-    Rp += F;
-    Rc += F * cb;
-    const double dFdp = rb * P.hy * (2.0 * KP / (P.mu * P.hx));
-    const double dFdc = inflow ? 0.0 : P.drho * u * P.hy;
-    D[0] += dFdp;
-    D[1] += dFdc;
-    D[2] += cb * dFdp;
-    D[3] += cb * dFdc + (inflow ? 0.0 : F);
-    if (P.right_dir) {
-      Rc += 2.0 * rP * phP * P.Dm * (cP - 1.0) * wb;
-      D[3] += 2.0 * phP * P.Dm * wb * (P.drho * (cP - 1.0) + rP);
-    }
-  }
+  boundary_terms(P, G.nx, i, j, pP, cP, phP, KP, u_in, Rp, Rc, D);
   if (WRITE_R) {
     R[id] = Rp;
     R[N + id] = Rc;

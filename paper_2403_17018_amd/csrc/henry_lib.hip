@@ -34,6 +34,7 @@
 #include "henry_coarse.hpp"
 #include "henry_dense.hpp"
 #include "henry_gbsv.hpp"
+#include "henry_tail.hpp"
 #include "henry_mlmc.hpp"
 #include "henry_adjoint.hpp"
 #include "henry_vc.hpp"
@@ -329,6 +330,8 @@ struct Plan {
   DevBuf nhist;            // per sample: last undamped Newton update size, previous |R|^2
   size_t lu_stride;
   int mb;
+  bool inverse = false;    // the coarsest operator is applied as an explicit inverse (henry_tail.hpp)
+  DevBuf tailJ;            // Jacobians of the grids that the cycle takes in one launch
   int* h_ctrl = nullptr;   // pinned mirror of ctrl
   // Compacted sub-batch for the last Newton iterations of a step: same shape and
   // capacity, used with an effective sample count Sa <= S (see Solver::compact_newton).
@@ -524,6 +527,15 @@ static hipGraphExec_t capture_graph(hipStream_t st, F&& f) {
   return ex;
 }
 
+// The grid from which the cycle runs in one launch (k_mg_tail): the finest coarse grid of at
+// most TAIL_CELLS cells with at most TAIL_LEVELS smoothed grids from it down.  The fine grid
+// keeps its own launches (their classes are timed).
+static int tail_start(const Plan& P) {
+  int k = P.nlev - 1;
+  while (k > 1 && P.nlev - k <= TAIL_LEVELS && P.lv[k - 1]->ncell <= TAIL_CELLS) --k;
+  return k;
+}
+
 template <typename T>
 static void plan_alloc_levels(Plan& P) {
   for (int k = 0; k < P.nlev; ++k) {
@@ -552,6 +564,18 @@ static void plan_alloc_levels(Plan& P) {
     P.lu_stride = gb_stride(C.nx, C.ny);
     P.LU.alloc(P.lu_stride * P.S * sizeof(T));
     P.perm.alloc(2 * (size_t)C.ncell * P.S * sizeof(int));
+  } else if (P.nlev > 1 && 2 * C.ncell <= TAIL_NMAX) {
+    // Coarsest grids of up to 64 cells: an explicit inverse (n^2 values a sample) and the cycle's
+    // coarse end in one launch; 8x4 cells took 56 us to factor and 15 us a solve in band form,
+    // serial chains of 32 cells whatever the batch.  Above that the inverse outgrows the
+    // registers of a workgroup, and the banded factors are smaller than it.
+    P.inverse = true;
+    P.lu_stride = 4 * (size_t)C.ncell * C.ncell;
+    P.LU.alloc(P.lu_stride * P.S * sizeof(double));
+    const int k = tail_start(P);
+    size_t n = 0;
+    for (int l = k; l + 1 < P.nlev; ++l) n += 20 * (size_t)P.lv[l]->ncell;
+    if (n) P.tailJ.alloc(n * P.S * sizeof(T));
   } else {
     P.lu_stride = (size_t)C.ncell * (2 * P.mb + 1) * 4;
     P.LU.alloc(P.lu_stride * P.S * sizeof(T));
@@ -782,8 +806,9 @@ struct Solver {
   }
 
   // fine-grid residual/Jacobian, rediscretised coarse Jacobians, coarse factorisation
+  // (tr: for the transposed solves of the adjoint)
   template <typename T>
-  void assemble_all() {
+  void assemble_all(bool tr = false) {
     const Map& m = P.m;
     timed(ctx, st, HENRY_PROF_ASSEMBLE, (long long)P.N, [&] {
       if (spmv32())   // only the FP32 Jacobian: the multigrid and the Krylov products read it
@@ -799,7 +824,8 @@ struct Solver {
                            phys, P.p.as<double>(), P.c.as<double>(), P.c_old.as<double>(), P.phi.as<double>(),
                            P.K.as<double>(), P.uin.as<double>(), P.R.as<double>(), P.J.as<double>(), (float*)nullptr);
     });
-    for (int k = 1; k < P.nlev; ++k) {
+    const int own = P.inverse ? tail_first() : P.nlev;   // grids from here on: k_tail_setup
+    for (int k = 1; k < own; ++k) {
       MGLevel& F = *P.lv[k - 1];
       MGLevel& C = *P.lv[k];
       const double* fp_ = k == 1 ? P.p.as<double>() : F.p.as<double>();
@@ -811,7 +837,34 @@ struct Solver {
                          C.phi.as<double>(), C.K.as<double>(), P.uin.as<double>(), (double*)nullptr, C.J.as<T>(),
                          (float*)nullptr);
     }
-    coarse_factor<T>();
+    if (P.inverse) tail_setup<T>(own, tr);
+    else coarse_factor<T>();
+  }
+
+  template <typename T>
+  void tail_setup(int k, bool tr) {
+    TailSetup<T> A{};
+    A.S = P.S;
+    A.nl = P.nlev - 1 - k;
+    A.transposed = tr;
+    for (int l = 0; l <= A.nl; ++l) {
+      MGLevel& L = *P.lv[k + l];
+      A.nx[l] = L.nx;
+      A.ny[l] = L.ny;
+      A.phi[l] = L.phi.as<double>();
+      A.K[l] = L.K.as<double>();
+    }
+    A.p = k == 1 ? P.p.as<double>() : P.lv[k - 1]->p.as<double>();
+    A.c = k == 1 ? P.c.as<double>() : P.lv[k - 1]->c.as<double>();
+    A.J = P.tailJ.as<T>();
+    A.inv = P.LU.as<double>();
+    const int nc = P.lv[P.nlev - 1]->ncell;
+    const dim3 g(8 * tail_chunk(P.S)), bl(SETUP_THREADS);
+    const uint32_t lds = (uint32_t)setup_lds(A);
+    timed(ctx, st, HENRY_PROF_BAND_FACTOR, (long long)nc * P.S, [&] {
+      if (nc <= 32) launch_timed((k_tail_setup<T, 2, 16>), g, bl, lds, st, A, phys);
+      else launch_timed((k_tail_setup<T, 4, 32>), g, bl, lds, st, A, phys);
+    });
   }
 
   // factors of the coarsest operator: banded LU, or the dense matrix and its pivoted LU
@@ -851,6 +904,32 @@ struct Solver {
     return (const T*)P.J.as<double>();
   }
 
+  // The first grid of the cycle's single launch: a W-cycle or a cycle without post-smoothing has
+  // only its coarsest grid in it.
+  int tail_first() const { return o.mg_cycle == 1 && o.nu_post >= 1 ? tail_start(P) : P.nlev - 1; }
+  template <typename T, bool TR>
+  void tail(int k, const T* b, T* x) {
+    const int nl = P.nlev - 1 - k;
+    TailArgs<T> A{};
+    A.S = P.S;
+    A.nu_pre = o.nu_pre;
+    A.nu_post = o.nu_post;
+    for (int l = 0; l <= nl; ++l) {
+      A.nx[l] = P.lv[k + l]->nx;
+      A.ny[l] = P.lv[k + l]->ny;
+    }
+    A.J = P.tailJ.as<T>();
+    A.inv = P.LU.as<double>();
+    const dim3 g(8 * tail_chunk(P.S)), bl(tail_threads(A, nl));
+    const uint32_t lds = (uint32_t)tail_lds(A, nl);
+    timed(ctx, st, HENRY_PROF_BAND_SOLVE, (long long)P.lv[P.nlev - 1]->ncell * P.S, [&] {
+      if (nl == 0) launch_timed((k_mg_tail<T, TR, 0>), g, bl, lds, st, A, b, x);
+      else if (nl == 1) launch_timed((k_mg_tail<T, TR, 1>), g, bl, lds, st, A, b, x);
+      else if (nl == 2) launch_timed((k_mg_tail<T, TR, 2>), g, bl, lds, st, A, b, x);
+      else launch_timed((k_mg_tail<T, TR, 3>), g, bl, lds, st, A, b, x);
+    });
+  }
+
   // One multigrid cycle x = M^{-1} b on level k (TR: the same cycle built from transposed
   // operators, a preconditioner for J^T): a V-cycle, or a W-cycle (mg_cycle 2: the coarse
   // problem gets two cycles, the second from the first's result).  zero: x starts at 0.
@@ -868,6 +947,10 @@ struct Solver {
       return f(std::integral_constant<int, 1>{});
     };
     auto wide_map = [&](int sp) -> const Map& { return sp == 4 ? P.mw4 : sp == 2 ? P.mw2 : m; };
+    if (P.inverse && k == tail_first()) {
+      tail<T, TR>(k, b, x);
+      return;
+    }
     if (k == P.nlev - 1 && P.csolver == 1) {
       timed(ctx, st, HENRY_PROF_DENSE_SOLVE, (long long)P.S, [&] {
         launch_timed((k_dense_solve<T, TR>), dim3(P.S), dim3(DENSE_SOLVE_THREADS), dense_solve_lds<T>(2 * L.ncell), st,
@@ -1518,7 +1601,7 @@ struct Solver {
         const double* um = seg + (size_t)(n - 1 - n0) * 2 * N;
         load(un);
         HIPCHK(hipMemcpyAsync(P.c_old.p, um + N, N * 8, hipMemcpyDeviceToDevice, st));
-        assemble_all<T>();
+        assemble_all<T>(true);
         // first guess: lambda of the step after (guess 1) or its linear extrapolation
         // 2 lambda^{n+1} - lambda^{n+2} (guess 2); the tolerance stays relative to |rhs|
         const int gmode = std::min(guess, solved);

@@ -82,3 +82,50 @@ def test_fields_with_fewer_modes(hx, n_phi, n_logK):
     b = hx.sample_fields(_cu(z), g, P.problem())
     for u, v in zip(a, b):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("S", [1, 17, 130])
+@pytest.mark.parametrize("nx,ny,coarse,sweeps", [
+    (16, 8, 8, (1, 2)),      # the coarsest grid alone
+    (32, 16, 8, (1, 1)),     # one smoothed grid with it
+    (64, 32, 8, (2, 2)),     # two, the finest of 512 cells, two pre-smoothing sweeps
+    (64, 32, 4, (1, 2)),     # three
+    (128, 64, 2, (1, 2)),    # three in one launch, more above
+    (40, 20, 10, (1, 2)),    # a coarsest grid of 50 cells, odd rows
+])
+def test_coarse_grids_in_one_launch(hx, prec, S, nx, ny, coarse, sweeps):
+    """The multigrid's coarse end (state restriction, Jacobians, inverse of the coarsest operator
+    and the cycle) in launches of one workgroup per sample: the solve against the oracle (1e-8,
+    the workload's bound), and the preconditioner's strength, which a wrong coarse correction
+    would take away: at most 1.35 BiCGStab iterations per Newton iteration on average (1.00 to
+    1.13 with a launch per grid and pass)."""
+    import paper_2403_17018_amd as P
+    from tests.oracle_runs import oracle_batch, rel_inf
+    th = draw_theta(41, S, level=1)
+    g = P.grid(nx, ny, 3)
+    kw = dict(T=36000.0 * 3 / (3 * ny))
+    o = P.solver_opts(mg_precision=prec, coarse_nx=coarse, coarse_ny=max(1, coarse // 2), nu_pre=sweeps[0],
+                      nu_post=sweeps[1])
+    r = hx.solve(_cu(th), g, P.problem(**kw), o)
+    assert r.nfailed == 0
+    pick = sorted({0, S // 2, S - 1})
+    ref = oracle_batch(th[pick], nx, ny, 3, kw)
+    assert rel_inf(r.c_T.permute(2, 0, 1).cpu().numpy()[pick], ref["c"]).max() <= 1e-8
+    newton, bicg = r.stats[:, 0].sum().item(), r.stats[:, 1].sum().item()
+    assert bicg <= 1.35 * newton, (newton, bicg)
+
+
+def test_coarse_grids_in_one_launch_transposed(hx):
+    """The transposed cycle of the adjoint through three smoothed grids in one launch: the
+    gradient against the one with the pivoted coarse solver and a launch per pass."""
+    import paper_2403_17018_amd as P
+    th = _cu(draw_theta(42, 5, level=1))
+    g, prob = P.grid(64, 32, 6), P.problem(T=2250.0)
+    tight = dict(newton_tol=1e-13, krylov_rtol=1e-12, krylov_maxit=200, newton_maxit=60, krylov_rtol_adjoint=1e-12)
+    ref = hx.adjoint(th, g, prob, P.solver_opts(coarse_solver=2, **tight), checkpoint_every=4)[1]
+    for cnx in (4, 8):
+        for prec in (64, 32):
+            gr = hx.adjoint(th, g, prob, P.solver_opts(coarse_nx=cnx, coarse_ny=cnx // 2, mg_precision=prec, **tight),
+                            checkpoint_every=4)[1]
+            assert (gr - ref).abs().max() <= 1e-9 * ref.abs().max(), (cnx, prec)
