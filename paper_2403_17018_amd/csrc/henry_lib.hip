@@ -748,6 +748,8 @@ static void plan_set_samples(Plan& Q, int Sa, int red_blocks, int sample_block) 
 // ---------------------------------------------------------------------------
 // solver
 // ---------------------------------------------------------------------------
+constexpr size_t COMPACT_MIN = 5 << 17;   // see Solver::may_compact
+
 struct Solver {
   henry_ctx* ctx;
   const henry_problem& pr;
@@ -1387,7 +1389,7 @@ struct Solver {
       const int remaining = read_ctrl(1);
       const bool fresh = P.h_ctrl[2] > 0;
       if (remaining > 0) {
-        if (allow_compact && 4 * remaining <= 3 * S) compact_newton<T>(remaining, 1);
+        if (may_compact() && 4 * remaining <= 3 * S) compact_newton<T>(remaining, 1);
         else newton_loop<T>(1, fresh);
       }
     } else {
@@ -1415,7 +1417,7 @@ struct Solver {
       if (fresh) assemble_all<T>();
       else assemble_residual();
       // predictive stops can leave few samples iterating before the solve: compact first
-      const bool can_compact = allow_compact && o.newton_predict > 0.0 && it + 1 < o.newton_maxit;
+      const bool can_compact = may_compact() && o.newton_predict > 0.0 && it + 1 < o.newton_maxit;
       const int left = bicgstab<T, false>(P.R.as<double>(), -1.0, P.ndone.as<int>(), o.krylov_rtol, true,
                                           can_compact ? (3 * S) / 4 : -1);
       if (left >= 0) {
@@ -1426,7 +1428,7 @@ struct Solver {
       remaining = read_ctrl(1);
       // chord iteration next (same J) while every iterating sample's update was small
       fresh = P.h_ctrl[2] > 0;
-      if (allow_compact && remaining > 0 && 4 * remaining <= 3 * S && it + 1 < o.newton_maxit) {
+      if (may_compact() && remaining > 0 && 4 * remaining <= 3 * S && it + 1 < o.newton_maxit) {
         compact_newton<T>(remaining, it + 1);
         return;
       }
@@ -1436,7 +1438,15 @@ struct Solver {
                          P.status.as<int>());
   }
 
+  // Compaction pays where the fine launches are bound by their cells: below COMPACT_MIN
+  // cell-samples they are bound by launch and memory latency, which fewer samples do not
+  // shorten, and the gathers and scatters (some 20 launches) and the Jacobian assembled anew for
+  // the smaller batch are a loss.  With and without, ms a solve: 65 536 cell-samples 43.0 and
+  // 38.9 (level 0), 42.2 and 38.9 (level 1); 262 144: 56.0 and 51.2, 59.0 and 55.4, 71.7 and 67.3
+  // (level 2); 524 288: 76.4 and 73.8, 89.7 and 87.6 (level 3), 61.0 and 58.6 (FP32 cycle);
+  // 681 984: 108.9 and 112.1; 819 200: 105.1 and 107.1; 2 097 152: 158.9 and 172.3.
   bool allow_compact = true;
+  bool may_compact() const { return allow_compact && P.N >= COMPACT_MIN; }
 
   // Gather the Sa samples still iterating into the compact sub-plan, finish their Newton
   // iterations there and scatter state, status and statistics back.
