@@ -720,6 +720,13 @@ __global__ void k_convert(size_t n, const TI* __restrict__ a, TO* __restrict__ b
 // per-sample scalar slots
 enum { SC_RHO = 0, SC_ALPHA, SC_OMEGA, SC_BETA, SC_R0, SC_RNORM, SC_ACTIVE, SC_ITS, SC_HALF, SC_NSLOT };
 
+// Clears the control counters (at most 16): called in a kernel of one or more whole blocks that
+// runs before the finalisation kernel that counts into them, which saves a launch for it.
+__device__ __forceinline__ void clear_ctrl(int* ctrl, int n = 16) {
+  const int t = threadIdx.y * blockDim.x + threadIdx.x;
+  if (blockIdx.x == 0 && t < n) ctrl[t] = 0;
+}
+
 // r = sign * R (zero for samples with ndone[s] set; ndone may be NULL), rhat = r, p = r; partial |r|^2
 // b = sign * R (0 for samples flagged in ndone); r0 = b - A x0, where A x0 is given in ax
 // (warm start) or x0 = 0 (ax == nullptr).  Writes p = r0 (the first iteration reads r0
@@ -728,8 +735,9 @@ enum { SC_RHO = 0, SC_ALPHA, SC_OMEGA, SC_BETA, SC_R0, SC_RNORM, SC_ACTIVE, SC_I
 __global__ void __launch_bounds__(256) k_bicg_init(Map m, int ncell, const double* __restrict__ R, double sign,
                                                    const double* __restrict__ ax, const int* __restrict__ ndone,
                                                    double* __restrict__ rhat, double* __restrict__ p,
-                                                   double* __restrict__ part) {
+                                                   double* __restrict__ part, int* __restrict__ ctrl) {
   __shared__ double lds[2 * 256];
+  clear_ctrl(ctrl);
   const int sblk = blockIdx.x % m.nsb, cblk = blockIdx.x / m.nsb;
   const int s = sblk * m.SX + threadIdx.x;
   const bool sv = s < m.S;
@@ -859,8 +867,10 @@ __global__ void __launch_bounds__(256) k_bicg_xr(Map m, int ncell, int first, co
                                                  const TP* __restrict__ ph, const TP* __restrict__ sh,
                                                  const double* __restrict__ sv_, const double* __restrict__ t,
                                                  const double* __restrict__ rhat, double* __restrict__ x,
-                                                 double* __restrict__ r, double* __restrict__ part) {
+                                                 double* __restrict__ r, double* __restrict__ part,
+                                                 int* __restrict__ ctrl) {
   __shared__ double lds[2 * 256];
+  clear_ctrl(ctrl);
   const int sblk = blockIdx.x % m.nsb, cblk = blockIdx.x / m.nsb;
   const int s = sblk * m.SX + threadIdx.x;
   const bool sv = s < m.S;
@@ -981,8 +991,9 @@ __global__ void __launch_bounds__(64 * FIN_Y) k_fin_init(Map m, const double* __
 
 __global__ void __launch_bounds__(64 * FIN_Y) k_fin_alpha(Map m, const double* __restrict__ part,
                                                           double* __restrict__ sc, double breakdown,
-                                                          int* __restrict__ status) {
+                                                          int* __restrict__ status, int* __restrict__ ctrl) {
   __shared__ double lds[64 * FIN_Y];
+  clear_ctrl(ctrl);
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   double v[1];
   reduce_partials<1>(m, part, s, v, lds);
@@ -1085,8 +1096,9 @@ __global__ void __launch_bounds__(64 * FIN_Y) k_fin_rho(Map m, const double* __r
 // ==========================================================================
 // partial max |dp|, |dc| per sample
 __global__ void __launch_bounds__(256) k_delta_max(Map m, int ncell, const double* __restrict__ d,
-                                                   double* __restrict__ part) {
+                                                   double* __restrict__ part, int* __restrict__ ctrl) {
   __shared__ double lds[2 * 256];
+  clear_ctrl(ctrl);
   const int sblk = blockIdx.x % m.nsb, cblk = blockIdx.x / m.nsb;
   const int s = sblk * m.SX + threadIdx.x;
   const bool sv = s < m.S;

@@ -240,11 +240,13 @@ static dim3 block_of(const Map& m) { return dim3(m.SX, m.CY); }
 // the assembly's tiles: one workgroup per (sample block, ASM_TX x ASM_TY cells)
 static dim3 asm_grid(const Map& m, const Grid2& G) { return dim3((unsigned)((long long)m.nsb * asm_tiles(G.nx, G.ny))); }
 static dim3 asm_block(const Map& m) { return dim3(m.SX, ASM_T); }
-// Finalisation launch shape: blockDim.x = min(64, S rounded up to a power of 2) samples,
-// the rest of the 64 * FIN_Y threads split each sample's partial sums.
+// Finalisation launch shape: blockDim.x = min(16, S rounded up to a power of 2) samples (16 are
+// a 128-byte line of a partial array), the rest of the 64 * FIN_Y threads split each sample's
+// partial sums.  These launches are bound by their chain of loads: with 64 samples a block they
+// took 9.8 to 13 us at level 1 x 64 (512 partials, one block), 4.3 to 7 us with 16.
 static int fin_sx(int S) {
   int x = 1;
-  while (x < S && x < 64) x <<= 1;
+  while (x < S && x < 16) x <<= 1;
   return x;
 }
 static dim3 fin_grid(int S) { return dim3((unsigned)((S + fin_sx(S) - 1) / fin_sx(S))); }
@@ -1094,11 +1096,10 @@ struct Solver {
                       black_exact ? (const double*)P.vp.as<double>() : nullptr);
     });
     hipLaunchKernelGGL(k_fin_alpha, fg, fb, 0, st, m, P.part.as<double>(), sc, o.krylov_breakdown,
-                       P.status.as<int>());
+                       P.status.as<int>(), P.ctrl.as<int>());
     // r0 is held in p (unchanged until the second iteration's p update)
     hipLaunchKernelGGL(k_bicg_s, rg, bl, 0, st, m, P.G.ncell, sc, first ? P.vp.as<double>() : P.vr.as<double>(),
                        P.vv.as<double>(), P.vs.as<double>(), P.part.as<double>());
-    zero_ctrl();
     hipLaunchKernelGGL(k_fin_half, fg, fb, 0, st, m, P.part.as<double>(), sc, rtol2, P.ctrl.as<int>());
   }
 
@@ -1119,12 +1120,11 @@ struct Solver {
       hipLaunchKernelGGL(k_bicg_xr<float>, grid_red(m), block_of(m), 0, st, m, P.G.ncell, first, P.sc.as<double>(),
                          reinterpret_cast<const float*>(P.vph.p), reinterpret_cast<const float*>(P.vsh.p),
                          P.vs.as<double>(), P.vt.as<double>(), rh, P.vx.as<double>(), P.vr.as<double>(),
-                         P.part.as<double>());
+                         P.part.as<double>(), P.ctrl.as<int>());
     else
       hipLaunchKernelGGL(k_bicg_xr<double>, grid_red(m), block_of(m), 0, st, m, P.G.ncell, first, P.sc.as<double>(),
                          P.vph.as<double>(), P.vsh.as<double>(), P.vs.as<double>(), P.vt.as<double>(), rh,
-                         P.vx.as<double>(), P.vr.as<double>(), P.part.as<double>());
-    zero_ctrl();
+                         P.vx.as<double>(), P.vr.as<double>(), P.part.as<double>(), P.ctrl.as<int>());
     hipLaunchKernelGGL(k_fin_rho, fin_grid(P.S), fin_block(P.S), 0, st, m, P.part.as<double>(), P.sc.as<double>(),
                        rtol2, P.status.as<int>(), P.ctrl.as<int>());
   }
@@ -1138,8 +1138,8 @@ struct Solver {
     const dim3 rg = grid_red(m), bl = block_of(m);
     if (warm) spmv<1, TR, double>(P.vx.as<double>(), P.vv.as<double>(), P.vx.as<double>(), nullptr);
     hipLaunchKernelGGL(k_bicg_init, rg, bl, 0, st, m, P.G.ncell, rhs, sign, warm ? (const double*)P.vv.as<double>() : nullptr,
-                       mask, alias_rhat ? (double*)nullptr : P.vrh.as<double>(), P.vp.as<double>(), P.part.as<double>());
-    zero_ctrl();
+                       mask, alias_rhat ? (double*)nullptr : P.vrh.as<double>(), P.vp.as<double>(), P.part.as<double>(),
+                       P.ctrl.as<int>());
     hipLaunchKernelGGL(k_fin_init, fin_grid(P.S), fin_block(P.S), 0, st, m, P.part.as<double>(), P.sc.as<double>(),
                        P.ctrl.as<int>(), newton ? P.nhist.as<double>() : (double*)nullptr, mask,
                        o.newton_tol * o.newton_predict, rtol2, alias_rhat ? sign : 1.0);
@@ -1310,8 +1310,7 @@ struct Solver {
     const Map& m = P.m;
     const int S = P.S;
     hipLaunchKernelGGL(k_delta_max, grid_red(m), block_of(m), 0, st, m, P.G.ncell, P.vx.as<double>(),
-                       P.part.as<double>());
-    zero_ctrl();
+                       P.part.as<double>(), P.ctrl.as<int>());
     hipLaunchKernelGGL(k_fin_newton, fin_grid(S), fin_block(S), 0, st, m, P.part.as<double>(),
                        pr.rho0 * pr.g * pr.Ly, o.newton_tol, o.newton_dc_max, P.lam.as<double>(), P.ndone.as<int>(),
                        P.status.as<int>(), P.stats.as<double>(), P.ctrl.as<int>(), P.nhist.as<double>(),
@@ -1521,7 +1520,7 @@ struct Solver {
       if (B.series) {
         hipLaunchKernelGGL(k_series, grid_red(P.m), block_of(P.m), 0, st, P.m, P.G, phys, P.c.as<double>(),
                            P.part.as<double>());
-        hipLaunchKernelGGL(k_fin_series, fin_grid(S), fin_block(S), 0, st, P.m, P.part.as<double>(),
+        hipLaunchKernelGGL(k_fin_series, dim3(fin_grid(S).x, NSERIES), fin_block(S), 0, st, P.m, P.part.as<double>(),
                            B.series + (size_t)n * NSERIES * S);
       }
     }
@@ -2837,7 +2836,6 @@ struct VCSolver {
     ctx->host_sync_ns += std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - t0).count();
     return *h_ctrl;
   }
-  void zero_ctrl() { hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, (size_t)1, ctrl.as<int>()); }
   template <int NQ>
   void dots(VCPairs ab) {
     hipLaunchKernelGGL((k_vc_dots<NQ>), grid_red(m), block_of(m), 0, st, m, nv, ab, part.as<double>());
@@ -2882,9 +2880,8 @@ struct VCSolver {
     double* scp = sc.as<double>();
     const dim3 fg = fin_grid(S), fb = fin_block(S);
     hipLaunchKernelGGL(k_vc_rhs, g2(), dim3(256), 0, st, 2 * NV, NV, S, (const double*)scp, (const double*)R.as<double>(),
-                       x.as<double>(), r.as<double>(), pv.as<double>(), rh.as<double>());
+                       x.as<double>(), r.as<double>(), pv.as<double>(), rh.as<double>(), ctrl.as<int>());
     dots<1>(VCPairs{{r.as<double>(), nullptr, nullptr}, {r.as<double>(), nullptr, nullptr}});
-    zero_ctrl();
     hipLaunchKernelGGL(k_vc_bicg_start, fg, fb, 0, st, m, (const double*)part.as<double>(), scp, ctrl.as<int>(),
                        o.newton_tol * o.newton_predict);
     if (read_ctrl() == 0) return 0;
@@ -2921,9 +2918,8 @@ struct VCSolver {
     hipLaunchKernelGGL(k_vc_bicg_omega, fg, fb, 0, st, m, (const double*)part.as<double>(), scp, rtol2);
     hipLaunchKernelGGL(k_vc_update_xr, g2(), dim3(256), 0, st, 2 * NV, NV, S, (const double*)scp,
                        (const double*)ph.as<double>(), (const double*)sh.as<double>(), (const double*)sv.as<double>(),
-                       (const double*)t.as<double>(), x.as<double>(), r.as<double>());
+                       (const double*)t.as<double>(), x.as<double>(), r.as<double>(), ctrl.as<int>());
     dots<2>(VCPairs{{rh.as<double>(), r.as<double>(), nullptr}, {r.as<double>(), r.as<double>(), nullptr}});
-    zero_ctrl();
     hipLaunchKernelGGL(k_vc_bicg_beta, fg, fb, 0, st, m, (const double*)part.as<double>(), scp, rtol2,
                        status.as<int>(), ctrl.as<int>());
     hipLaunchKernelGGL(k_vc_update_p, g2(), dim3(256), 0, st, 2 * NV, NV, S, (const double*)scp,
@@ -2975,8 +2971,7 @@ struct VCSolver {
         coarse_assemble(it == 0);
         bicgstab();
         hipLaunchKernelGGL(k_vc_absmax, grid_red(m), block_of(m), 0, st, m, nv, (const double*)x.as<double>(),
-                           part.as<double>());
-        zero_ctrl();
+                           part.as<double>(), ctrl.as<int>());
         hipLaunchKernelGGL(k_vc_newton_fin, fg, fb, 0, st, m, (const double*)part.as<double>(), scp, o.newton_tol, p_ref,
                            o.newton_dc_max, status.as<int>(), ctrl.as<int>());
         hipLaunchKernelGGL(k_vc_newton_update, dim3((unsigned)((NV + 255) / 256)), dim3(256), 0, st, NV, S,

@@ -179,22 +179,14 @@ __global__ void __launch_bounds__(256) k_series(Map m, Grid2 G, Phys P, const do
   }
 }
 
-// out[q][s] = sum of the partials (fixed order), q < NSERIES
+// out[q][s] = sum of the partials (fixed order), q < NSERIES, quantity q in row q of the grid
 __global__ void __launch_bounds__(64 * FIN_Y) k_fin_series(Map m, const double* __restrict__ part,
                                                            double* __restrict__ out) {
-  __shared__ double lds[4 * 64 * FIN_Y];
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  for (int q0 = 0; q0 < 16; q0 += 4) {
-    double a[4];
-    reduce_partials<4>(m, part + (size_t)q0 * m.ncb * m.S, s, a, lds);
-    if (threadIdx.y == 0 && s < m.S) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) out[(size_t)(q0 + q) * m.S + s] = a[q];
-    }
-  }
+  __shared__ double lds[64 * FIN_Y];
+  const int s = blockIdx.x * blockDim.x + threadIdx.x, q = blockIdx.y;
   double a[1];
-  reduce_partials<1>(m, part + (size_t)16 * m.ncb * m.S, s, a, lds);
-  if (threadIdx.y == 0 && s < m.S) out[(size_t)16 * m.S + s] = a[0];
+  reduce_partials<1>(m, part + (size_t)q * m.ncb * m.S, s, a, lds);
+  if (threadIdx.y == 0 && s < m.S) out[(size_t)q * m.S + s] = a[0];
 }
 
 // Fixed-order tree sum over 256 threads.

@@ -339,8 +339,9 @@ __global__ void __launch_bounds__(256) k_vc_dots(Map m, int nv, VCPairs ab, doub
 
 // Per-sample max |dp| and |dc| partials (for the Newton damping and stopping test)
 __global__ void __launch_bounds__(256) k_vc_absmax(Map m, int nv, const double* __restrict__ d,
-                                                   double* __restrict__ part) {
+                                                   double* __restrict__ part, int* __restrict__ ctrl) {
   __shared__ double lds[2 * 256];
+  clear_ctrl(ctrl, 1);
   const int sblk = blockIdx.x % m.nsb, cblk = blockIdx.x / m.nsb;
   const int s = sblk * m.SX + threadIdx.x;
   const bool sv = s < m.S;
@@ -487,7 +488,8 @@ __global__ void k_vc_axpy_s(size_t n2, size_t NV, int S, const double* __restric
 __global__ void k_vc_update_xr(size_t n2, size_t NV, int S, const double* __restrict__ sc,
                                const double* __restrict__ ph, const double* __restrict__ sh,
                                const double* __restrict__ sv, const double* __restrict__ t, double* __restrict__ x,
-                               double* __restrict__ r) {
+                               double* __restrict__ r, int* __restrict__ ctrl) {
+  clear_ctrl(ctrl, 1);
   const size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
   if (e >= n2) return;
   int s;
@@ -512,7 +514,8 @@ __global__ void k_vc_update_p(size_t n2, size_t NV, int S, const double* __restr
 // right-hand side b = -R for samples still in Newton (0 for converged ones); x = 0, r = p = b
 __global__ void k_vc_rhs(size_t n2, size_t NV, int S, const double* __restrict__ sc, const double* __restrict__ R,
                          double* __restrict__ x, double* __restrict__ r, double* __restrict__ p,
-                         double* __restrict__ rh) {
+                         double* __restrict__ rh, int* __restrict__ ctrl) {
+  clear_ctrl(ctrl, 1);
   const size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
   if (e >= n2) return;
   int s;
