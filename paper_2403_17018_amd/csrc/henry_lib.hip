@@ -2605,7 +2605,7 @@ int mlmc_optimal_samples(int L, const double* V_l, const double* s_l, double eps
 // ---------------------------------------------------------------------------
 namespace {
 
-// The coarsest vertex grid is factored with partial pivoting in one workgroup per sample; its
+// The coarsest vertex grid is inverted with partial pivoting in one workgroup per sample; its
 // dense matrix may need more LDS than a launch gets by default: raise the limit once per device.
 template <typename K>
 static void vc_lds_prepare(K* kernel, size_t bytes) {
@@ -2619,7 +2619,10 @@ static void vc_lds_prepare(K* kernel, size_t bytes) {
                              (int)bytes));
   if (dev >= 0 && dev < 64) done[dev] = true;
 }
-static size_t vc_dense_lds(int n, size_t tsz) { return (size_t)n * n * tsz + (size_t)n * sizeof(double) + 16; }
+static size_t vc_dense_lds(int n) {   // the matrix and the row order; the inverse's columns too where they fit
+  const size_t a = (size_t)n * n * sizeof(double) + (size_t)n * sizeof(int) + 16, x = (size_t)n * n * sizeof(double);
+  return a + x <= VC_LDS_MAX ? a + x : a;
+}
 
 // one coarse level of the vertex-grid multigrid (the finest level is the solver's own data)
 struct VCLevel {
@@ -2640,7 +2643,9 @@ struct VCSolver {
   Grid2 E;
   Phys P;
   size_t NV;
-  DevBuf phi, K, uin, p, c, c_old, R, J, x, r, rh, pv, ph, v, sv, sh, t, part, sc, ctrl, status, mgr, LUc, pivc;
+  DevBuf phi, K, uin, p, c, c_old, R, J, x, r, rh, pv, ph, v, sv, sh, t, part, sc, ctrl, status, mgr;
+  DevBuf tailJ, coarseJ, inv;   // the cycle's coarse end (k_vc_tail): its Jacobians, the coarsest's, its inverse
+  int tail0 = 1;                // the level from which it runs
   // multigrid precision (mg_precision): 64, or 32 with the Jacobian stored in FP32 for the
   // cycle and the Krylov products, and the cycle's input and output rounded at its ends (mb, mx)
   int prec;
@@ -2702,15 +2707,22 @@ struct VCSolver {
     if (!lv.empty()) {
       const int n = 2 * lv.back()->nv;
       mgr.alloc(2 * NV * tsz);
-      LUc.alloc((size_t)n * n * S * tsz);
-      pivc.alloc((size_t)n * S * sizeof(int));
-      if (prec == 32) {
-        vc_lds_prepare(&k_vc_dense_factor<float>, vc_dense_lds(VC_DENSE_MAX, 4));
-        vc_lds_prepare(&k_vc_dense_solve<float>, vc_dense_lds(VC_DENSE_MAX, 4));
-      } else {
-        vc_lds_prepare(&k_vc_dense_factor<double>, vc_dense_lds(VC_DENSE_MAX, 8));
-        vc_lds_prepare(&k_vc_dense_solve<double>, vc_dense_lds(VC_DENSE_MAX, 8));
+      // the coarsest level, and those above it whose vertices fit the workgroup's threads
+      const int nl = (int)lv.size();
+      int threads = 0;
+      tail0 = nl;
+      while (tail0 > 1 && nl - tail0 < VC_TAIL_LEVELS &&
+             threads + vc_wave_threads(lv[tail0 - 2]->nv) <= VC_TAIL_THREADS) {
+        threads += vc_wave_threads(lv[tail0 - 2]->nv);
+        --tail0;
       }
+      size_t nj = 0;
+      for (int k = tail0; k < nl; ++k) nj += 36 * (size_t)lv[k - 1]->nv;
+      if (nj) tailJ.alloc(nj * S * tsz);
+      coarseJ.alloc(36 * (size_t)lv.back()->nv * S * tsz);
+      inv.alloc((size_t)n * n * S * 8);
+      if (prec == 32) vc_lds_prepare(&k_vc_dense_inverse<float>, VC_LDS_MAX);
+      else vc_lds_prepare(&k_vc_dense_inverse<double>, VC_LDS_MAX);
     }
     if (prec == 32) {
       mb.alloc(2 * NV * 4);
@@ -2736,10 +2748,11 @@ struct VCSolver {
       Ef = L->E;
     }
   }
-  // Coarse operators at the injected state.  The coarsest grid's operator serves only its LU
-  // factors, which are refreshed at the first Newton iteration of each step (refresh_coarsest)
+  // Coarse operators at the injected state.  The coarsest grid's operator serves only its
+  // inverse, which is refreshed at the first Newton iteration of each step (refresh_coarsest)
   // and kept for the step's later iterations: the preconditioner changes, not the fixed point.
   void coarse_assemble(bool refresh_coarsest) {
+    if (lv.empty()) return;
     if (prec == 32) coarse_assemble_t<float>(refresh_coarsest);
     else coarse_assemble_t<double>(refresh_coarsest);
   }
@@ -2747,8 +2760,8 @@ struct VCSolver {
   void coarse_assemble_t(bool refresh_coarsest) {
     const double *pf = p.as<double>(), *cf = c.as<double>(), *cof = c_old.as<double>();
     Grid2 Ef = E;
-    for (auto& L : lv) {
-      if (L == lv.back() && !refresh_coarsest) return;
+    for (int k = 1; k < tail0; ++k) {
+      auto& L = lv[k - 1];
       hipLaunchKernelGGL(k_vc_inject, grid_cells(L->m, L->nv), block_of(L->m), 0, st, L->m, L->E, Ef, pf, cf, cof,
                          L->p.as<double>(), L->c.as<double>(), L->co.as<double>());
       Phys Pl = L->P;
@@ -2763,11 +2776,25 @@ struct VCSolver {
       cof = L->co.as<double>();
       Ef = L->E;
     }
-    if (!lv.empty()) {
-      const VCLevel& Lc = *lv.back();
-      hipLaunchKernelGGL(k_vc_dense_factor<T>, dim3(S), dim3(256), vc_dense_lds(2 * Lc.nv, sizeof(T)), st, S, Lc.E,
-                         (const T*)Lc.J.as<T>(), LUc.as<T>(), pivc.as<int>());
+    VCTailSetup<T> A{};
+    A.S = S;
+    A.nl = (int)lv.size() - tail0;
+    for (int l = 0; l <= A.nl; ++l) {
+      const VCLevel& L = *lv[tail0 - 1 + l];
+      A.nx[l] = L.nx;
+      A.ny[l] = L.ny;
+      A.phi[l] = L.phi.as<double>();
+      A.K[l] = L.K.as<double>();
     }
+    A.p = pf;
+    A.c = cf;
+    A.J = tailJ.as<T>();
+    A.Jc = refresh_coarsest ? coarseJ.as<T>() : nullptr;
+    if (A.nl > 0 || refresh_coarsest)
+      hipLaunchKernelGGL(k_vc_tail_setup<T>, dim3(8 * tail_chunk(S)), dim3(256), vc_setup_lds(A), st, A, P);
+    if (refresh_coarsest)
+      hipLaunchKernelGGL(k_vc_dense_inverse<T>, dim3(S), dim3(256), vc_dense_lds(2 * lv.back()->nv), st, S, lv.back()->E,
+                         (const T*)coarseJ.as<T>(), inv.as<double>());
   }
   // one V-cycle on level k (0: the fine grid) for J_k x = b from x = 0, in precision T
   template <typename T>
@@ -2777,9 +2804,20 @@ struct VCSolver {
     const Grid2& Ek = k > 0 ? L->E : E;
     const int nvk = k > 0 ? L->nv : nv;
     const T* Jk = k > 0 ? L->J.as<T>() : J.as<T>();
-    if (k == (int)lv.size()) {   // coarsest: the direct solve with this step's factors
-      hipLaunchKernelGGL(k_vc_dense_solve<T>, dim3(S), dim3(64), vc_dense_lds(2 * nvk, sizeof(T)), st, S, Ek,
-                         (const T*)LUc.as<T>(), (const int*)pivc.as<int>(), b, xo);
+    if (k == tail0) {
+      VCTail<T> A{};
+      A.S = S;
+      A.nl = (int)lv.size() - tail0;
+      A.nu_pre = std::max(1, o.nu_pre);
+      A.nu_post = std::max(1, o.nu_post);
+      for (int l = 0; l <= A.nl; ++l) {
+        A.nx[l] = lv[tail0 - 1 + l]->nx;
+        A.ny[l] = lv[tail0 - 1 + l]->ny;
+      }
+      A.J = tailJ.as<T>();
+      A.inv = inv.as<double>();
+      hipLaunchKernelGGL(k_vc_tail<T>, dim3(8 * tail_chunk(S)), dim3(vc_tail_threads(A.nx, A.ny, A.nl)), vc_tail_lds(A),
+                         st, A, b, xo);
       return;
     }
     // x starts at zero: the first forward sweep skips the colours not yet swept, so x is not

@@ -8,6 +8,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "henry_tail.hpp"
+
 namespace henry {
 
 constexpr int VC_BLK = 9;
@@ -82,8 +84,115 @@ __device__ __forceinline__ void vc_face(int f, const double (&pk)[4], const doub
   }
 }
 
-// Residual (and Jacobian) of one implicit-Euler step at every vertex: a thread per (vertex,
-// sample) gathers the two faces of each element around its vertex that bound its box.
+// Residual (Rp, Rc) and Jacobian row Jb of one implicit-Euler step at vertex (i, j): gathers the
+// two faces of each element around the vertex that bound its box.  pc(i, j, p, c) and
+// el(i, j, phi, K) give the state of a vertex and the fields of an element of the grid, co the
+// vertex's old concentration, u_in the sample's inflow (times P.uin_fac).  What the caller does
+// not use of R and J is not computed.
+template <bool WANT_J, typename PC, typename EL>
+__device__ __forceinline__ void vc_row(const Phys& P, int nx, int ny, int i, int j, PC&& pc, EL&& el, double co,
+                                       double u_in, double& Rp, double& Rc, double (&Jb)[36]) {
+  const double y = -P.Ly + j * P.hy;
+#pragma unroll
+  for (int q = 0; q < 36; ++q) Jb[q] = 0.0;
+  Rp = Rc = 0.0;
+  if (i == nx) {   // seaside: p = -rho1 g y, c = 1
+    double p, c;
+    pc(i, j, p, c);
+    Rp = p + P.rho1 * P.g * y;
+    Rc = c - 1.0;
+    Jb[16] = 1.0;
+    Jb[19] = 1.0;
+    return;
+  }
+  double pn[3][3], cn[3][3];
+#pragma unroll
+  for (int dj = -1; dj <= 1; ++dj)
+#pragma unroll
+    for (int di = -1; di <= 1; ++di) {
+      const int qi = i + di, qj = j + dj;
+      const bool in = qi >= 0 && qi <= nx && qj >= 0 && qj <= ny;
+      double p, c;
+      pc(in ? qi : i, in ? qj : j, p, c);
+      pn[dj + 1][di + 1] = in ? p : 0.0;
+      cn[dj + 1][di + 1] = in ? c : 0.0;
+    }
+  // every load of the vertex is issued here, before any arithmetic: the four elements' phi and K
+  // too (an element outside the grid reads element (0, 0) and is skipped below).  Issued where
+  // they are used, each would be a separate trip to memory, and at two wavefronts per SIMD
+  // little of that latency is hidden.
+  double phi_e[4], K_e[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int xi = i + (t & 1) - 1, xj = j + (t >> 1) - 1;
+    const bool ok = xi >= 0 && xi < nx && xj >= 0 && xj < ny;
+    el(ok ? xi : 0, ok ? xj : 0, phi_e[t], K_e[t]);
+  }
+  double box = 0.0;
+#pragma unroll
+  for (int ej = -1; ej <= 0; ++ej)
+#pragma unroll
+    for (int ei = -1; ei <= 0; ++ei) {
+      const int xi = i + ei, xj = j + ej;
+      if (xi < 0 || xi >= nx || xj < 0 || xj >= ny) continue;
+      const int t = (ej + 1) * 2 + (ei + 1);
+      const double phie = phi_e[t], Ke = K_e[t];
+      box += 0.25 * P.hx * P.hy * phie;
+      const int kv = ei == 0 ? (ej == 0 ? 0 : 3) : (ej == 0 ? 1 : 2);   // local index of v
+      double pk[4], ck[4];
+      int dik[4], djk[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        dik[k] = ei + ((k == 1 || k == 2) ? 1 : 0);
+        djk[k] = ej + ((k == 2 || k == 3) ? 1 : 0);
+        pk[k] = pn[djk[k] + 1][dik[k] + 1];
+        ck[k] = cn[djk[k] + 1][dik[k] + 1];
+      }
+      // the two faces of this element that touch local vertex kv
+      const int f0 = kv == 0 ? 0 : kv == 1 ? 0 : kv == 2 ? 1 : 2;
+      const int f1 = kv == 0 ? 3 : kv == 1 ? 1 : kv == 2 ? 2 : 3;
+#pragma unroll
+      for (int ff = 0; ff < 2; ++ff) {
+        const int f = ff == 0 ? f0 : f1;
+        int a, b, axis;
+        double s_, t_;
+        vc_face_geom(f, a, b, axis, s_, t_);
+        const double sgn = a == kv ? 1.0 : -1.0;   // out of v's box
+        double F, G, dFp[4], dFc[4], dGp[4], dGc[4];
+        vc_face(f, pk, ck, Ke, phie, P, F, G, dFp, dFc, dGp, dGc);
+        Rp += sgn * F;
+        Rc += sgn * G;
+        if (WANT_J) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int bl = (djk[k] + 1) * 3 + (dik[k] + 1);
+            Jb[bl * 4 + 0] += sgn * dFp[k];
+            Jb[bl * 4 + 1] += sgn * dFc[k];
+            Jb[bl * 4 + 2] += sgn * dGp[k];
+            Jb[bl * 4 + 3] += sgn * dGc[k];
+          }
+        }
+      }
+    }
+  const double cv = cn[1][1];
+  Rp += box * (P.drho * (cv - co)) / P.tau;
+  Rc += box * ((P.rho0 + P.drho * cv) * cv - (P.rho0 + P.drho * co) * co) / P.tau;
+  Jb[17] += box * P.drho / P.tau;
+  Jb[19] += box * (P.rho0 + 2.0 * P.drho * cv) / P.tau;
+  if (i == 0) {   // inflow side: mass flux rho(c_left) u_in enters; c = c_left
+    const double len = (j == 0 || j == ny) ? 0.5 * P.hy : P.hy;
+    Rp -= (P.rho0 + P.drho * P.c_left) * u_in * P.uin_fac * len;
+    Rc = cv - P.c_left;
+#pragma unroll
+    for (int bl = 0; bl < VC_BLK; ++bl) {
+      Jb[bl * 4 + 2] = 0.0;
+      Jb[bl * 4 + 3] = 0.0;
+    }
+    Jb[19] = 1.0;
+  }
+}
+
+// Residual (and Jacobian) of one implicit-Euler step: one thread per (vertex, sample).
 // E: the element grid; phi, K: [element][S]; uin: [S] (times P.uin_fac).
 // TJ: the Jacobian's storage type (float for the FP32 multigrid and its Krylov products)
 template <bool WRITE_J, typename TJ = double>
@@ -99,107 +208,18 @@ __global__ void __launch_bounds__(256) k_vc_assemble(Map m, Grid2 E, Phys P, con
   const size_t NV = (size_t)nv * S;
   const int j = v / nvx, i = v - j * nvx;
   const size_t id = (size_t)v * S + s;
-  const double y = -P.Ly + j * P.hy;
-  double Jb[36];
-#pragma unroll
-  for (int q = 0; q < 36; ++q) Jb[q] = 0.0;
-  double Rp = 0.0, Rc = 0.0;
-  if (i == E.nx) {   // seaside: p = -rho1 g y, c = 1
-    Rp = p[id] + P.rho1 * P.g * y;
-    Rc = c[id] - 1.0;
-    Jb[16] = 1.0;
-    Jb[19] = 1.0;
-  } else {
-    double pn[3][3], cn[3][3];
-#pragma unroll
-    for (int dj = -1; dj <= 1; ++dj)
-#pragma unroll
-      for (int di = -1; di <= 1; ++di) {
-        const int qi = i + di, qj = j + dj;
-        const bool in = qi >= 0 && qi < nvx && qj >= 0 && qj < nvy;
-        const size_t q = ((size_t)(in ? qj : j) * nvx + (in ? qi : i)) * S + s;
-        pn[dj + 1][di + 1] = in ? p[q] : 0.0;
-        cn[dj + 1][di + 1] = in ? c[q] : 0.0;
-      }
-    // every load of the vertex is issued here, before any arithmetic: the four elements'
-    // phi and K (an element outside the grid reads element 0 of the sample and is skipped
-    // below), the old concentration and the sample's inflow.  Issued where they are used,
-    // each would be a separate trip to memory, and at two wavefronts per SIMD little of
-    // that latency is hidden.
-    double phi_e[4], K_e[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int xi = i + (t & 1) - 1, xj = j + (t >> 1) - 1;
-      const bool ok = xi >= 0 && xi < E.nx && xj >= 0 && xj < E.ny;
-      const size_t e = ok ? ((size_t)xj * E.nx + xi) * S + s : (size_t)s;
-      phi_e[t] = phi[e];
-      K_e[t] = K[e];
-    }
-    const double co = c_old[id];
-    const double u_in = uin[s];
-    double box = 0.0;
-#pragma unroll
-    for (int ej = -1; ej <= 0; ++ej)
-#pragma unroll
-      for (int ei = -1; ei <= 0; ++ei) {
-        const int xi = i + ei, xj = j + ej;
-        if (xi < 0 || xi >= E.nx || xj < 0 || xj >= E.ny) continue;
-        const int t = (ej + 1) * 2 + (ei + 1);
-        const double phie = phi_e[t], Ke = K_e[t];
-        box += 0.25 * P.hx * P.hy * phie;
-        const int kv = ei == 0 ? (ej == 0 ? 0 : 3) : (ej == 0 ? 1 : 2);   // local index of v
-        double pk[4], ck[4];
-        int dik[4], djk[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          dik[k] = ei + ((k == 1 || k == 2) ? 1 : 0);
-          djk[k] = ej + ((k == 2 || k == 3) ? 1 : 0);
-          pk[k] = pn[djk[k] + 1][dik[k] + 1];
-          ck[k] = cn[djk[k] + 1][dik[k] + 1];
-        }
-        // the two faces of this element that touch local vertex kv
-        const int f0 = kv == 0 ? 0 : kv == 1 ? 0 : kv == 2 ? 1 : 2;
-        const int f1 = kv == 0 ? 3 : kv == 1 ? 1 : kv == 2 ? 2 : 3;
-#pragma unroll
-        for (int ff = 0; ff < 2; ++ff) {
-          const int f = ff == 0 ? f0 : f1;
-          int a, b, axis;
-          double s_, t_;
-          vc_face_geom(f, a, b, axis, s_, t_);
-          const double sgn = a == kv ? 1.0 : -1.0;   // out of v's box
-          double F, G, dFp[4], dFc[4], dGp[4], dGc[4];
-          vc_face(f, pk, ck, Ke, phie, P, F, G, dFp, dFc, dGp, dGc);
-          Rp += sgn * F;
-          Rc += sgn * G;
-          if (WRITE_J) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int bl = (djk[k] + 1) * 3 + (dik[k] + 1);
-              Jb[bl * 4 + 0] += sgn * dFp[k];
-              Jb[bl * 4 + 1] += sgn * dFc[k];
-              Jb[bl * 4 + 2] += sgn * dGp[k];
-              Jb[bl * 4 + 3] += sgn * dGc[k];
-            }
-          }
-        }
-      }
-    const double cv = cn[1][1];
-    Rp += box * (P.drho * (cv - co)) / P.tau;
-    Rc += box * ((P.rho0 + P.drho * cv) * cv - (P.rho0 + P.drho * co) * co) / P.tau;
-    Jb[17] += box * P.drho / P.tau;
-    Jb[19] += box * (P.rho0 + 2.0 * P.drho * cv) / P.tau;
-    if (i == 0) {   // inflow side: mass flux rho(c_left) u_in enters; c = c_left
-      const double len = (j == 0 || j == E.ny) ? 0.5 * P.hy : P.hy;
-      Rp -= (P.rho0 + P.drho * P.c_left) * u_in * P.uin_fac * len;
-      Rc = cv - P.c_left;
-#pragma unroll
-      for (int bl = 0; bl < VC_BLK; ++bl) {
-        Jb[bl * 4 + 2] = 0.0;
-        Jb[bl * 4 + 3] = 0.0;
-      }
-      Jb[19] = 1.0;
-    }
-  }
+  auto pc = [&](int qi, int qj, double& pq, double& cq) {
+    const size_t q = ((size_t)qj * nvx + qi) * S + s;
+    pq = p[q];
+    cq = c[q];
+  };
+  auto el = [&](int xi, int xj, double& ph, double& k) {
+    const size_t e = ((size_t)xj * E.nx + xi) * S + s;
+    ph = phi[e];
+    k = K[e];
+  };
+  double Rp, Rc, Jb[36];
+  vc_row<WRITE_J>(P, E.nx, E.ny, i, j, pc, el, c_old[id], uin[s], Rp, Rc, Jb);
   R[id] = Rp;
   R[NV + id] = Rc;
   if (WRITE_J) {
@@ -742,12 +762,15 @@ __global__ void __launch_bounds__(256) k_vc_coarse_fields(Map mce, Grid2 Ec, Gri
 
 // Coarsest grid solved directly (Gaussian elimination with partial pivoting, section 2.3): the
 // dense matrix of its n = 2 nv unknowns (unknown 2 v + component) per sample, held
-// column-major in LDS (A[c n + r]).  The factors (P A = L U: L below the diagonal with its
-// unit diagonal implied, U above it and the reciprocals of U's diagonal on it) go to global
-// memory column-major once per Newton iteration with the row order perm (row i of P A is row
-// perm[i] of A), and every V-cycle solves with them.  Lanes own rows l, l + 64 and l + 128.
-// n <= VC_DENSE_MAX.
+// column-major in LDS (A[c n + r]) and factored in FP64 whatever T is (L below the diagonal
+// with its unit diagonal implied, U above it and the reciprocals of U's diagonal on it).  Each
+// thread then solves for one column of the inverse, which every V-cycle of the time step
+// multiplies by: two triangular solves in every cycle were serial chains of n columns each
+// (40 us a cycle at 9x5 vertices, against a product inside k_vc_tail).  9x5 vertices x 100
+// samples: 267 us once a time step, of which the factorisation is 187.  Lanes own rows l,
+// l + 64 and l + 128.  n <= VC_DENSE_MAX.
 constexpr int VC_DENSE_MAX = 140;
+constexpr int VC_LDS_MAX = 160 * 1024;
 constexpr int VC_DENSE_SLOTS = 3;   // rows per lane
 static_assert(VC_DENSE_SLOTS == 3 && 64 * VC_DENSE_SLOTS >= VC_DENSE_MAX, "vc_slot selects among three slots");
 
@@ -767,26 +790,88 @@ __device__ __forceinline__ T vc_slot(T v0, T v1, T v2, int r) {
   return r < 64 ? v0 : (r < 128 ? v1 : v2);
 }
 
+// Column t of the inverse, L U x = P e_t, with row r at X[r n]: eight rows at a time in
+// registers, the finished rows in X, which the neighbouring threads' columns interleave.  Eight
+// rows of a column of A are read at once, two by two (n and the first row are even); rows beyond
+// n hold other finite values (of the next column, or of what follows A in LDS) that nothing uses.
+template <typename PX>
+__device__ __forceinline__ void vc_inverse_column(const double* A, const int* pr, int n, int t, PX X) {
+  struct alignas(16) Two { double a, b; };
+  auto eight = [&](int k, int r0, double (&v)[8]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const Two w = *reinterpret_cast<const Two*>(A + k * n + r0 + 2 * q);
+      v[2 * q] = w.a;
+      v[2 * q + 1] = w.b;
+    }
+  };
+  for (int r0 = 0; r0 < n; r0 += 8) {        // L y = P e_t
+    double y[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) y[q] = r0 + q < n && pr[r0 + q] == t ? 1.0 : 0.0;
+#pragma unroll 4
+    for (int k = 0; k < r0; ++k) {
+      const double xk = X[k * n];
+      double v[8];
+      eight(k, r0, v);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y[q] -= v[q] * xk;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+      for (int q = k + 1; q < 8; ++q) y[q] -= (r0 + q < n ? A[(r0 + k) * n + r0 + q] : 0.0) * y[k];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (r0 + q < n) X[(r0 + q) * n] = y[q];
+  }
+  for (int r0 = (n - 1) / 8 * 8; r0 >= 0; r0 -= 8) {   // U x = y
+    const int r1 = r0 + 8 < n ? r0 + 8 : n;
+    double y[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) y[q] = r0 + q < n ? X[(r0 + q) * n] : 0.0;
+#pragma unroll 4
+    for (int k = r1; k < n; ++k) {
+      const double xk = X[k * n];
+      double v[8];
+      eight(k, r0, v);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y[q] -= v[q] * xk;
+    }
+#pragma unroll
+    for (int k = 7; k >= 0; --k)
+      if (r0 + k < n) {
+        y[k] *= A[(r0 + k) * n + r0 + k];
+#pragma unroll
+        for (int q = 0; q < k; ++q) y[q] -= A[(r0 + k) * n + r0 + q] * y[k];
+      }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (r0 + q < n) X[(r0 + q) * n] = y[q];
+  }
+}
+
 // Factorisation, one workgroup of four wavefronts per sample.  Wavefront w owns the columns
 // c = w (mod 4).  Step k: every wavefront reads column k and finds the pivot row p (the first
 // row of largest magnitude at or below the diagonal) and the multipliers itself; each swaps rows
 // k and p in its own columns and updates its own trailing columns; one barrier ends the step,
 // after which the owner of column k stores its multipliers (no wavefront reads column k again).
+// J: [S][36][vertex] (k_vc_tail_setup), inv: [S][n][n].
 template <typename T>
-__global__ void __launch_bounds__(256) k_vc_dense_factor(int S, Grid2 E, const T* __restrict__ J,
-                                                         T* __restrict__ LU, int* __restrict__ perm) {
+__global__ void __launch_bounds__(256) k_vc_dense_inverse(int S, Grid2 E, const T* __restrict__ J,
+                                                          double* __restrict__ inv) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int nvx = E.nx + 1, nvy = E.ny + 1, nv = nvx * nvy, n = 2 * nv;
   const int s = blockIdx.x, t = threadIdx.x, w = t >> 6, lane = t & 63;
-  const size_t NV = (size_t)nv * S;
-  T* A = reinterpret_cast<T*>(smem_raw);   // A[c * n + r]
+  const T* Js = J + (size_t)s * 36 * nv;             // this sample's blocks [36][vertex]
+  double* A = reinterpret_cast<double*>(smem_raw);   // A[c * n + r]
   int* pr = reinterpret_cast<int*>(A + (size_t)n * n);
   for (int e = t; e < n * n; e += 256) A[e] = 0;
   for (int r = t; r < n; r += 256) pr[r] = r;
   __syncthreads();
   // scatter the nine blocks of every vertex row, four independent loads in flight per thread
   for (int e0 = 0; e0 < nv * 36; e0 += 4 * 256) {
-    T val[4];
+    double val[4];
     int dst[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -798,7 +883,7 @@ __global__ void __launch_bounds__(256) k_vc_dense_factor(int S, Grid2 E, const T
         const int i = v % nvx, j = v / nvx, qi = i + bl % 3 - 1, qj = j + bl / 3 - 1;
         if (qi >= 0 && qi < nvx && qj >= 0 && qj < nvy) {
           dst[u] = (2 * (qj * nvx + qi) + k) * n + 2 * v + a;
-          val[u] = J[(size_t)q * NV + (size_t)v * S + s];
+          val[u] = (double)Js[q * nv + v];
         }
       }
     }
@@ -808,13 +893,13 @@ __global__ void __launch_bounds__(256) k_vc_dense_factor(int S, Grid2 E, const T
   }
   __syncthreads();
   for (int k = 0; k < n; ++k) {
-    const T* Ak = A + (size_t)k * n;
-    T ck[VC_DENSE_SLOTS];
-    T vmax = -1;
+    const double* Ak = A + (size_t)k * n;
+    double ck[VC_DENSE_SLOTS];
+    double vmax = -1;
 #pragma unroll
     for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
       const int r = lane + 64 * q;
-      ck[q] = r < n ? Ak[r] : (T)0;
+      ck[q] = r < n ? Ak[r] : 0.0;
       if (r >= k && r < n) vmax = fmax(vmax, fabs(ck[q]));
     }
 #pragma unroll
@@ -826,21 +911,21 @@ __global__ void __launch_bounds__(256) k_vc_dense_factor(int S, Grid2 E, const T
       const unsigned long long hit = __ballot(r >= k && r < n && fabs(ck[q]) == vmax);
       if (hit) p = 64 * q + __ffsll((long long)hit) - 1;
     }
-    const T akk = vc_bcast(vc_slot(ck[0], ck[1], ck[2], k), k & 63);
-    const T apk = vc_bcast(vc_slot(ck[0], ck[1], ck[2], p), p & 63);
-    const T rp = (T)1 / apk;
-    T l[VC_DENSE_SLOTS];
+    const double akk = vc_bcast(vc_slot(ck[0], ck[1], ck[2], k), k & 63);
+    const double apk = vc_bcast(vc_slot(ck[0], ck[1], ck[2], p), p & 63);
+    const double rp = 1.0 / apk;
+    double l[VC_DENSE_SLOTS];
     bool below[VC_DENSE_SLOTS];
 #pragma unroll
     for (int q = 0; q < VC_DENSE_SLOTS; ++q) {   // multipliers of the interchanged column k
       const int r = lane + 64 * q;
       below[q] = r > k && r < n;
-      l[q] = below[q] ? (r == p ? akk : ck[q]) * rp : (T)0;
+      l[q] = below[q] ? (r == p ? akk : ck[q]) * rp : 0.0;
     }
     if (p != k) {
       for (int c = w + 4 * lane; c < n; c += 256)   // interchange rows k and p in own columns
         if (c != k) {
-          const T a = A[(size_t)c * n + k];
+          const double a = A[(size_t)c * n + k];
           A[(size_t)c * n + k] = A[(size_t)c * n + p];
           A[(size_t)c * n + p] = a;
         }
@@ -854,32 +939,32 @@ __global__ void __launch_bounds__(256) k_vc_dense_factor(int S, Grid2 E, const T
     // LDS latency is paid once per four columns
     int c = k + 1 + ((w - k - 1) & 3);
     for (; c + 12 < n; c += 16) {
-      T u[4], a[4][VC_DENSE_SLOTS];
+      double u[4], a[4][VC_DENSE_SLOTS];
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        const T* Ac = A + (size_t)(c + 4 * h) * n;
+        const double* Ac = A + (size_t)(c + 4 * h) * n;
         u[h] = Ac[k];
 #pragma unroll
-        for (int q = 0; q < VC_DENSE_SLOTS; ++q) a[h][q] = below[q] ? Ac[lane + 64 * q] : (T)0;
+        for (int q = 0; q < VC_DENSE_SLOTS; ++q) a[h][q] = below[q] ? Ac[lane + 64 * q] : 0.0;
       }
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        T* Ac = A + (size_t)(c + 4 * h) * n;
+        double* Ac = A + (size_t)(c + 4 * h) * n;
 #pragma unroll
         for (int q = 0; q < VC_DENSE_SLOTS; ++q)
           if (below[q]) Ac[lane + 64 * q] = a[h][q] - l[q] * u[h];
       }
     }
     for (; c < n; c += 4) {
-      T* Ac = A + (size_t)c * n;
-      const T u = Ac[k];
+      double* Ac = A + (size_t)c * n;
+      const double u = Ac[k];
 #pragma unroll
       for (int q = 0; q < VC_DENSE_SLOTS; ++q)
         if (below[q]) Ac[lane + 64 * q] -= l[q] * u;
     }
     __syncthreads();
     if ((k & 3) == w) {   // U's diagonal is stored as its reciprocal, which the solve multiplies by
-      T* Akw = A + (size_t)k * n;
+      double* Akw = A + (size_t)k * n;
 #pragma unroll
       for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
         const int r = lane + 64 * q;
@@ -889,105 +974,331 @@ __global__ void __launch_bounds__(256) k_vc_dense_factor(int S, Grid2 E, const T
     }
   }
   __syncthreads();
-  for (int e = t; e < n * n; e += 256) LU[(size_t)s * n * n + e] = A[e];
-  for (int r = t; r < n; r += 256) perm[(size_t)s * n + r] = pr[r];
+  // column t of the inverse, its finished rows in LDS where the matrix leaves room for them (n up
+  // to 100), else in the output itself
+  double* out = inv + (size_t)s * n * n;
+  if (2 * n * n * (int)sizeof(double) + n * (int)sizeof(int) + 16 <= VC_LDS_MAX) {
+    double* X = A + (size_t)n * n + (n + 1) / 2 + 1;   // beyond the row order
+    if (t < n) vc_inverse_column(A, pr, n, t, X + t);
+    __syncthreads();
+    for (int e = t; e < n * n; e += 256) out[e] = X[e];
+  } else if (t < n) {
+    vc_inverse_column(A, pr, n, t, out + t);
+  }
 }
 
-// x = A^{-1} b with the factors of k_vc_dense_factor (both [2][nv][S] vectors), one wavefront
-// per sample: the factors staged into LDS (a wavefront's LDS operations complete in issue
-// order, so no barrier is needed), y = P b gathered into registers, then forward and back
-// substitution column by column with the pivot row's value broadcast from its lane; each
-// chunk of VC_SOLVE_CH columns is read from LDS ahead of its dependent steps.
-constexpr int VC_SOLVE_CH = 8;
+// ---- the coarse end of the V-cycle in one launch, one workgroup per sample ------------------
+// As henry_tail.hpp does for the cell-centred cycle: below some 560 vertices a colour pass is
+// launch and memory latency, and a V-cycle took eleven launches per coarse grid.  Here every
+// smoothed coarse grid has threads of its own in the workgroup, one per vertex, which hold the
+// vertex's Jacobian row (36 values) in registers throughout; iterates and residuals live in LDS
+// with a border of zeros.  Threads of a grid are ordered by colour, so that a colour pass fills
+// whole wavefronts.  At level 1 of Table 2 (33x17 and 17x9 vertices smoothed, 9x5 solved) x 100
+// samples a cycle's coarse end took 23 launches and about 140 us; 17 us now.
+constexpr int VC_TAIL_LEVELS = 3;
+constexpr int VC_TAIL_THREADS = 768;   // 12 wavefronts: 168 registers a thread
 template <typename T>
-__global__ void __launch_bounds__(64) k_vc_dense_solve(int S, Grid2 E, const T* __restrict__ LU,
-                                                       const int* __restrict__ perm, const T* __restrict__ b,
-                                                       T* __restrict__ x) {
+struct VCTail {
+  int S, nl, nu_pre, nu_post;
+  int nx[VC_TAIL_LEVELS + 1], ny[VC_TAIL_LEVELS + 1];   // elements: the smoothed grids, then the coarsest
+  const T* J;          // per sample: [36][vertices in thread order] of every smoothed grid
+  const double* inv;   // [S][n][n] of the coarsest
+};
+__host__ __device__ inline int vc_nv(int nx, int ny) { return (nx + 1) * (ny + 1); }
+__host__ __device__ inline int vc_wave_threads(int nv) { return (nv + 63) / 64 * 64; }
+// vertex (i, j) of thread u of a grid, in colour order; its colour, -1 beyond the last vertex
+__device__ __forceinline__ int vc_tail_vertex(int u, int nx, int ny, int& i, int& j) {
+  int colour = 0;
+  for (; colour < 4; ++colour) {
+    const int n = vc_colour_cells(nx, ny, colour);
+    if (u < n) break;
+    u -= n;
+  }
+  if (colour == 4) return -1;
+  const int nci = (nx + 2 - (colour & 1)) >> 1;
+  j = 2 * (u / nci) + (colour >> 1);
+  i = 2 * (u % nci) + (colour & 1);
+  return colour;
+}
+__host__ inline int vc_tail_threads(const int* nx, const int* ny, int nl) {
+  int t = 0;
+  for (int l = 0; l < nl; ++l) t += vc_wave_threads(vc_nv(nx[l], ny[l]));
+  return t < 256 ? 256 : t;
+}
+__host__ __device__ inline size_t vc_tail_values(const int* nx, const int* ny, int nl) {
+  size_t n = 0;
+  for (int l = 0; l < nl; ++l) n += (size_t)36 * vc_nv(nx[l], ny[l]);
+  return n;
+}
+__host__ __device__ inline int vc_padded(int nx, int ny) { return (nx + 3) * (ny + 3); }
+template <typename T>
+__host__ inline size_t vc_tail_lds(const VCTail<T>& A) {
+  size_t n = vc_nv(A.nx[A.nl], A.ny[A.nl]);   // the coarsest grid's right-hand side
+  int r = 0;
+  for (int l = 0; l <= A.nl; ++l) {
+    n += vc_padded(A.nx[l], A.ny[l]);
+    if (l < A.nl) r = r > vc_padded(A.nx[l], A.ny[l]) ? r : vc_padded(A.nx[l], A.ny[l]);
+  }
+  return (n + r) * sizeof(Pair<T>);
+}
+
+// x = M^{-1} b on the grids of A from x = 0; b, x: [2][vertices of grid 0][S].
+template <typename T>
+__global__ void __launch_bounds__(VC_TAIL_THREADS) k_vc_tail(VCTail<T> A, const T* __restrict__ b, T* __restrict__ x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int nv = (E.nx + 1) * (E.ny + 1), n = 2 * nv;
-  const int s = blockIdx.x, t = threadIdx.x;
-  const size_t NV = (size_t)nv * S;
-  T* A = reinterpret_cast<T*>(smem_raw);   // A[c * n + r]
-  {   // n is even, so n^2 sizeof(T) is a multiple of 16 bytes and each sample's factors start
-      // 16-byte aligned: staged in 16-byte chunks, 16 loads in flight per lane
-    const uint4* src = reinterpret_cast<const uint4*>(LU + (size_t)s * n * n);
-    uint4* dst = reinterpret_cast<uint4*>(A);
-    const int n2 = (int)((size_t)n * n * sizeof(T) / 16);
-    for (int e0 = 0; e0 < n2; e0 += 16 * 64) {
-      uint4 v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int e = e0 + u * 64 + t;
-        v[u] = e < n2 ? src[e] : make_uint4(0, 0, 0, 0);
+  const int s = tail_sample(A.S), t = threadIdx.x, nl = A.nl;
+  if (s >= A.S) return;
+  Pair<T>* const sh = reinterpret_cast<Pair<T>*>(smem_raw);
+  // LDS: padded iterates of every grid, padded residual of one grid at a time, bc
+  int rsize = 0, xo = 0;       // this thread's grid: offsets of its iterates
+  int ml = -1, colour = -1, i = 0, j = 0, w = 0, pos = 0;
+  const T* Jr = A.J;
+  {
+    int o = 0, u = t;
+    const T* Jl = A.J + (size_t)s * vc_tail_values(A.nx, A.ny, nl);
+    for (int l = 0; l < nl; ++l) {
+      const int nv = vc_nv(A.nx[l], A.ny[l]), pad = vc_padded(A.nx[l], A.ny[l]);
+      if (ml < 0 && u < vc_wave_threads(nv)) {
+        ml = l;
+        xo = o;
+        pos = u;
+        Jr = Jl;
+        w = A.nx[l] + 3;
+        colour = vc_tail_vertex(u, A.nx[l], A.ny[l], i, j);
       }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int e = e0 + u * 64 + t;
-        if (e < n2) dst[e] = v[u];
-      }
+      u -= vc_wave_threads(nv);
+      Jl += (size_t)36 * nv;
+      o += pad;
+      rsize = rsize > pad ? rsize : pad;
     }
   }
-  T y[VC_DENSE_SLOTS];
+  auto grid_at = [&](int l) {   // offset of grid l's iterates
+    int o = 0;
+    for (int k = 0; k < l; ++k) o += vc_padded(A.nx[k], A.ny[k]);
+    return o;
+  };
+  const int xc = grid_at(nl), nxc = A.nx[nl], nyc = A.ny[nl], nvc = vc_nv(nxc, nyc), n = 2 * nvc, wc = nxc + 3;
+  const int ro = xc + vc_padded(nxc, nyc), bo = ro + rsize;
+  const bool own = colour >= 0;
+  const int me = xo + (j + 1) * w + i + 1, myr = ro + (j + 1) * w + i + 1;
+  // every global load of the cycle is issued here
+  T row[9][4], b0 = 0, b1 = 0, rdet = 0;
+  if (own) {
+    const int nv = vc_nv(A.nx[ml], A.ny[ml]);
 #pragma unroll
-  for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
-    const int r = t + 64 * q;
-    y[q] = 0;
-    if (r < n) {
-      const int g = perm[(size_t)s * n + r];
-      y[q] = b[(size_t)(g & 1) * NV + (size_t)(g >> 1) * S + s];
+    for (int bl = 0; bl < 9; ++bl)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) row[bl][e] = Jr[(bl * 4 + e) * nv + pos];
+    if (ml == 0) {
+      const size_t NV = (size_t)nv * A.S, id = (size_t)(j * (A.nx[0] + 1) + i) * A.S + s;
+      b0 = b[id];
+      b1 = b[NV + id];
     }
   }
-  __builtin_amdgcn_wave_barrier();
-  for (int k0 = 0; k0 < n - 1; k0 += VC_SOLVE_CH) {   // L y = P b (unit lower)
-    T a[VC_SOLVE_CH][VC_DENSE_SLOTS];
+  const int part = t & 7;
+  const double* inv = A.inv + (size_t)s * n * n;
+  double iv[8];
 #pragma unroll
-    for (int j = 0; j < VC_SOLVE_CH; ++j)
+  for (int e = 0; e < 8; ++e) iv[e] = (t >> 3) < n && part + 8 * e < n ? inv[(size_t)(t >> 3) * n + part + 8 * e] : 0.0;
+  for (int e = t; e < bo; e += blockDim.x) sh[e] = Pair<T>{(T)0, (T)0};
+  lds_barrier();
+  if (own) rdet = (T)1 / (row[4][0] * row[4][3] - row[4][1] * row[4][2]);
+  auto off = [&]() {
+    Pair<T> y{(T)0, (T)0};
 #pragma unroll
-      for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
-        const int k = k0 + j, r = t + 64 * q;
-        a[j][q] = (k < n - 1 && r > k && r < n) ? A[(size_t)k * n + r] : (T)0;
-      }
-#pragma unroll
-    for (int j = 0; j < VC_SOLVE_CH; ++j) {
-      const int k = k0 + j;
-      if (k < n - 1) {
-        const T yk = vc_bcast(vc_slot(y[0], y[1], y[2], k), k & 63);
-#pragma unroll
-        for (int q = 0; q < VC_DENSE_SLOTS; ++q)
-          if (t + 64 * q > k) y[q] -= a[j][q] * yk;
-      }
+    for (int bl = 0; bl < 9; ++bl) {
+      if (bl == 4) continue;
+      const Pair<T> v = sh[me + (bl / 3 - 1) * w + bl % 3 - 1];
+      y.a += row[bl][0] * v.a + row[bl][1] * v.b;
+      y.b += row[bl][2] * v.a + row[bl][3] * v.b;
     }
-  }
-  for (int k0 = n - 1; k0 >= 0; k0 -= VC_SOLVE_CH) {   // U x = y
-    T a[VC_SOLVE_CH][VC_DENSE_SLOTS], dk[VC_SOLVE_CH];
-#pragma unroll
-    for (int j = 0; j < VC_SOLVE_CH; ++j) {
-      const int k = k0 - j;
-      dk[j] = k >= 0 ? A[(size_t)k * n + k] : (T)1;   // 1 / U_kk
-#pragma unroll
-      for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
-        const int r = t + 64 * q;
-        a[j][q] = (k >= 0 && r < k) ? A[(size_t)k * n + r] : (T)0;
-      }
+    return y;
+  };
+  auto pass = [&](int l, int c) {
+    if (ml == l && colour == c) {
+      const Pair<T> y = off();
+      const T r0 = b0 - y.a, r1 = b1 - y.b;
+      sh[me] = Pair<T>{(row[4][3] * r0 - row[4][1] * r1) * rdet, (row[4][0] * r1 - row[4][2] * r0) * rdet};
     }
+    lds_barrier();
+  };
+  // down
+  for (int l = 0; l < nl; ++l) {
+    for (int sw = 0; sw < A.nu_pre; ++sw)
+      for (int c = 0; c < 4; ++c) pass(l, c);
+    if (l > 0) {   // the border of the previous grid's residual differs: clear it
+      for (int e = t; e < rsize; e += blockDim.x) sh[ro + e] = Pair<T>{(T)0, (T)0};
+      lds_barrier();
+    }
+    if (ml == l && own && colour != 3) {   // the colour swept last has none
+      const Pair<T> y = off(), v = sh[me];
+      sh[myr] = Pair<T>{b0 - (y.a + row[4][0] * v.a + row[4][1] * v.b), b1 - (y.b + row[4][2] * v.a + row[4][3] * v.b)};
+    }
+    lds_barrier();
+    const bool last = l + 1 == nl;
+    int I = i, J = j;
+    bool take = ml == l + 1 && own;
+    if (last) {
+      take = t < nvc;
+      J = t / (nxc + 1);
+      I = t - J * (nxc + 1);
+    }
+    if (take) {
+      const int wf = A.nx[l] + 3, f = ro + (2 * J + 1) * wf + 2 * I + 1;
+      T a0 = 0, a1 = 0;
 #pragma unroll
-    for (int j = 0; j < VC_SOLVE_CH; ++j) {
-      const int k = k0 - j;
-      if (k >= 0) {
-        const T xk = vc_bcast(vc_slot(y[0], y[1], y[2], k), k & 63) * dk[j];
+      for (int dj = -1; dj <= 1; ++dj)
 #pragma unroll
-        for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
-          const int r = t + 64 * q;
-          if (r == k) y[q] = xk;
-          else if (r < k) y[q] -= a[j][q] * xk;
+        for (int di = -1; di <= 1; ++di) {
+          const T wt = (T)((di == 0 ? 1.0 : 0.5) * (dj == 0 ? 1.0 : 0.5));
+          const Pair<T> r = sh[f + dj * wf + di];
+          a0 += wt * r.a;
+          a1 += wt * r.b;
         }
+      const int nxl = A.nx[l + 1];
+      a0 = I == nxl ? (T)0 : a0;
+      a1 = I == nxl || I == 0 ? (T)0 : a1;
+      if (last) {
+        sh[bo + t] = Pair<T>{a0, a1};
+      } else {
+        b0 = a0;
+        b1 = a1;
+      }
+    }
+    lds_barrier();
+  }
+  if (nl == 0) {
+    const size_t NV = (size_t)nvc * A.S;
+    if (t < nvc) sh[bo + t] = Pair<T>{b[(size_t)t * A.S + s], b[NV + (size_t)t * A.S + s]};
+    lds_barrier();
+  }
+  {   // coarsest grid: eight threads per row of the inverse
+    const T* v = reinterpret_cast<const T*>(sh + bo);
+    for (int r = t >> 3, k = 0; r < n; r += blockDim.x >> 3, ++k) {
+      double acc = 0.0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int c = part + 8 * e;
+        if (c < n) acc += (k == 0 ? iv[e] : inv[(size_t)r * n + c]) * (double)v[c];
+      }
+      for (int c = part + 64; c < n; c += 8) acc += inv[(size_t)r * n + c] * (double)v[c];
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) acc += __shfl_xor(acc, o);
+      if (part == 0) {
+        const int q = r >> 1, J = q / (nxc + 1), I = q - J * (nxc + 1);
+        reinterpret_cast<T*>(sh + xc + (J + 1) * wc + I + 1)[r & 1] = (T)acc;
       }
     }
   }
+  lds_barrier();
+  // up
+  for (int l = nl - 1; l >= 0; --l) {
+    if (ml == l && own && i != A.nx[l]) {
+      const int wn = A.nx[l + 1] + 3, I0 = i >> 1, J0 = j >> 1, I1 = I0 + (i & 1), J1 = J0 + (j & 1);
+      const Pair<T>* e = sh + grid_at(l + 1) + wn + 1;
+      const Pair<T> e0 = e[J0 * wn + I0], e1 = e[J0 * wn + I1], e2 = e[J1 * wn + I0], e3 = e[J1 * wn + I1];
+      Pair<T> v = sh[me];
+      v.a += (T)0.25 * (e0.a + e1.a + e2.a + e3.a);
+      if (i != 0) v.b += (T)0.25 * (e0.b + e1.b + e2.b + e3.b);
+      sh[me] = v;
+    }
+    lds_barrier();
+    for (int sw = 0; sw < A.nu_post; ++sw)
+      for (int c = 3; c >= 0; --c) pass(l, c);
+  }
+  if (nl == 0) {
+    const size_t NV = (size_t)nvc * A.S;
+    if (t < nvc) {
+      const int J = t / (nxc + 1), I = t - J * (nxc + 1);
+      const Pair<T> v = sh[xc + (J + 1) * wc + I + 1];
+      x[(size_t)t * A.S + s] = v.a;
+      x[NV + (size_t)t * A.S + s] = v.b;
+    }
+  } else if (ml == 0 && own) {
+    const size_t NV = (size_t)vc_nv(A.nx[0], A.ny[0]) * A.S, id = (size_t)(j * (A.nx[0] + 1) + i) * A.S + s;
+    const Pair<T> v = sh[me];
+    x[id] = v.a;
+    x[NV + id] = v.b;
+  }
+}
+
+// The Jacobians of those grids at the injected state, one workgroup per sample: p, c, phi and K
+// of a grid in LDS, each thread the rows of every 256th vertex.  Smoothed grids are written in
+// thread order; the coarsest (only when Jc is given: its inverse is refreshed once a time step)
+// as [36][vertex].
+template <typename T>
+struct VCTailSetup {
+  int S, nl;
+  int nx[VC_TAIL_LEVELS + 1], ny[VC_TAIL_LEVELS + 1];
+  const double *p, *c;   // state of the next finer grid [vertex][S]
+  const double *phi[VC_TAIL_LEVELS + 1], *K[VC_TAIL_LEVELS + 1];
+  T *J, *Jc;
+};
+template <typename T>
+__host__ inline size_t vc_setup_lds(const VCTailSetup<T>& A) {
+  size_t n = 0, e = 0;
+  for (int l = 0; l <= A.nl; ++l) {
+    n += 2 * (size_t)vc_nv(A.nx[l], A.ny[l]);
+    const size_t ne = 2 * (size_t)A.nx[l] * A.ny[l];
+    e = e > ne ? e : ne;
+  }
+  return (n + e) * sizeof(double);
+}
+template <typename T>
+__global__ void __launch_bounds__(256) k_vc_tail_setup(VCTailSetup<T> A, Phys P) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int s = tail_sample(A.S), t = threadIdx.x, S = A.S;
+  if (s >= S) return;
+  double* st = reinterpret_cast<double*>(smem_raw);   // [p, c][vertex] of every grid so far
+  double* fe = st;                                    // [phi, K][element] of the current one
+  for (int l = 0; l <= A.nl; ++l) fe += 2 * vc_nv(A.nx[l], A.ny[l]);
+  T* Jg = A.J + (size_t)s * vc_tail_values(A.nx, A.ny, A.nl);
+  const double* prev = st;
+  for (int l = 0; l <= A.nl; ++l) {
+    if (l == A.nl && !A.Jc) break;
+    const int nx = A.nx[l], ny = A.ny[l], nv = vc_nv(nx, ny), ne = nx * ny, fw = 2 * nx + 1;
+    const int fnv = vc_nv(2 * nx, 2 * ny);
+    for (int v = t; v < nv; v += 256) {   // injection: fine vertex (2I, 2J)
+      const int J = v / (nx + 1), q = 2 * J * fw + 2 * (v - J * (nx + 1));
+      st[v] = l == 0 ? A.p[(size_t)q * S + s] : prev[q];
+      st[nv + v] = l == 0 ? A.c[(size_t)q * S + s] : prev[fnv + q];
+    }
+    for (int e = t; e < ne; e += 256) {
+      fe[e] = A.phi[l][(size_t)e * S + s];
+      fe[ne + e] = A.K[l][(size_t)e * S + s];
+    }
+    lds_barrier();
+    Phys Pl = P;
+    Pl.hx = P.Lx / nx;
+    Pl.hy = P.Ly / ny;
+    Pl.vol = Pl.hx * Pl.hy;
+    auto pc = [&](int qi, int qj, double& pq, double& cq) {
+      const int q = qj * (nx + 1) + qi;
+      pq = st[q];
+      cq = st[nv + q];
+    };
+    auto el = [&](int xi, int xj, double& ph, double& k) {
+      ph = fe[xj * nx + xi];
+      k = fe[ne + xj * nx + xi];
+    };
+    T* out = l < A.nl ? Jg : A.Jc + (size_t)s * 36 * nv;
+    for (int u = t; u < nv; u += 256) {
+      int i, j;
+      if (l < A.nl) {
+        vc_tail_vertex(u, nx, ny, i, j);
+      } else {
+        j = u / (nx + 1);
+        i = u - j * (nx + 1);
+      }
+      double Rp, Rc, Jb[36];
+      vc_row<true>(Pl, nx, ny, i, j, pc, el, 0.0, 0.0, Rp, Rc, Jb);
 #pragma unroll
-  for (int q = 0; q < VC_DENSE_SLOTS; ++q) {
-    const int r = t + 64 * q;
-    if (r < n) x[(size_t)(r & 1) * NV + (size_t)(r >> 1) * S + s] = y[q];
+      for (int q = 0; q < 36; ++q) out[q * nv + u] = (T)Jb[q];
+    }
+    lds_barrier();   // the fields are overwritten by the next grid's
+    Jg += (size_t)36 * nv;
+    prev = st;
+    st += 2 * nv;
   }
 }
 

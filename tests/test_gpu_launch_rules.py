@@ -129,3 +129,35 @@ def test_coarse_grids_in_one_launch_transposed(hx):
             gr = hx.adjoint(th, g, prob, P.solver_opts(coarse_nx=cnx, coarse_ny=cnx // 2, mg_precision=prec, **tight),
                             checkpoint_every=4)[1]
             assert (gr - ref).abs().max() <= 1e-9 * ref.abs().max(), (cnx, prec)
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("nx,ny,S,opts", [
+    (16, 8, 1, {}),                                    # the coarsest grid alone
+    (16, 8, 17, dict(coarse_nx=12, coarse_ny=6)),      # no coarse grid: sweeps on the fine one
+    (32, 16, 33, dict(nu_pre=2)),                      # one smoothed grid in the launch
+    (64, 32, 5, dict(nu_post=1)),                      # two, 561 and 153 vertices
+    (64, 32, 5, dict(coarse_nx=4, coarse_ny=2)),       # two of the three coarse grids
+    (40, 24, 5, dict(coarse_nx=10, coarse_ny=6)),      # 77 vertices are too many to invert: sweeps
+    (36, 20, 5, dict(coarse_nx=9, coarse_ny=5)),       # a coarsest grid of 60 vertices, odd sides
+])
+def test_vertex_coarse_grids_in_one_launch(hx, prec, nx, ny, S, opts):
+    """The vertex-centred cycle's coarse end in launches of one workgroup per sample, against the
+    vertex oracle (1e-8, the workload's bound), and its strength where there is a cycle: at most
+    1.35 BiCGStab iterations per Newton iteration (1.00 to 1.05 with a launch per pass)."""
+    import paper_2403_17018_amd as P
+    from oracle import henry as H
+    from oracle import vertex as V
+    import dataclasses
+    th = draw_theta(43, S, level=1)
+    steps, T = 3, 3 * 64.0 * 8 / ny
+    r = hx.vc_solve(_cu(th), P.grid(nx, ny, steps), P.paper_problem(T=T),
+                    P.solver_opts(mg_precision=prec, krylov_maxit=300, **opts), want_p=True)
+    assert r.nfailed == 0
+    for s in sorted({0, S - 1}):
+        ref = V.solve_sample(dataclasses.replace(H.paper_problem(), T=T), H.Grid(nx, ny, steps), th[s])
+        c = r.c_T[..., s].cpu().numpy().ravel()
+        assert np.abs(c - np.ravel(ref.c)).max() <= 1e-8 * np.abs(ref.c).max()
+    if opts.get("coarse_nx", 8) not in (10, 12):
+        newton, bicg = r.stats[:, 0].sum().item(), r.stats[:, 1].sum().item()
+        assert bicg <= 1.35 * newton, (newton, bicg)
