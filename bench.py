@@ -127,8 +127,7 @@ print(json.dumps(dict(mode=mode, njobs=len(jobs), wall=time.perf_counter() - t0,
 def solver_config(o):
     """The solver settings that ran, for the config label."""
     return {"coarse_grid": f"{o.coarse_nx}x{o.coarse_ny}",
-            "coarse_solver": {1: "dense LU with partial pivoting",
-                              2: "LU with partial pivoting in band storage (the dense elimination's pivots)"}.get(
+            "coarse_solver": {1: "LU with partial pivoting", 2: "LU with partial pivoting (any size, short bands)"}.get(
                 getattr(o, "coarse_solver", 0), "block-banded LU without pivoting"),
             "smoother": f"red-black 2x2-block Gauss-Seidel, {o.nu_pre} pre + {o.nu_post} post sweeps",
             "cycle": "V" if o.mg_cycle == 1 else "W",
@@ -489,37 +488,24 @@ def extra_lines(hx, P, args):
                                 f"(seed {w['seed']}), FP32 multigrid in FP64 BiCGStab/Newton",
                     "unit": "sample-timesteps/s", **m}
         del th
-    # the workload as named: multigrid to a 32x16 coarse grid solved by the batched dense LU with
-    # partial pivoting (four grids from 256x128); the factorisation's matrix-core roofline
+    # the workload as named: multigrid to a 32x16 coarse grid solved by Gaussian elimination with
+    # partial pivoting (four grids from 256x128); coarse_solver 1 and 2 take different sizes and
+    # run the same kernels
     w = WORKLOADS["c2_fp64_level3"]
     g = P.grid(*level_grid(w["level"]))
     th = torch.from_numpy(draw_theta(w["seed"], w["nsamples"], level=w["level"])).cuda()
-    o = P.solver_opts(coarse_nx=32, coarse_ny=16, coarse_solver=1)
-    m = measure_batch(hx, th, g, P.problem(), o, 1, 1, "c2_fp64_level3", "kl")
-    prof = m.pop("_prof")
-    nf, uf, msf = prof["dense_factor"]
     n = 2 * 32 * 16
-    flops = uf / nf * 2.0 * n ** 3 / 3.0                  # per launch: samples x 2n^3/3
-    achieved = flops / (msf / nf * 1e-3) / 1e12
-    out["c2_named_32x16_dense_lu"] = {
-        "workload": f"c2_fp64_level3 with the 32x16 coarsest grid and the batched dense LU with partial pivoting "
-                    f"(n = {n} unknowns per sample), FP64", "unit": "sample-timesteps/s", **m,
-        "solver": solver_config(o),
-        "dense_factor_roofline": {"bound": "mfma", "kernel": "k_dense_factor", "achieved": achieved,
-                                  "peak": 78.6, "unit": "TFLOP/s", "frac": achieved / 78.6,
-                                  "avg_launch_us": msf / nf * 1e3, "launches": nf,
-                                  "flops_per_launch": flops}}
-    # the same named configuration with the elimination in band storage: the dense LU's pivots
-    # and factors, without its work on the zeros outside the band
-    o = P.solver_opts(coarse_nx=32, coarse_ny=16, coarse_solver=2)
-    m = measure_batch(hx, th, g, P.problem(), o, 1, 1, "c2_fp64_level3", "kl")
-    prof = m.pop("_prof")
-    out["c2_named_32x16_pivoted_band_lu"] = {
-        "workload": f"c2_fp64_level3 with the 32x16 coarsest grid and Gaussian elimination with partial pivoting "
-                    f"in band storage (n = {n}, 2 x 33 diagonals, pivots as the dense LU's), FP64",
-        "unit": "sample-timesteps/s", **m, "solver": solver_config(o),
-        "coarse_ms": {"factor": prof["band_factor"][2], "factor_launches": prof["band_factor"][0],
-                      "solve": prof["band_solve"][2], "solve_launches": prof["band_solve"][0]}}
+    for key, solver, fac, sol in (("c2_named_32x16_dense_lu", 1, "dense_factor", "dense_solve"),
+                                  ("c2_named_32x16_pivoted_band_lu", 2, "band_factor", "band_solve")):
+        o = P.solver_opts(coarse_nx=32, coarse_ny=16, coarse_solver=solver)
+        m = measure_batch(hx, th, g, P.problem(), o, 1, 1, "c2_fp64_level3", "kl")
+        prof = m.pop("_prof")
+        out[key] = {
+            "workload": f"c2_fp64_level3 with the 32x16 coarsest grid and batched LU with partial pivoting "
+                        f"(n = {n} unknowns per sample, worked on its band of 2 x 33 diagonals), FP64",
+            "unit": "sample-timesteps/s", **m, "solver": solver_config(o),
+            "coarse_ms": {"factor": prof[fac][2], "factor_launches": prof[fac][0],
+                          "solve": prof[sol][2], "solve_launches": prof[sol][0]}}
     del th
     w = WORKLOADS["c4_mlmc_levels0to4"]
     thetas = [torch.from_numpy(draw_theta(w["seed"], k, level=l)).cuda() for l, k in zip(w["levels"], w["nsamples"])]

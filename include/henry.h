@@ -141,14 +141,14 @@ typedef struct {
                                  krylov_rtol_adjoint stays relative to the right-hand side [2] */
   int coarse_solver;          /* direct solver of the coarsest grid (Gaussian elimination, section 2.3).
                                  0: block-banded LU without pivoting (cells ordered j fastest, block
-                                 bandwidth coarse ny), one wavefront per sample [0].  1: dense LU with
-                                 partial pivoting of the 2*cells x 2*cells matrix, one workgroup per
-                                 sample, trailing updates on the matrix cores; needs 2*cells divisible
-                                 by 16 and its 16-column panel in LDS (32x16 cells at most in FP64).
-                                 2: the same elimination with partial pivoting in band storage (cells
-                                 ordered i-major: kl = ku = 2 coarse_ny + 1 scalar diagonals; the
-                                 dense LU's pivots and factors without its work on the zeros outside
-                                 the band), one workgroup per sample; needs coarse_ny <= 19 */
+                                 bandwidth coarse ny), or the explicit inverse by the same elimination
+                                 where the coarsest grid has at most 64 cells [0].  1: LU with partial
+                                 pivoting of the 2*cells x 2*cells matrix, trailing updates on the
+                                 matrix cores; needs 2*cells divisible by 16 and a 16-column panel of
+                                 all rows within the LDS (32x16 cells at most in FP64).  2: the same for
+                                 any number of cells with coarse_ny <= 19.  1 and 2 work on the
+                                 operator's band only (cells numbered along the shorter side first),
+                                 in FP64, one workgroup per sample */
   int step_graphs;            /* 1: once a step's kernel arguments are settled (constant inflow, full
                                  extrapolation history), its first Newton iteration -- the step's
                                  start, assembly, one BiCGStab iteration with both halves and the
@@ -357,10 +357,9 @@ HENRY_API int henry_gs_pass(henry_ctx* ctx, henry_grid grid, int S, const double
                             int colour, int transpose);
 
 /* Direct solve of a block operator on a coarse grid (Gaussian elimination, section 2.3):
- * x = J^{-1} b (or J^{-T} b) with solver 0 (block-banded LU without pivoting), 1 (dense LU
- * with partial pivoting) or 2 (LU with partial pivoting in band storage), factored and solved
- * in `precision` 64 or 32 (J and b are rounded to
- * FP32 first in the latter).  J: device FP64 [20][ny][nx][S] as in henry_assemble; b, x:
+ * x = J^{-1} b (or J^{-T} b) with solver 0 (block-banded LU without pivoting), 1 or 2 (LU with
+ * partial pivoting; the sizes each takes are those of coarse_solver), in `precision` 64 or 32
+ * (J and b are rounded to FP32 first in the latter).  J: device FP64 [20][ny][nx][S] as in henry_assemble; b, x:
  * device FP64 [2][ny][nx][S].  HENRY_EUNSUPPORTED when the grid does not fit the solver. */
 HENRY_API int henry_coarse_solve(henry_ctx* ctx, int solver, int precision, henry_grid coarse, int S, const double* J,
                                  const double* b, double* x, int transpose);
@@ -431,8 +430,8 @@ enum henry_prof_class {
   HENRY_PROF_BAND_FACTOR = 5, /* coarsest grid's banded LU factorisation or explicit inverse */
   HENRY_PROF_BAND_SOLVE = 6,  /* coarsest grid's banded triangular solves, or the cycle's coarse grids
                                  taken together with it in one launch */
-  HENRY_PROF_DENSE_FACTOR = 7,/* dense coarse LU: the pivoted factorisation (units: samples) */
-  HENRY_PROF_DENSE_SOLVE = 8, /* dense coarse triangular solves (units: samples) */
+  HENRY_PROF_DENSE_FACTOR = 7,/* coarse_solver 1: the pivoted factorisation (units: samples) */
+  HENRY_PROF_DENSE_SOLVE = 8, /* coarse_solver 1: its triangular solves (units: samples) */
   HENRY_PROF_HOST_SYNC = 9,   /* the solver's host round trips (control reads): launches = their
                                  number, units = 0, total_ms = host time spent waiting in them;
                                  counted whether or not event timing is enabled */

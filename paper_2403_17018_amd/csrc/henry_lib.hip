@@ -32,9 +32,8 @@
 #include "../../include/henry.h"
 #include "henry_kernels.hpp"
 #include "henry_coarse.hpp"
-#include "henry_dense.hpp"
-#include "henry_gbsv.hpp"
 #include "henry_tail.hpp"
+#include "henry_plu.hpp"
 #include "henry_mlmc.hpp"
 #include "henry_adjoint.hpp"
 #include "henry_vc.hpp"
@@ -557,15 +556,11 @@ static void plan_alloc_levels(Plan& P) {
   }
   const MGLevel& C = *P.lv[P.nlev - 1];
   P.mb = C.ny;
-  if (P.csolver == 1) {
-    const size_t n = 2 * (size_t)C.ncell;
-    P.lu_stride = n * n;
-    P.LU.alloc(P.lu_stride * P.S * sizeof(T));
-    P.perm.alloc(n * P.S * sizeof(int));
-  } else if (P.csolver == 2) {
-    P.lu_stride = gb_stride(C.nx, C.ny);
-    P.LU.alloc(P.lu_stride * P.S * sizeof(T));
-    P.perm.alloc(2 * (size_t)C.ncell * P.S * sizeof(int));
+  if (P.csolver != 0) {
+    const PluShape sh(C.nx, C.ny);
+    P.lu_stride = sh.values();
+    P.LU.alloc(P.lu_stride * P.S * sizeof(double));
+    P.perm.alloc(sh.pivots() * P.S * sizeof(int));
   } else if (P.nlev > 1 && 2 * C.ncell <= TAIL_NMAX) {
     // Coarsest grids of up to 64 cells: an explicit inverse (n^2 values a sample) and the cycle's
     // coarse end in one launch; 8x4 cells took 56 us to factor and 15 us a solve in band form,
@@ -597,29 +592,66 @@ static size_t max_lds_per_block() {
   return (size_t)std::max(v, o);
 }
 
-// The dense factorisation needs more than the default LDS limit of a launch: raise it once
-// per instantiation (and device) before its first launch.
-template <typename T>
-static void dense_factor_prepare(size_t lds) {
+// Sizes the pivoted solvers take: `solver` 1 (stated as a dense LU) whole 16-column panels of
+// all n rows in LDS, 2 (stated as a band LU) bands of up to 39 diagonals a side.  Both run
+// k_plu_factor, whose window is smaller than either.
+static void check_plu_size(int solver, int nx, int ny, int prec) {
+  const size_t n = 2 * (size_t)nx * ny, tsz = prec == 32 ? 4 : 8;
+  if (solver == 1) {
+    const size_t need = n * 16 * tsz + 16 * 64 * tsz + 1024 * (tsz + sizeof(int)) + n * sizeof(int);
+    if (n % 16) fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d: the dense LU needs 2 * cells divisible by 16", nx, ny);
+    if (need > max_lds_per_block())
+      fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d too large for the dense LU's LDS panel (%zu bytes)", nx, ny, need);
+  } else {
+    const size_t kl = 2 * (size_t)ny + 1, cols = 2 * kl + 1;
+    const size_t factor = ((kl + 2) * (cols + 1) + 16 * cols + cols) * tsz + 16, solve = (n + 2 * 16 * cols) * tsz + 128;
+    if (kl * 2 * kl > 3072 || factor > 64 * 1024 || solve > 64 * 1024)
+      fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d too large for the pivoted band LU (ny <= 19 and the LDS limit)", nx,
+           ny);
+  }
+}
+
+// The factorisation's window may need more LDS than a launch gets by default: raise the limit
+// once per instantiation (and device) before its first launch.
+template <typename K>
+static void lds_prepare(K* kernel, size_t bytes) {
   static std::mutex mu;
-  static bool done[64] = {};
+  static std::map<std::pair<const void*, int>, bool> done;
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(mu);
-  if (dev >= 0 && dev < 64 && done[dev]) return;
-  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dense_factor<T, 16>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  if (dev >= 0 && dev < 64) done[dev] = true;
+  bool& d = done[{reinterpret_cast<const void*>(kernel), dev}];
+  if (d) return;
+  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes));
+  d = true;
 }
-
-// Band LU with partial pivoting: the pivot search covers kl + 1 rows in one wavefront, and the
-// factor window and the solve's staging must fit the default LDS limit of a launch.
-static void check_gb_size(int nxc, int nyc, int prec) {
-  const size_t f = prec == 32 ? gb_factor_lds<float>(nyc) : gb_factor_lds<double>(nyc);
-  const size_t sv = prec == 32 ? gb_solve_lds<float>(nxc, nyc) : gb_solve_lds<double>(nxc, nyc);
-  if (gb_kl(nyc) + 1 > 64 || gb_kl(nyc) * 2 * gb_kl(nyc) > GB_THREADS * GB_UPD || f > 64 * 1024 || sv > 64 * 1024)
-    fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d too large for the pivoted band LU (ny <= 19 and the LDS limit)", nxc,
-         nyc);
+// Launch shapes by the window's rows: one per lane up to 64 (shorter side <= 23 cells), else two.
+template <typename T>
+static void plu_factor(hipStream_t st, int S, int nx, int ny, const T* J, double* F, int* piv) {
+  const PluShape sh(nx, ny);
+  const dim3 g(8 * tail_chunk(S)), bl(PLU_THREADS);
+  const uint32_t lds = (uint32_t)sh.factor_lds();
+  constexpr int LDS = 160 * 1024;
+  if (sh.m <= 64) {
+    lds_prepare(&k_plu_factor<T, 1, 3>, LDS);
+    launch_timed((k_plu_factor<T, 1, 3>), g, bl, lds, st, S, nx, ny, J, F, piv);
+  } else {
+    lds_prepare(&k_plu_factor<T, 2, 6>, LDS);
+    launch_timed((k_plu_factor<T, 2, 6>), g, bl, lds, st, S, nx, ny, J, F, piv);
+  }
+}
+template <typename T, bool TR>
+static void plu_solve(hipStream_t st, int S, int nx, int ny, const double* F, const int* piv, const T* b, T* x) {
+  const PluShape sh(nx, ny);
+  const dim3 g(8 * tail_chunk(S));
+  const uint32_t lds = (uint32_t)sh.solve_lds();
+  if (lds > 64 * 1024) {   // FP32 bands of more than 7 000 unknowns
+    lds_prepare(&k_plu_solve<T, TR, 1>, 160 * 1024);
+    lds_prepare(&k_plu_solve<T, TR, 2>, 160 * 1024);
+  }
+  if (sh.m <= 64) launch_timed((k_plu_solve<T, TR, 1>), g, dim3(64), lds, st, S, nx, ny, F, piv, b, x);
+  else launch_timed((k_plu_solve<T, TR, 2>), g, dim3(64), lds, st, S, nx, ny, F, piv, b, x);
 }
 
 static void plan_set_wide(Plan& Q, int sample_block) {
@@ -657,14 +689,8 @@ static std::unique_ptr<Plan> make_plan(int nx, int ny, int S, const henry_solver
     gy /= 2;
   }
   P->nlev = (int)P->lv.size();
-  if (o.coarse_solver == 1) {
-    const int n = 2 * P->lv.back()->ncell;
-    const size_t need = o.mg_precision == 32 ? dense_factor_lds<float>(n, 16) : dense_factor_lds<double>(n, 16);
-    if (n % 16) fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d: the dense LU needs 2 * cells divisible by 16", gx, gy);
-    if (need > max_lds_per_block())
-      fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d too large for the dense LU's LDS panel (%zu bytes)", gx, gy, need);
-  } else if (o.coarse_solver == 2) {
-    check_gb_size(gx, gy, o.mg_precision);
+  if (o.coarse_solver != 0) {
+    check_plu_size(o.coarse_solver, gx, gy, o.mg_precision);
   } else {
     if (P->lv.back()->ny > 44) fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d: band width %d exceeds 44", gx, gy, gy);
     const int n = P->lv.back()->ncell, mb = P->lv.back()->ny;
@@ -871,27 +897,14 @@ struct Solver {
     });
   }
 
-  // factors of the coarsest operator: banded LU, or the dense matrix and its pivoted LU
+  // factors of the coarsest operator: banded LU without or LU with partial pivoting
   template <typename T>
   void coarse_factor() {
     const MGLevel& Cc = *P.lv[P.nlev - 1];
-    if (P.csolver == 1) {
-      const int n = 2 * Cc.ncell;
-      const size_t lds = dense_factor_lds<T>(n, 16);
-      dense_factor_prepare<T>(lds);
-      hipLaunchKernelGGL((k_dense_build<T>), dim3(n, P.S), dim3(256), 0, st, P.S, Cc.nx, Cc.ny,
-                         level_J<T>(P.nlev - 1), P.LU.as<T>());
-      timed(ctx, st, HENRY_PROF_DENSE_FACTOR, (long long)P.S, [&] {
-        launch_timed((k_dense_factor<T, 16>), dim3(P.S), dim3(DENSE_THREADS), lds, st, n, P.LU.as<T>(),
-                           P.perm.as<int>());
-      });
-      return;
-    }
-    if (P.csolver == 2) {
-      timed(ctx, st, HENRY_PROF_BAND_FACTOR, (long long)Cc.ncell * P.S, [&] {
-        launch_timed((k_gb_factor<T>), dim3(P.S), dim3(GB_THREADS), gb_factor_lds<T>(Cc.ny), st, P.S, Cc.nx,
-                           Cc.ny, level_J<T>(P.nlev - 1), P.LU.as<T>(), P.perm.as<int>());
-      });
+    if (P.csolver != 0) {
+      auto f = [&] { plu_factor<T>(st, P.S, Cc.nx, Cc.ny, level_J<T>(P.nlev - 1), P.LU.as<double>(), P.perm.as<int>()); };
+      if (P.csolver == 1) timed(ctx, st, HENRY_PROF_DENSE_FACTOR, (long long)P.S, f);
+      else timed(ctx, st, HENRY_PROF_BAND_FACTOR, (long long)Cc.ncell * P.S, f);
       return;
     }
     const size_t lds = (size_t)(P.mb + 1) * (P.mb + 1) * 4 * sizeof(T);
@@ -955,18 +968,10 @@ struct Solver {
       tail<T, TR>(k, b, x);
       return;
     }
-    if (k == P.nlev - 1 && P.csolver == 1) {
-      timed(ctx, st, HENRY_PROF_DENSE_SOLVE, (long long)P.S, [&] {
-        launch_timed((k_dense_solve<T, TR>), dim3(P.S), dim3(DENSE_SOLVE_THREADS), dense_solve_lds<T>(2 * L.ncell), st,
-                           P.S, L.ncell, P.LU.as<T>(), (const int*)P.perm.as<int>(), b, x);
-      });
-      return;
-    }
-    if (k == P.nlev - 1 && P.csolver == 2) {
-      timed(ctx, st, HENRY_PROF_BAND_SOLVE, (long long)L.ncell * P.S, [&] {
-        launch_timed((k_gb_solve<T, TR>), dim3(P.S), dim3(64), gb_solve_lds<T>(L.nx, L.ny), st, P.S, L.nx, L.ny,
-                           (const T*)P.LU.as<T>(), (const int*)P.perm.as<int>(), b, x);
-      });
+    if (k == P.nlev - 1 && P.csolver != 0) {
+      auto f = [&] { plu_solve<T, TR>(st, P.S, L.nx, L.ny, P.LU.as<double>(), P.perm.as<int>(), b, x); };
+      if (P.csolver == 1) timed(ctx, st, HENRY_PROF_DENSE_SOLVE, (long long)P.S, f);
+      else timed(ctx, st, HENRY_PROF_BAND_SOLVE, (long long)L.ncell * P.S, f);
       return;
     }
     if (k == P.nlev - 1) {
@@ -2366,35 +2371,17 @@ int henry_gs_pass(henry_ctx* ctx, henry_grid grid, int S, const double* J, const
 template <typename T>
 static void coarse_solve_t(henry_ctx* ctx, int solver, henry_grid g, int S, const T* J, const T* b, T* x, int tr,
                            void* ws) {
-  const int nc = g.nx * g.ny, n = 2 * nc;
+  const int nc = g.nx * g.ny;
   hipStream_t st = ctx->stream;
+  if (solver != 0) {
+    double* F = static_cast<double*>(ws);
+    int* piv = reinterpret_cast<int*>(F + PluShape(g.nx, g.ny).values() * S);
+    plu_factor<T>(st, S, g.nx, g.ny, J, F, piv);
+    if (tr) plu_solve<T, true>(st, S, g.nx, g.ny, F, piv, b, x);
+    else plu_solve<T, false>(st, S, g.nx, g.ny, F, piv, b, x);
+    return;
+  }
   T* LU = static_cast<T*>(ws);
-  if (solver == 1) {
-    int* perm = reinterpret_cast<int*>(LU + (size_t)n * n * S);
-    const size_t lds = dense_factor_lds<T>(n, 16);
-    dense_factor_prepare<T>(lds);
-    hipLaunchKernelGGL((k_dense_build<T>), dim3(n, S), dim3(256), 0, st, S, g.nx, g.ny, J, LU);
-    hipLaunchKernelGGL((k_dense_factor<T, 16>), dim3(S), dim3(DENSE_THREADS), lds, st, n, LU, perm);
-    if (tr)
-      hipLaunchKernelGGL((k_dense_solve<T, true>), dim3(S), dim3(DENSE_SOLVE_THREADS), dense_solve_lds<T>(n), st, S, nc, LU,
-                         (const int*)perm, b, x);
-    else
-      hipLaunchKernelGGL((k_dense_solve<T, false>), dim3(S), dim3(DENSE_SOLVE_THREADS), dense_solve_lds<T>(n), st, S, nc,
-                         LU, (const int*)perm, b, x);
-    return;
-  }
-  if (solver == 2) {
-    int* piv = reinterpret_cast<int*>(LU + gb_stride(g.nx, g.ny) * S);
-    hipLaunchKernelGGL((k_gb_factor<T>), dim3(S), dim3(GB_THREADS), gb_factor_lds<T>(g.ny), st, S, g.nx, g.ny, J, LU,
-                       piv);
-    if (tr)
-      hipLaunchKernelGGL((k_gb_solve<T, true>), dim3(S), dim3(64), gb_solve_lds<T>(g.nx, g.ny), st, S, g.nx, g.ny,
-                         (const T*)LU, (const int*)piv, b, x);
-    else
-      hipLaunchKernelGGL((k_gb_solve<T, false>), dim3(S), dim3(64), gb_solve_lds<T>(g.nx, g.ny), st, S, g.nx, g.ny,
-                         (const T*)LU, (const int*)piv, b, x);
-    return;
-  }
   const int mb = g.ny;
   hipLaunchKernelGGL((k_band_factor<T>), dim3(S), dim3(64), (size_t)(mb + 1) * (mb + 1) * 4 * sizeof(T), st, S, g.nx,
                      g.ny, J, LU);
@@ -2415,21 +2402,18 @@ int henry_coarse_solve(henry_ctx* ctx, int solver, int precision, henry_grid coa
     if (coarse.nx < 1 || coarse.ny < 1 || S < 1 || !J || !b || !x) fail(HENRY_EINVAL, "grid, S or a NULL array");
     if (solver < 0 || solver > 2) fail(HENRY_EINVAL, "solver must be 0 (banded), 1 (dense) or 2 (pivoted band)");
     if (precision != 64 && precision != 32) fail(HENRY_EINVAL, "precision must be 64 or 32");
-    const int nc = coarse.nx * coarse.ny, n = 2 * nc;
+    const int nc = coarse.nx * coarse.ny;
     const size_t N = (size_t)nc * S;
     const size_t tsz = precision == 64 ? 8 : 4;
-    if (solver == 1) {
-      const size_t need = precision == 64 ? dense_factor_lds<double>(n, 16) : dense_factor_lds<float>(n, 16);
-      if (n % 16 || need > max_lds_per_block()) fail(HENRY_EUNSUPPORTED, "grid %dx%d: no dense LU", coarse.nx, coarse.ny);
-    } else if (solver == 2) {
-      check_gb_size(coarse.nx, coarse.ny, precision);
+    if (solver != 0) {
+      check_plu_size(solver, coarse.nx, coarse.ny, precision);
     } else {
       if (coarse.ny > 44 || band_solve_lds<double>(nc, coarse.ny, 1) > 64 * 1024)
         fail(HENRY_EUNSUPPORTED, "grid %dx%d: no banded LU", coarse.nx, coarse.ny);
     }
-    const size_t fac = solver == 1   ? (size_t)n * n * S * tsz + (size_t)n * S * sizeof(int)
-                       : solver == 2 ? gb_stride(coarse.nx, coarse.ny) * S * tsz + (size_t)n * S * sizeof(int)
-                                     : (size_t)nc * (2 * coarse.ny + 1) * 4 * S * tsz;
+    const PluShape sh(coarse.nx, coarse.ny);
+    const size_t fac = solver != 0 ? sh.values() * S * sizeof(double) + sh.pivots() * S * sizeof(int)
+                                   : (size_t)nc * (2 * coarse.ny + 1) * 4 * S * tsz;
     const size_t conv = precision == 32 ? (20 * N + 4 * N) * sizeof(float) : 0;   // FP32 copies of J, b and x
     ctx->kws.alloc(conv + fac);
     hipStream_t st = ctx->stream;
@@ -2605,20 +2589,6 @@ int mlmc_optimal_samples(int L, const double* V_l, const double* s_l, double eps
 // ---------------------------------------------------------------------------
 namespace {
 
-// The coarsest vertex grid is inverted with partial pivoting in one workgroup per sample; its
-// dense matrix may need more LDS than a launch gets by default: raise the limit once per device.
-template <typename K>
-static void vc_lds_prepare(K* kernel, size_t bytes) {
-  static std::mutex mu;
-  static bool done[64] = {};
-  int dev = 0;
-  HIPCHK(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lk(mu);
-  if (dev >= 0 && dev < 64 && done[dev]) return;
-  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes));
-  if (dev >= 0 && dev < 64) done[dev] = true;
-}
 static size_t vc_dense_lds(int n) {   // the matrix and the row order; the inverse's columns too where they fit
   const size_t a = (size_t)n * n * sizeof(double) + (size_t)n * sizeof(int) + 16, x = (size_t)n * n * sizeof(double);
   return a + x <= VC_LDS_MAX ? a + x : a;
@@ -2721,8 +2691,8 @@ struct VCSolver {
       if (nj) tailJ.alloc(nj * S * tsz);
       coarseJ.alloc(36 * (size_t)lv.back()->nv * S * tsz);
       inv.alloc((size_t)n * n * S * 8);
-      if (prec == 32) vc_lds_prepare(&k_vc_dense_inverse<float>, VC_LDS_MAX);
-      else vc_lds_prepare(&k_vc_dense_inverse<double>, VC_LDS_MAX);
+      if (prec == 32) lds_prepare(&k_vc_dense_inverse<float>, VC_LDS_MAX);
+      else lds_prepare(&k_vc_dense_inverse<double>, VC_LDS_MAX);
     }
     if (prec == 32) {
       mb.alloc(2 * NV * 4);

@@ -20,10 +20,16 @@
 
 #include <hip/hip_runtime.h>
 
-#include "henry_gbsv.hpp"   // lds_barrier
 #include "henry_kernels.hpp"
 
 namespace henry {
+
+// Barrier for LDS traffic only: this wavefront's LDS operations complete, then every wavefront
+// of the workgroup arrives.  Unlike __syncthreads() it does not wait for global loads and stores
+// in flight (prefetches, results nobody in the kernel reads back), which would put a memory
+// latency on every step.  The memory clobber keeps the compiler from moving memory accesses
+// across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 constexpr int TAIL_LEVELS = 3;     // smoothed grids in one launch at most
 constexpr int TAIL_CELLS = 512;    // cells of the finest of them at most: one per thread

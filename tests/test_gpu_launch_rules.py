@@ -161,3 +161,41 @@ def test_vertex_coarse_grids_in_one_launch(hx, prec, nx, ny, S, opts):
     if opts.get("coarse_nx", 8) not in (10, 12):
         newton, bicg = r.stats[:, 0].sum().item(), r.stats[:, 1].sum().item()
         assert bicg <= 1.35 * newton, (newton, bicg)
+
+
+@pytest.mark.parametrize("nx,ny,S,solver", [
+    (2, 2, 1, 2),        # one panel, wider than the matrix
+    (3, 3, 3, 2),        # 18 unknowns: a last panel of 2
+    (4, 4, 2, 1), (16, 8, 17, 1), (32, 16, 130, 1),
+    (9, 19, 2, 2),       # the longer side second
+    (40, 19, 2, 2),      # the widest band
+    (60, 9, 3, 2),
+    (32, 32, 2, 1),      # two rows a lane (FP32 operators only)
+])
+def test_pivoted_solvers_at_panel_edges(hx, nx, ny, S, solver):
+    """LU with partial pivoting, plain and transposed, on random blocks whose first cell has a zero
+    pivot: normwise backward error at most 200 eps (n eps growth of a stable elimination, with
+    its constants) and the error against numpy within its condition."""
+    import paper_2403_17018_amd as P
+    from tests.test_gpu_kernels import _blocks_to_sparse
+    rng = np.random.default_rng(nx * 100 + ny)
+    J = rng.normal(size=(20, ny, nx, S))
+    J[4:8, :, 0] = J[8:12, :, -1] = 0.0
+    J[12:16, 0] = J[16:20, -1] = 0.0
+    J[0:4, 0, 0] = np.array([0.0, 1.0, 1.0, 0.0])[:, None]
+    b = rng.normal(size=(2, ny, nx, S))
+    for prec in ((32,) if (nx, ny) == (32, 32) else (64, 32)):
+        if prec == 32:
+            J, b = J.astype(np.float32).astype(float), b.astype(np.float32).astype(float)
+        for tr in (False, True):
+            x = hx.coarse_solve(_cu(J), _cu(b), P.grid(nx, ny, 1), solver, prec, tr).cpu().numpy()
+            for s in sorted({0, S - 1}):
+                A = _blocks_to_sparse(J[..., s], nx, ny).toarray()
+                A = A.T if tr else A
+                vec = lambda a: np.stack([a[0, ..., s].ravel(), a[1, ..., s].ravel()], axis=1).ravel()
+                bs, xs = vec(b), vec(x)
+                eps = 2.2e-16 if prec == 64 else 6e-8   # FP32: rounding of the result alone
+                berr = np.abs(A @ xs - bs).max() / (np.abs(A).sum(1).max() * np.abs(xs).max() + np.abs(bs).max())
+                assert berr <= 200 * eps, (prec, tr, s, berr)
+                ref = np.linalg.solve(A, bs)
+                assert np.abs(xs - ref).max() <= 1000 * eps * np.linalg.cond(A, np.inf) * np.abs(ref).max()
