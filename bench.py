@@ -32,8 +32,10 @@ from paper_2403_17018_amd.metrics import (BYTES_PER_UNIT as BYTES, HBM_PEAK_GBS,
                                           MetricsLog, batch_record)
 
 METRICS = None   # MetricsLog of --metrics: one JSON line per measured batch
-KERNEL_NAME = dict(gs="k_gs_colour", spmv="k_spmv_dot", assemble="k_assemble", restrict="k_residual_restrict",
-                   prolong="k_gs_colour (fused prolongation)")
+KERNEL_NAME = {64: dict(gs="k_gs_free", spmv="k_spmv_free", assemble="k_assemble", restrict="k_restrict_free",
+                        prolong="k_gs_free (fused prolongation)"),
+               32: dict(gs="k_gs_colour", spmv="k_spmv_dot", assemble="k_assemble", restrict="k_residual_restrict",
+                        prolong="k_gs_colour (fused prolongation)")}
 
 
 def host_cores():
@@ -362,9 +364,9 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
     per_launch_bytes = units / n * BYTES[prec][cls]
     achieved = per_launch_bytes / (ms / n * 1e-3) / 1e9
     return dict(value=S * g.nsteps / dt, ms_per_step=dt * 1e3,
-                roofline={"bound": "hbm", "kernel": KERNEL_NAME[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
+                roofline={"bound": "hbm", "kernel": KERNEL_NAME[prec][cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
                           "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                          "traffic": pmc_traffic(KERNEL_NAME[cls], prec, workload, model),
+                          "traffic": pmc_traffic(KERNEL_NAME[prec][cls], prec, workload, model),
                           "avg_launch_us": ms / n * 1e3, "launches": n,
                           "algorithmic_bytes_per_launch": per_launch_bytes},
                 kernel_classes_ms={k: round(v[2], 3) for k, v in prof.items()},
@@ -429,9 +431,9 @@ def bench_vc(hx, P, S=VC_SAMPLES, graphs=1, prec=64):
                     + ("; FP32 multigrid and Jacobian" if prec == 32 else "")
                     + ("; BiCGStab iterations replayed from a hipGraph" if graphs else ""),
         "unit": "sample-timesteps/s", "value": S * g.nsteps / dt, "ms_per_step": dt * 1e3,
-        "roofline": {"bound": "hbm", "kernel": VC_KERNEL_NAME[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": VC_KERNEL_NAME[prec][cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": pmc_traffic(VC_KERNEL_NAME[cls], prec, "f3_vc_level1_paper", "paper", "henry_vc.hpp"),
+                     "traffic": pmc_traffic(VC_KERNEL_NAME[prec][cls], prec, "f3_vc_level1_paper", "paper", "henry_vc.hpp"),
                      "avg_launch_us": ms / n * 1e3, "launches": n, "algorithmic_bytes_per_launch": per_launch,
                      "timed_in": "a stream-launched repeat of the run" if graphs else "the timed run"},
         "kernel_classes_ms": {k: round(prof_k[k][2], 3) for k in table},

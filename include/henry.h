@@ -130,9 +130,11 @@ typedef struct {
                                  update) is <= newton_predict * newton_tol; 0 disables [1] */
   double newton_jac_reuse;    /* > 0: after a Newton update whose size (as for newton_tol) is
                                  <= newton_jac_reuse for every sample still iterating, the next
-                                 iteration keeps the Jacobian, the multigrid hierarchy and the
-                                 coarse factors (a chord step; only R is reassembled).  The first
-                                 iteration of each step always assembles.  0 disables [1e-3] */
+                                 iteration keeps the multigrid hierarchy, the coarse factors and
+                                 the stored Jacobian (a chord step; only R is reassembled; large
+                                 FP64 batches form the fine operator from the current state, so
+                                 their step stays Newton's).  The first iteration of each step
+                                 always assembles.  0 disables [1e-3] */
   int mg_cycle;               /* 1: V-cycle; 2: W-cycle (two coarse cycles per level above the
                                  coarsest) [1] */
   int adjoint_guess;          /* first guess of each transposed solve of the reverse sweep.

@@ -32,6 +32,7 @@
 #include "../../include/henry.h"
 #include "henry_kernels.hpp"
 #include "henry_coarse.hpp"
+#include "henry_free.hpp"
 #include "henry_tail.hpp"
 #include "henry_plu.hpp"
 #include "henry_mlmc.hpp"
@@ -304,6 +305,14 @@ static FieldParams make_fp(const henry_problem& pr) {
 // ---------------------------------------------------------------------------
 // per-shape plan: multigrid hierarchy and Krylov workspace of one batch
 // ---------------------------------------------------------------------------
+// From this many cell-samples on the FP64 forward solves read no stored Jacobian: their passes are
+// bound by memory there, and by launches below, of which a cycle has one more (a stored diagonal
+// block lets the pre-smoothing pass form the red half on the fly).  Stored and formed, ms a solve:
+// 8192 cell-samples 30.8 and 33.1, 51 200: 35.9 and 36.9, 131 072: 42.7 and 40.5 (32x16 cells),
+// 42.2 and 43.1 (64x32), 55.5 and 56.2 (128x64), and these three in concurrent streams 142 and
+// 130; 512 000: 54.7 and 47.4, 524 288: 60.4 and 53.8 (128x64), 74.1 and 63.5 (256x128), 681 984:
+// 108.5 and 90.3, 2 097 152: 169.4 and 130.2.
+constexpr size_t FREE_MIN = 1 << 17;
 struct MGLevel {
   int nx, ny, ncell;
   Grid2 G;
@@ -331,6 +340,7 @@ struct Plan {
   DevBuf nhist;            // per sample: last undamped Newton update size, previous |R|^2
   size_t lu_stride;
   int mb;
+  bool free_rows = false;  // forward solves form their operator's rows from the state (henry_free.hpp)
   bool inverse = false;    // the coarsest operator is applied as an explicit inverse (henry_tail.hpp)
   DevBuf tailJ;            // Jacobians of the grids that the cycle takes in one launch
   int* h_ctrl = nullptr;   // pinned mirror of ctrl
@@ -689,6 +699,7 @@ static std::unique_ptr<Plan> make_plan(int nx, int ny, int S, const henry_solver
     gy /= 2;
   }
   P->nlev = (int)P->lv.size();
+  P->free_rows = o.mg_precision == 64 && P->N >= FREE_MIN;
   if (o.coarse_solver != 0) {
     check_plu_size(o.coarse_solver, gx, gy, o.mg_precision);
   } else {
@@ -827,7 +838,19 @@ struct Solver {
     }
   }
 
-  // Residual only: the Jacobian hierarchy and the coarse factors of an earlier iterate are kept.
+  // The FP64 forward solves form their operator's rows from the state (henry_free.hpp) from
+  // FREE_MIN cell-samples on; the FP32 cycle, whose stored row is no larger than the state it would
+  // be formed from, and the transposed solves read stored Jacobians.
+  template <typename T, bool TR>
+  bool free_rows() const { return sizeof(T) == 8 && !TR && P.free_rows; }
+  FreeOp free_op(int k) const {
+    if (k == 0) return {P.p.as<double>(), P.c.as<double>(), P.phi.as<double>(), P.K.as<double>()};
+    const MGLevel& L = *P.lv[k];
+    return {L.p.as<double>(), L.c.as<double>(), L.phi.as<double>(), L.K.as<double>()};
+  }
+
+  // Residual only: the coarse operators and factors of an earlier iterate are kept, and the stored
+  // fine Jacobian where there is one (rows formed from the state follow it at no cost).
   void assemble_residual() {
     const Map& m = P.m;
     hipLaunchKernelGGL((k_assemble<true, double, false, false>), asm_grid(m, P.G), asm_block(m), asm_lds(m.SX), st, m, P.G,
@@ -840,8 +863,13 @@ struct Solver {
   template <typename T>
   void assemble_all(bool tr = false) {
     const Map& m = P.m;
+    const bool rows = !tr && free_rows<T, false>();
     timed(ctx, st, HENRY_PROF_ASSEMBLE, (long long)P.N, [&] {
-      if (spmv32())   // only the FP32 Jacobian: the multigrid and the Krylov products read it
+      if (rows && P.nlev > 1)   // (a grid that is its own coarsest is factored from its Jacobian)
+        launch_timed((k_assemble<true, double, false, false>), asm_grid(m, P.G), asm_block(m), asm_lds(m.SX), st, m, P.G,
+                           phys, P.p.as<double>(), P.c.as<double>(), P.c_old.as<double>(), P.phi.as<double>(),
+                           P.K.as<double>(), P.uin.as<double>(), P.R.as<double>(), (double*)nullptr, (float*)nullptr);
+      else if (spmv32())   // only the FP32 Jacobian: the multigrid and the Krylov products read it
         launch_timed((k_assemble<true, float, false>), asm_grid(m, P.G), asm_block(m), asm_lds(m.SX), st, m, P.G,
                            phys, P.p.as<double>(), P.c.as<double>(), P.c_old.as<double>(), P.phi.as<double>(),
                            P.K.as<double>(), P.uin.as<double>(), P.R.as<double>(), P.J32.as<float>(), (float*)nullptr);
@@ -862,6 +890,7 @@ struct Solver {
       const double* fc_ = k == 1 ? P.c.as<double>() : F.c.as<double>();
       hipLaunchKernelGGL(k_restrict_state, grid_cells(m, C.ncell), block_of(m), 0, st, m, F.G, C.G, fp_, fc_,
                          C.p.as<double>(), C.c.as<double>());
+      if (rows && k < P.nlev - 1) continue;
       hipLaunchKernelGGL((k_assemble<false, T, false>), asm_grid(m, C.G), asm_block(m), asm_lds(m.SX), st, m, C.G,
                          phys_level(k), C.p.as<double>(), C.c.as<double>(), (const double*)nullptr,
                          C.phi.as<double>(), C.K.as<double>(), P.uin.as<double>(), (double*)nullptr, C.J.as<T>(),
@@ -947,6 +976,19 @@ struct Solver {
     });
   }
 
+  // A colour pass of level k with rows formed from the state (modes of k_gs_free).
+  void gs_free(int k, int colour, int mode, const double* b, double* x) {
+    const Map& m = P.m;
+    const MGLevel &L = *P.lv[k], &C = *P.lv[k + 1];
+    const dim3 gg = grid_cells(m, L.ny * ((L.nx + 1) / 2)), bb = block_of(m);
+    const Phys ph = phys_level(k);
+    const FreeOp A = free_op(k);
+    const double* e = mode == 2 ? C.x.as<double>() : nullptr;
+    if (mode == 1) launch_timed((k_gs_free<1>), gg, bb, 0, st, m, L.G, C.G, colour, ph, A, b, x, e);
+    else if (mode == 2) launch_timed((k_gs_free<2>), gg, bb, 0, st, m, L.G, C.G, colour, ph, A, b, x, e);
+    else launch_timed((k_gs_free<0>), gg, bb, 0, st, m, L.G, C.G, colour, ph, A, b, x, e);
+  }
+
   // One multigrid cycle x = M^{-1} b on level k (TR: the same cycle built from transposed
   // operators, a preconditioner for J^T): a V-cycle, or a W-cycle (mg_cycle 2: the coarse
   // problem gets two cycles, the second from the first's result).  zero: x starts at 0.
@@ -986,6 +1028,7 @@ struct Solver {
       });
       return;
     }
+    const bool rows = free_rows<T, TR>();
     const T* J = level_J<T>(k);
     const int half = (L.nx + 1) / 2;
     // fine-grid smoother passes that read neighbours are timed as one class
@@ -1006,14 +1049,21 @@ struct Solver {
         launch_timed((k_gs_colour<T, TR, 0, SP>), gg, bb, 0, st, mg, L.G, C.G, colour, J, b, x, (const T*)nullptr);
     };
     auto gs = [&](int colour, int mode) {
-      auto f = [&] { wide([&](auto sp_tag) { gs_launch(sp_tag, colour, mode); }); };
+      auto f = [&] {
+        if constexpr (sizeof(T) == 8) {
+          if (rows) return gs_free(k, colour, mode, b, x);
+        }
+        wide([&](auto sp_tag) { gs_launch(sp_tag, colour, mode); });
+      };
       if (k == 0 && mode == 0) timed(ctx, st, HENRY_PROF_GS, half_units, f);
       else f();
     };
     // One pre-smoothing sweep followed by post-smoothing: the red half of the sweep is
     // never stored (its values are D^{-1} b, formed where they are read, and the first
-    // post-smoothing pass recomputes red without them).
-    const bool implicit_red = zero && o.nu_pre == 1 && o.nu_post >= 1;
+    // post-smoothing pass recomputes red without them).  Rows formed from the state have no stored
+    // diagonal blocks to read there: they store the red half.
+    const bool exact_red = zero && o.nu_pre == 1 && o.nu_post >= 1;
+    const bool implicit_red = exact_red && !rows;
     if (implicit_red) {
       gs(1, 3);
     } else {
@@ -1023,6 +1073,13 @@ struct Solver {
       }
     }
     auto rr = [&] {
+      if constexpr (sizeof(T) == 8) {
+        if (rows) {
+          launch_timed(k_restrict_free, grid_cells(m, C.ncell), block_of(m), 0, st, m, L.G, C.G, exact_red ? 1 : 0,
+                       phys_level(k), free_op(k), b, x, C.b.as<T>());
+          return;
+        }
+      }
       wide([&](auto sp_tag) {
         constexpr int SP = decltype(sp_tag)::value;
         const Map& mg = wide_map(SP);
@@ -1168,6 +1225,13 @@ struct Solver {
   template <int NDOT, bool TR, typename TX>
   void spmv(const TX* x, double* y, const double* d0, const double* yb) {
     const Map& m = P.m;
+    if constexpr (sizeof(TX) == 8 && !TR) {
+      if (P.free_rows) {
+        launch_timed((k_spmv_free<NDOT>), grid_red(m), block_of(m), 0, st, m, P.G, phys, free_op(0), x, y, d0,
+                           P.part.as<double>(), yb);
+        return;
+      }
+    }
     if (spmv32())
       launch_timed((k_spmv_dot<NDOT, TR, float, TX>), grid_red(m), block_of(m), 0, st, m, P.G,
                          (const float*)P.J32.as<float>(), x, y, d0, P.part.as<double>(), yb);

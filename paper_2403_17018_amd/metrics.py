@@ -23,9 +23,10 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 # Algorithmic bytes per unit of each bandwidth-bound kernel class (FP64 / FP32 multigrid): what
 # one launch must move per cell-sample (per swept cell for the smoother, per fine cell for the
 # restriction), counted from the arrays the kernel reads and writes.  The profiler's units are
-# the cell-samples each launch covers.
+# the cell-samples each launch covers.  FP64: the rows formed from p, c, phi and K (smaller batches
+# read a stored row of 160 bytes instead).
 BYTES_PER_UNIT = {
-    64: dict(gs=208, spmv=136, assemble=216, restrict=76, prolong=216),
+    64: dict(gs=112, spmv=88, assemble=56, restrict=44, prolong=120),
     32: dict(gs=104, spmv=96, assemble=136, restrict=38, prolong=108),
 }
 # The vertex-centred path (henry_vc_solve), per vertex-sample: the four-colour pass reads the
