@@ -28,14 +28,15 @@ sys.path.insert(0, ROOT)
 from henry_inputs import WORKLOADS, draw_theta, level_grid  # noqa: E402
 
 # HBM peak and the algorithmic bytes per unit of each kernel class (FP64 / FP32 multigrid)
-from paper_2403_17018_amd.metrics import (BYTES_PER_UNIT as BYTES, HBM_PEAK_GBS, VC_BYTES_PER_UNIT,  # noqa: E402
-                                          MetricsLog, batch_record)
+from paper_2403_17018_amd.metrics import (BYTES_MARCH, BYTES_ROWS, HBM_PEAK_GBS, VC_BYTES_PER_UNIT,  # noqa: E402
+                                          MetricsLog, batch_record, bytes_per_unit)
 
 METRICS = None   # MetricsLog of --metrics: one JSON line per measured batch
-KERNEL_NAME = {64: dict(gs="k_gs_free", spmv="k_spmv_free", assemble="k_assemble", restrict="k_restrict_free",
-                        prolong="k_gs_free (fused prolongation)"),
-               32: dict(gs="k_gs_colour", spmv="k_spmv_dot", assemble="k_assemble", restrict="k_residual_restrict",
-                        prolong="k_gs_colour (fused prolongation)")}
+KERNEL_NAME = dict(gs="k_gs_colour", spmv="k_spmv_dot", assemble="k_assemble", restrict="k_residual_restrict",
+                   prolong="k_gs_colour (fused prolongation)")
+KERNEL_NAME_ROWS = dict(KERNEL_NAME, gs="k_gs_free", spmv="k_spmv_free", restrict="k_restrict_free",
+                        prolong="k_gs_free (fused prolongation)")
+KERNEL_NAME_MARCH = dict(KERNEL_NAME_ROWS, restrict="k_march", prolong="k_march")
 
 
 def host_cores():
@@ -359,14 +360,16 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
         METRICS.write(batch_record(workload, g, r, seconds=dt, prof=prof, mg_precision=prec, timed_runs=steps,
                                    coarse=f"{opts.coarse_nx}x{opts.coarse_ny}", coarse_solver=opts.coarse_solver))
     st = r.stats.cpu()
-    cls = max(BYTES[prec], key=lambda k: prof[k][2])      # dominant kernel class by summed time
+    table = bytes_per_unit(prec, g.nx * g.ny * S)
+    name = KERNEL_NAME_MARCH if table is BYTES_MARCH else KERNEL_NAME_ROWS if table is BYTES_ROWS else KERNEL_NAME
+    cls = max(table, key=lambda k: prof[k][2])            # dominant kernel class by summed time
     n, units, ms = prof[cls]
-    per_launch_bytes = units / n * BYTES[prec][cls]
+    per_launch_bytes = units / n * table[cls]
     achieved = per_launch_bytes / (ms / n * 1e-3) / 1e9
     return dict(value=S * g.nsteps / dt, ms_per_step=dt * 1e3,
-                roofline={"bound": "hbm", "kernel": KERNEL_NAME[prec][cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
+                roofline={"bound": "hbm", "kernel": name[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
                           "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                          "traffic": pmc_traffic(KERNEL_NAME[prec][cls], prec, workload, model),
+                          "traffic": pmc_traffic(name[cls], prec, workload, model),
                           "avg_launch_us": ms / n * 1e3, "launches": n,
                           "algorithmic_bytes_per_launch": per_launch_bytes},
                 kernel_classes_ms={k: round(v[2], 3) for k, v in prof.items()},
@@ -431,9 +434,9 @@ def bench_vc(hx, P, S=VC_SAMPLES, graphs=1, prec=64):
                     + ("; FP32 multigrid and Jacobian" if prec == 32 else "")
                     + ("; BiCGStab iterations replayed from a hipGraph" if graphs else ""),
         "unit": "sample-timesteps/s", "value": S * g.nsteps / dt, "ms_per_step": dt * 1e3,
-        "roofline": {"bound": "hbm", "kernel": VC_KERNEL_NAME[prec][cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": VC_name[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": pmc_traffic(VC_KERNEL_NAME[prec][cls], prec, "f3_vc_level1_paper", "paper", "henry_vc.hpp"),
+                     "traffic": pmc_traffic(VC_name[cls], prec, "f3_vc_level1_paper", "paper", "henry_vc.hpp"),
                      "avg_launch_us": ms / n * 1e3, "launches": n, "algorithmic_bytes_per_launch": per_launch,
                      "timed_in": "a stream-launched repeat of the run" if graphs else "the timed run"},
         "kernel_classes_ms": {k: round(prof_k[k][2], 3) for k in table},

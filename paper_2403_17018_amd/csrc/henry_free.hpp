@@ -26,15 +26,38 @@ struct CellState {
 
 __device__ __forceinline__ CellState ld_state(const FreeOp& A, size_t q) { return {A.p[q], A.c[q], A.phi[q], A.K[q]}; }
 
-// The constants of a row, set up once per thread (all uniform).
+// The constants of a row, set up on the host (kernel arguments: scalar registers).
 struct FreePhys {
   double w[2];      // face area over distance, x and y faces
   double qd[2];     // ... times Dm
   double gA;        // g times the y face's area
-  double inv_mu, hd;
-  __device__ __forceinline__ explicit FreePhys(const Phys& P)
-      : w{P.hy / P.hx, P.hx / P.hy}, qd{P.Dm * w[0], P.Dm * w[1]}, gA(P.g * P.hx), inv_mu(1.0 / P.mu), hd(0.5 * P.drho) {}
+  double inv_mu, hd, vt;
+  double side_dif;  // 2 Dm hy / hx
+  double side_k;    // outflow through the right side per pressure difference and K: hy / (mu hx / 2)
+  FreePhys() = default;
+  explicit FreePhys(const Phys& P)
+      : w{P.hy / P.hx, P.hx / P.hy}, qd{P.Dm * w[0], P.Dm * w[1]}, gA(P.g * P.hx), inv_mu(1.0 / P.mu),
+        hd(0.5 * P.drho), vt(P.vol / P.tau), side_dif(2.0 * P.Dm * P.hy / P.hx), side_k(2.0 * P.hy / (P.mu * P.hx)) {}
 };
+
+// The left and right sides' share of a cell's centre block (boundary_terms).
+__device__ __forceinline__ void side_terms(const Phys& P, const FreePhys& F, int nx, int i, int j, const CellState& o,
+                                           double (&D)[4]) {
+  const double rP = P.rho0 + P.drho * o.c, dif = o.phi * F.side_dif;
+  if (i == 0) D[3] += dif * (P.drho * (o.c - P.c_left) + rP);
+  if (i == nx - 1) {
+    const double k = o.K * F.side_k, y = -P.Ly + (j + 0.5) * P.hy;
+    const double u = k * (o.p + P.rho1 * P.g * y);
+    const bool inflow = u < 0.0;
+    const double dFdp = (inflow ? P.rho1 : rP) * k, dFdc = inflow ? 0.0 : P.drho * u;
+    const double cb = inflow ? 1.0 : o.c;
+    D[0] += dFdp;
+    D[1] += dFdc;
+    D[2] += cb * dFdp;
+    D[3] += cb * dFdc + (inflow ? 0.0 : rP * u);
+    if (P.right_dir) D[3] += dif * (P.drho * (o.c - 1.0) + rP);
+  }
+}
 
 // 1/x of a normal x to rounding: the hardware's estimate and two Newton steps.
 __device__ __forceinline__ double rcp_normal(double x) {
@@ -51,7 +74,8 @@ struct FaceRow {
 
 // NORTH: a face between rows; HIGH: the cell is the face's high (east, north) side.
 template <bool NORTH, bool HIGH>
-__device__ __forceinline__ FaceRow face_row(const Phys& P, const FreePhys& F, const CellState& own, const CellState& nb) {
+__device__ __forceinline__ FaceRow face_row(const Phys& P, const FreePhys& F, const CellState& own,
+                                            const CellState& nb) {
   const CellState &L = HIGH ? nb : own, &H = HIGH ? own : nb;
   const double kf = 2.0 * L.K * H.K * rcp_normal(L.K + H.K) * F.inv_mu;
   const double rf = P.rho0 + F.hd * (L.c + H.c);
@@ -82,8 +106,8 @@ __device__ __forceinline__ FaceRow face_row(const Phys& P, const FreePhys& F, co
 // A row being summed: y = the neighbours' part of A x, D = the centre block.
 struct RowSum {
   double y0 = 0.0, y1 = 0.0, D[4];
-  __device__ __forceinline__ RowSum(const Phys& P, const CellState& own) {
-    const double v = P.vol * own.phi / P.tau;
+  __device__ __forceinline__ RowSum(const Phys& P, const FreePhys& F, const CellState& own) {
+    const double v = F.vt * own.phi;
     D[0] = D[2] = 0.0;
     D[1] = v * P.drho;
     D[3] = v * (P.rho0 + 2.0 * P.drho * own.c);
@@ -97,11 +121,6 @@ struct RowSum {
   __device__ __forceinline__ void neighbour(const FaceRow& f, double x0, double x1) {
     y0 += f.sb * x1 - f.a * x0;
     y1 += f.dN * x1 - f.ac * x0;
-  }
-  __device__ __forceinline__ void sides(const Phys& P, int nx, int i, int j, const CellState& own) {
-    if (i != 0 && i != nx - 1) return;
-    double r0 = 0.0, r1 = 0.0;
-    boundary_terms(P, nx, i, j, own.p, own.c, own.phi, own.K, 0.0, r0, r1, D);
   }
   // x = D^{-1} (b - y)
   __device__ __forceinline__ void solve(double b0, double b1, double& x0, double& x1) const {
@@ -117,8 +136,8 @@ struct RowSum {
 // neighbour n (0 W, 1 E, 2 S, 3 N) at index q.  All loads are issued before any arithmetic; a
 // neighbour outside the grid reads the cell itself and is left out.
 template <bool WANT_D, bool WANT_Y, typename XV>
-__device__ __forceinline__ RowSum free_row(const FreeOp& A, const Phys& P, int nx, int ny, int S, size_t id, int i, int j,
-                                           const CellState& own, XV&& xv) {
+__device__ __forceinline__ RowSum free_row(const FreeOp& A, const Phys& P, const FreePhys& F, int nx, int ny, int S,
+                                           size_t id, int i, int j, const CellState& own, XV&& xv) {
   const bool ok[4] = {i > 0, i < nx - 1, j > 0, j < ny - 1};
   const long long step[4] = {-(long long)S, S, -(long long)nx * S, (long long)nx * S};
   CellState nb[4];
@@ -129,8 +148,7 @@ __device__ __forceinline__ RowSum free_row(const FreeOp& A, const Phys& P, int n
     nb[n] = ld_state(A, q);
     if (WANT_Y) xv(n, q, xa[n], xb[n]);
   }
-  const FreePhys F(P);
-  RowSum r(P, own);
+  RowSum r(P, F, own);
   auto add = [&](int n, const FaceRow& f) {
     if (!ok[n]) return;
     if (WANT_D) r.centre(f);
@@ -140,15 +158,15 @@ __device__ __forceinline__ RowSum free_row(const FreeOp& A, const Phys& P, int n
   add(1, face_row<false, false>(P, F, own, nb[1]));
   add(2, face_row<true, true>(P, F, own, nb[2]));
   add(3, face_row<true, false>(P, F, own, nb[3]));
-  if (WANT_D) r.sides(P, nx, i, j, own);
+  if (WANT_D) side_terms(P, F, nx, i, j, own, r.D);
   return r;
 }
 
 // One colour of a red-black sweep, as k_gs_colour: MODE 0 plain, 1 from x = 0 (neighbours' x not
 // read), 2 with the coarse correction e prolonged onto the neighbours on the fly.
 template <int MODE>
-__global__ void __launch_bounds__(256) k_gs_free(Map m, Grid2 G, Grid2 Gc, int colour, Phys P, FreeOp A,
-                                                 const double* __restrict__ b, double* __restrict__ x,
+__global__ void __launch_bounds__(256) k_gs_free(Map m, Grid2 G, Grid2 Gc, int colour, Phys P, FreePhys F,
+                                                 FreeOp A, const double* __restrict__ b, double* __restrict__ x,
                                                  const double* __restrict__ e) {
   int s, mc, sb, cb;
   const int half = (G.nx + 1) >> 1;
@@ -172,7 +190,7 @@ __global__ void __launch_bounds__(256) k_gs_free(Map m, Grid2 G, Grid2 Gc, int c
       x1 += v1;
     }
   };
-  const RowSum r = free_row<true, MODE != 1>(A, P, G.nx, G.ny, m.S, id, i, j, own, xv);
+  const RowSum r = free_row<true, MODE != 1>(A, P, F, G.nx, G.ny, m.S, id, i, j, own, xv);
   double x0, x1;
   r.solve(b0, b1, x0, x1);
   x[id] = x0;
@@ -182,9 +200,9 @@ __global__ void __launch_bounds__(256) k_gs_free(Map m, Grid2 G, Grid2 Gc, int c
 // Residual and restriction after a black pass, as k_residual_restrict: only the red rows' residuals
 // are not zero.  exact: red x = D^{-1} b (one pre-smoothing sweep from x = 0), so the residual is
 // minus the neighbours' part.
-__global__ void __launch_bounds__(256) k_restrict_free(Map m, Grid2 G, Grid2 Gc, int exact, Phys P, FreeOp A,
-                                                       const double* __restrict__ b, const double* __restrict__ x,
-                                                       double* __restrict__ bH) {
+__global__ void __launch_bounds__(256) k_restrict_free(Map m, Grid2 G, Grid2 Gc, int exact, Phys P, FreePhys F,
+                                                       FreeOp A, const double* __restrict__ b,
+                                                       const double* __restrict__ x, double* __restrict__ bH) {
   int s, cc, sb, cb;
   if (!map_cell(m, Gc.ncell, s, cc, sb, cb)) return;
   const int S = m.S;
@@ -201,11 +219,11 @@ __global__ void __launch_bounds__(256) k_restrict_free(Map m, Grid2 G, Grid2 Gc,
     const size_t id = ((size_t)j * G.nx + i) * S + s;
     const CellState own = ld_state(A, id);
     if (exact) {
-      const RowSum r = free_row<false, true>(A, P, G.nx, G.ny, S, id, i, j, own, xv);
+      const RowSum r = free_row<false, true>(A, P, F, G.nx, G.ny, S, id, i, j, own, xv);
       s0 -= r.y0;
       s1 -= r.y1;
     } else {
-      const RowSum r = free_row<true, true>(A, P, G.nx, G.ny, S, id, i, j, own, xv);
+      const RowSum r = free_row<true, true>(A, P, F, G.nx, G.ny, S, id, i, j, own, xv);
       const double x0 = x[id], x1 = x[N + id];
       s0 += b[id] - r.y0 - r.D[0] * x0 - r.D[1] * x1;
       s1 += b[N + id] - r.y1 - r.D[2] * x0 - r.D[3] * x1;
@@ -218,9 +236,10 @@ __global__ void __launch_bounds__(256) k_restrict_free(Map m, Grid2 G, Grid2 Gc,
 
 // y = A x and per-sample dots, as k_spmv_dot (yb: the black rows' product is known).
 template <int NDOT>
-__global__ void __launch_bounds__(256) k_spmv_free(Map m, Grid2 G, Phys P, FreeOp A, const double* __restrict__ x,
-                                                   double* __restrict__ y, const double* __restrict__ d0,
-                                                   double* __restrict__ part, const double* __restrict__ yb) {
+__global__ void __launch_bounds__(256) k_spmv_free(Map m, Grid2 G, Phys P, FreePhys F, FreeOp A,
+                                                   const double* __restrict__ x, double* __restrict__ y,
+                                                   const double* __restrict__ d0, double* __restrict__ part,
+                                                   const double* __restrict__ yb) {
   __shared__ double lds[2 * 256];
   const int sblk = blockIdx.x % m.nsb, cblk = blockIdx.x / m.nsb;
   const int s = sblk * m.SX + threadIdx.x;
@@ -245,7 +264,7 @@ __global__ void __launch_bounds__(256) k_spmv_free(Map m, Grid2 G, Phys P, FreeO
       };
       const CellState own = ld_state(A, id);
       const double x0 = x[id], x1 = x[N + id];
-      const RowSum r = free_row<true, true>(A, P, G.nx, G.ny, m.S, id, i, j, own, xv);
+      const RowSum r = free_row<true, true>(A, P, F, G.nx, G.ny, m.S, id, i, j, own, xv);
       y0 = r.y0 + r.D[0] * x0 + r.D[1] * x1;
       y1 = r.y1 + r.D[2] * x0 + r.D[3] * x1;
     }

@@ -33,6 +33,7 @@
 #include "henry_kernels.hpp"
 #include "henry_coarse.hpp"
 #include "henry_free.hpp"
+#include "henry_march.hpp"
 #include "henry_tail.hpp"
 #include "henry_plu.hpp"
 #include "henry_mlmc.hpp"
@@ -700,6 +701,10 @@ static std::unique_ptr<Plan> make_plan(int nx, int ny, int S, const henry_solver
   }
   P->nlev = (int)P->lv.size();
   P->free_rows = o.mg_precision == 64 && P->N >= FREE_MIN;
+  if (P->free_rows) {
+    lds_prepare(&k_march<MARCH_PRE, 64>, march_lds<MARCH_PRE, 64>());
+    lds_prepare(&k_march<MARCH_POST, 64>, march_lds<MARCH_POST, 64>());
+  }
   if (o.coarse_solver != 0) {
     check_plu_size(o.coarse_solver, gx, gy, o.mg_precision);
   } else {
@@ -982,11 +987,33 @@ struct Solver {
     const MGLevel &L = *P.lv[k], &C = *P.lv[k + 1];
     const dim3 gg = grid_cells(m, L.ny * ((L.nx + 1) / 2)), bb = block_of(m);
     const Phys ph = phys_level(k);
+    const FreePhys F(ph);
     const FreeOp A = free_op(k);
     const double* e = mode == 2 ? C.x.as<double>() : nullptr;
-    if (mode == 1) launch_timed((k_gs_free<1>), gg, bb, 0, st, m, L.G, C.G, colour, ph, A, b, x, e);
-    else if (mode == 2) launch_timed((k_gs_free<2>), gg, bb, 0, st, m, L.G, C.G, colour, ph, A, b, x, e);
-    else launch_timed((k_gs_free<0>), gg, bb, 0, st, m, L.G, C.G, colour, ph, A, b, x, e);
+    if (mode == 1) launch_timed((k_gs_free<1>), gg, bb, 0, st, m, L.G, C.G, colour, ph, F, A, b, x, e);
+    else if (mode == 2) launch_timed((k_gs_free<2>), gg, bb, 0, st, m, L.G, C.G, colour, ph, F, A, b, x, e);
+    else launch_timed((k_gs_free<0>), gg, bb, 0, st, m, L.G, C.G, colour, ph, F, A, b, x, e);
+  }
+
+  // Several passes of level k in one launch (henry_march.hpp).
+  template <int KIND>
+  void march(int k, const double* b, const double* xin, const double* e, double* x, double* bH) {
+    const MGLevel& L = *P.lv[k];
+    MarchArgs A{}, B{};
+    const long long cost = march_split<KIND, 32>(L.nx, L.ny, P.S, A);
+    const bool wide = march_split<KIND, 64>(L.nx, L.ny, P.S, B) < cost;
+    if (wide) A = B;
+    A.P = phys_level(k);
+    A.F = FreePhys(A.P);
+    A.op = free_op(k);
+    A.b = b;
+    A.xin = xin;
+    A.e = e;
+    A.x = x;
+    A.bH = bH;
+    const dim3 g(A.blocks());
+    if (wide) launch_timed((k_march<KIND, 64>), g, dim3(MARCH_NS * 64), march_lds<KIND, 64>(), st, A);
+    else launch_timed((k_march<KIND, 32>), g, dim3(MARCH_NS * 32), march_lds<KIND, 32>(), st, A);
   }
 
   // One multigrid cycle x = M^{-1} b on level k (TR: the same cycle built from transposed
@@ -1030,6 +1057,23 @@ struct Solver {
     }
     const bool rows = free_rows<T, TR>();
     const T* J = level_J<T>(k);
+    if constexpr (sizeof(T) == 8) {
+      if (rows && zero && o.nu_pre == 1 && o.nu_post == 2 && o.fuse_prolong && march_takes(L.nx, L.ny, P.S)) {
+        // the black half-way values go through the (unused) Jacobian's memory: a strip reads its
+        // neighbours' cells, so the second launch can't write what it reads
+        MGLevel& C = *P.lv[k + 1];
+        double* half = k > 0 ? L.J.as<double>() : P.J.as<double>();
+        auto pre = [&] { march<MARCH_PRE>(k, b, nullptr, nullptr, half, C.b.as<double>()); };
+        auto post = [&] { march<MARCH_POST>(k, b, half, C.x.as<double>(), x, nullptr); };
+        if (k == 0) timed(ctx, st, HENRY_PROF_RESTRICT, (long long)L.ncell * P.S, pre);
+        else pre();
+        const int visits = k + 2 < P.nlev ? o.mg_cycle : 1;
+        for (int v = 0; v < visits; ++v) vcycle<T, TR>(k + 1, C.b.as<T>(), C.x.as<T>(), v == 0);
+        if (k == 0) timed(ctx, st, HENRY_PROF_PROLONG, (long long)L.ncell * P.S, post);
+        else post();
+        return;
+      }
+    }
     const int half = (L.nx + 1) / 2;
     // fine-grid smoother passes that read neighbours are timed as one class
     const long long half_units = (long long)L.ny * half * P.S;
@@ -1076,7 +1120,7 @@ struct Solver {
       if constexpr (sizeof(T) == 8) {
         if (rows) {
           launch_timed(k_restrict_free, grid_cells(m, C.ncell), block_of(m), 0, st, m, L.G, C.G, exact_red ? 1 : 0,
-                       phys_level(k), free_op(k), b, x, C.b.as<T>());
+                       phys_level(k), FreePhys(phys_level(k)), free_op(k), b, x, C.b.as<T>());
           return;
         }
       }
@@ -1227,7 +1271,7 @@ struct Solver {
     const Map& m = P.m;
     if constexpr (sizeof(TX) == 8 && !TR) {
       if (P.free_rows) {
-        launch_timed((k_spmv_free<NDOT>), grid_red(m), block_of(m), 0, st, m, P.G, phys, free_op(0), x, y, d0,
+        launch_timed((k_spmv_free<NDOT>), grid_red(m), block_of(m), 0, st, m, P.G, phys, FreePhys(phys), free_op(0), x, y, d0,
                            P.part.as<double>(), yb);
         return;
       }

@@ -23,12 +23,26 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 # Algorithmic bytes per unit of each bandwidth-bound kernel class (FP64 / FP32 multigrid): what
 # one launch must move per cell-sample (per swept cell for the smoother, per fine cell for the
 # restriction), counted from the arrays the kernel reads and writes.  The profiler's units are
-# the cell-samples each launch covers.  FP64: the rows formed from p, c, phi and K (smaller batches
-# read a stored row of 160 bytes instead).
+# the cell-samples each launch covers.  These are for the stored Jacobian's rows (160 bytes).
 BYTES_PER_UNIT = {
-    64: dict(gs=112, spmv=88, assemble=56, restrict=44, prolong=120),
+    64: dict(gs=208, spmv=136, assemble=216, restrict=76, prolong=216),
     32: dict(gs=104, spmv=96, assemble=136, restrict=38, prolong=108),
 }
+# FP64 batches from 2^17 cell-samples form the rows from p, c, phi and K (32 bytes a cell), and from
+# 9 * 2^16 cell-samples the whole pre-smoothing with the restriction (restrict) and the whole
+# post-smoothing with the prolongation (prolong) of the fine grid are one launch each, per cell.
+ROWS_MIN, MARCH_MIN = 1 << 17, 9 << 16
+BYTES_ROWS = dict(gs=112, spmv=88, assemble=56, restrict=44, prolong=120)
+BYTES_MARCH = dict(BYTES_ROWS, restrict=60, prolong=76)
+
+
+def bytes_per_unit(mg_precision: int, cell_samples: int) -> dict:
+    """BYTES_PER_UNIT of the kernels that a batch of this many fine cell-samples runs."""
+    if mg_precision != 64 or cell_samples < ROWS_MIN:
+        return BYTES_PER_UNIT[mg_precision]
+    return BYTES_MARCH if cell_samples >= MARCH_MIN else BYTES_ROWS
+
+
 # The vertex-centred path (henry_vc_solve), per vertex-sample: the four-colour pass reads the
 # 36-entry Jacobian row and b, writes x and reads the other three colours' x once (3 x 16 B
 # per swept vertex); the SpMV reads J and x and writes y; the assembly reads p, c, c_old and
@@ -53,10 +67,10 @@ def _hist(x: np.ndarray, width: float) -> dict:
                 min=float(x.min()), mean=float(x.mean()), max=float(x.max()))
 
 
-def kernel_classes(prof: dict, mg_precision: int = 64) -> dict:
+def kernel_classes(prof: dict, mg_precision: int = 64, cell_samples: int = 0) -> dict:
     """{class: {launches, units, ms[, avg_launch_us, gbs, frac_of_peak]}} from Henry.profile_read()."""
     out = {}
-    table = BYTES_PER_UNIT[mg_precision]
+    table = bytes_per_unit(mg_precision, cell_samples)
     for name, (n, units, ms) in prof.items():
         if n == 0:
             continue
@@ -86,7 +100,7 @@ def batch_record(label: str, grid, result, seconds: float | None = None, prof: d
     if seconds is not None and seconds > 0:
         rec.update(seconds=float(seconds), sample_timesteps_per_s=S * grid.nsteps / seconds)
     if prof is not None:
-        rec["kernel_classes"] = kernel_classes(prof, mg_precision)
+        rec["kernel_classes"] = kernel_classes(prof, mg_precision, int(grid.nx) * int(grid.ny) * S)
     rec.update(extra)
     return rec
 

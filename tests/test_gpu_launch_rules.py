@@ -210,11 +210,17 @@ def test_pivoted_solvers_at_panel_edges(hx, nx, ny, S, solver):
     (128, 64, 33, dict(coarse_nx=16, coarse_ny=8, coarse_solver=2)),
     (68, 34, 115, dict()),                                      # 34x17 cells: no single launch, band LU
     (34, 17, 454, dict()),                                      # the fine grid is the coarsest
+    (64, 32, 289, dict()),                                      # marched through: one strip, odd batch
+    (32, 16, 1153, dict()),
+    (144, 72, 57, dict()),                                      # several strips
+    (128, 64, 73, dict(mg_cycle=2)),
+    (512, 256, 5, dict()),                                      # many strips and segments, part of a block
     (64, 32, 129, dict(problem=dict(recharge_omega=2e-3, q_in_amp=0.3, right_c_dirichlet=1))),
 ])
 def test_rows_formed_from_the_state(hx, nx, ny, S, opts):
-    """A batch of at least 2^17 cell-samples forms its operators' rows from the state; the same
-    samples alone read stored Jacobians.  Both solve the same equations to the Newton tolerance
+    """A batch of at least 2^17 cell-samples forms its operators' rows from the state, and one of at
+    least 9 * 2^16 marches through the grid with several passes a launch; the same samples alone
+    read stored Jacobians.  Both solve the same equations to the Newton tolerance
     (1e-8 on the state, the workload's bound), with as strong a preconditioner: at most 5 % and
     one BiCGStab iteration a sample more."""
     import paper_2403_17018_amd as P
