@@ -361,7 +361,8 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
                                    coarse=f"{opts.coarse_nx}x{opts.coarse_ny}", coarse_solver=opts.coarse_solver))
     st = r.stats.cpu()
     table = bytes_per_unit(prec, g.nx * g.ny * S)
-    name = KERNEL_NAME_MARCH if table is BYTES_MARCH else KERNEL_NAME_ROWS if table is BYTES_ROWS else KERNEL_NAME
+    name = (KERNEL_NAME_MARCH if table is BYTES_MARCH[prec] else
+            KERNEL_NAME_ROWS if table is BYTES_ROWS else KERNEL_NAME)
     cls = max(table, key=lambda k: prof[k][2])            # dominant kernel class by summed time
     n, units, ms = prof[cls]
     per_launch_bytes = units / n * table[cls]

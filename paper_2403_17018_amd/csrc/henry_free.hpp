@@ -235,9 +235,9 @@ __global__ void __launch_bounds__(256) k_restrict_free(Map m, Grid2 G, Grid2 Gc,
 }
 
 // y = A x and per-sample dots, as k_spmv_dot (yb: the black rows' product is known).
-template <int NDOT>
+template <int NDOT, typename TX>
 __global__ void __launch_bounds__(256) k_spmv_free(Map m, Grid2 G, Phys P, FreePhys F, FreeOp A,
-                                                   const double* __restrict__ x, double* __restrict__ y,
+                                                   const TX* __restrict__ x, double* __restrict__ y,
                                                    const double* __restrict__ d0, double* __restrict__ part,
                                                    const double* __restrict__ yb) {
   __shared__ double lds[2 * 256];
@@ -259,11 +259,11 @@ __global__ void __launch_bounds__(256) k_spmv_free(Map m, Grid2 G, Phys P, FreeP
       y1 = yb[N + id];
     } else {
       auto xv = [&](int, size_t q, double& x0, double& x1) {
-        x0 = x[q];
-        x1 = x[N + q];
+        x0 = (double)x[q];
+        x1 = (double)x[N + q];
       };
       const CellState own = ld_state(A, id);
-      const double x0 = x[id], x1 = x[N + id];
+      const double x0 = (double)x[id], x1 = (double)x[N + id];
       const RowSum r = free_row<true, true>(A, P, F, G.nx, G.ny, m.S, id, i, j, own, xv);
       y0 = r.y0 + r.D[0] * x0 + r.D[1] * x1;
       y1 = r.y1 + r.D[2] * x0 + r.D[3] * x1;

@@ -352,12 +352,14 @@ struct Plan {
   // captured BiCGStab iterations: [transposed][first iteration]
   hipGraphExec_t gexec[2][5] = {{nullptr, nullptr, nullptr, nullptr, nullptr},
                                 {nullptr, nullptr, nullptr, nullptr, nullptr}};
-  int gkey[2][5] = {{0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}};   // per operator: nu_pre, nu_post, precision, cycle, valid
+  // per operator: nu_pre, nu_post, precision, cycle, fuse_prolong, FP32 Jacobian in the products, valid
+  int gkey[2][7] = {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}};
   double grtol[2] = {0.0, 0.0};
   // captured first Newton iteration of a time step (step_graphs) and what it was captured for
   hipGraphExec_t step_exec = nullptr;
   Phys step_phys{};
   henry_solver_opts step_opts{};
+  bool step_spmv32 = false;
   int step_order = -1;
   void drop_step_graph() {
     if (step_exec) (void)hipGraphExecDestroy(step_exec);
@@ -369,7 +371,7 @@ struct Plan {
         (void)hipGraphExecDestroy(g);
         g = nullptr;
       }
-    gkey[tr][4] = 0;
+    gkey[tr][6] = 0;
   }
   void drop_graphs() {
     drop_graphs(0);
@@ -672,6 +674,13 @@ static void plan_set_wide(Plan& Q, int sample_block) {
   Q.mw4 = make_map_wide(Q.S, Q.nx * Q.ny, Q.sp4, sample_block);
 }
 
+// Workgroups of 64 columns may need more LDS than a launch gets by default.
+template <typename T, typename TB>
+static void march_prepare() {
+  lds_prepare(&k_march<MARCH_PRE, 64, T, TB>, march_lds<MARCH_PRE, 64, T>());
+  lds_prepare(&k_march<MARCH_POST, 64, T, TB>, march_lds<MARCH_POST, 64, T>());
+}
+
 static std::unique_ptr<Plan> make_plan(int nx, int ny, int S, const henry_solver_opts& o) {
   const int cnx = std::min(o.coarse_nx, nx), cny = std::min(o.coarse_ny, ny);
   auto P = std::make_unique<Plan>();
@@ -701,9 +710,13 @@ static std::unique_ptr<Plan> make_plan(int nx, int ny, int S, const henry_solver
   }
   P->nlev = (int)P->lv.size();
   P->free_rows = o.mg_precision == 64 && P->N >= FREE_MIN;
-  if (P->free_rows) {
-    lds_prepare(&k_march<MARCH_PRE, 64>, march_lds<MARCH_PRE, 64>());
-    lds_prepare(&k_march<MARCH_POST, 64>, march_lds<MARCH_POST, 64>());
+  if (P->N >= MARCH_MIN) {
+    if (o.mg_precision == 32) {
+      march_prepare<float, float>();
+      march_prepare<float, double>();
+    } else {
+      march_prepare<double, double>();
+    }
   }
   if (o.coarse_solver != 0) {
     check_plu_size(o.coarse_solver, gx, gy, o.mg_precision);
@@ -792,7 +805,7 @@ static void plan_set_samples(Plan& Q, int Sa, int red_blocks, int sample_block) 
 // ---------------------------------------------------------------------------
 // solver
 // ---------------------------------------------------------------------------
-constexpr size_t COMPACT_MIN = 5 << 17;   // see Solver::may_compact
+constexpr size_t COMPACT_MIN = 3 << 19;   // see Solver::may_compact
 
 struct Solver {
   henry_ctx* ctx;
@@ -843,11 +856,17 @@ struct Solver {
     }
   }
 
-  // The FP64 forward solves form their operator's rows from the state (henry_free.hpp) from
-  // FREE_MIN cell-samples on; the FP32 cycle, whose stored row is no larger than the state it would
-  // be formed from, and the transposed solves read stored Jacobians.
+  // The forward solves form their operator's rows from the state (henry_free.hpp) from FREE_MIN
+  // cell-samples on in FP64.  In FP32, where a stored row is no larger than the state it would be
+  // formed from, they do so on the grids that are marched through (henry_march.hpp), and in the
+  // products if the fine grid is one of them.  The transposed solves read stored Jacobians.
   template <typename T, bool TR>
   bool free_rows() const { return sizeof(T) == 8 && !TR && P.free_rows; }
+  bool marched(int k) const {
+    return k + 1 < P.nlev && o.nu_pre == 1 && o.nu_post == 2 && o.fuse_prolong &&
+           (P.prec == 64 ? P.free_rows : o.mg_cycle == 1) && march_takes(P.lv[k]->nx, P.lv[k]->ny, P.S, P.prec);
+  }
+  bool rows32() const { return P.prec == 32 && marched(0); }
   FreeOp free_op(int k) const {
     if (k == 0) return {P.p.as<double>(), P.c.as<double>(), P.phi.as<double>(), P.K.as<double>()};
     const MGLevel& L = *P.lv[k];
@@ -868,7 +887,7 @@ struct Solver {
   template <typename T>
   void assemble_all(bool tr = false) {
     const Map& m = P.m;
-    const bool rows = !tr && free_rows<T, false>();
+    const bool rows = !tr && (free_rows<T, false>() || rows32());
     timed(ctx, st, HENRY_PROF_ASSEMBLE, (long long)P.N, [&] {
       if (rows && P.nlev > 1)   // (a grid that is its own coarsest is factored from its Jacobian)
         launch_timed((k_assemble<true, double, false, false>), asm_grid(m, P.G), asm_block(m), asm_lds(m.SX), st, m, P.G,
@@ -895,7 +914,7 @@ struct Solver {
       const double* fc_ = k == 1 ? P.c.as<double>() : F.c.as<double>();
       hipLaunchKernelGGL(k_restrict_state, grid_cells(m, C.ncell), block_of(m), 0, st, m, F.G, C.G, fp_, fc_,
                          C.p.as<double>(), C.c.as<double>());
-      if (rows && k < P.nlev - 1) continue;
+      if (rows && (P.prec == 64 ? k < P.nlev - 1 : marched(k))) continue;
       hipLaunchKernelGGL((k_assemble<false, T, false>), asm_grid(m, C.G), asm_block(m), asm_lds(m.SX), st, m, C.G,
                          phys_level(k), C.p.as<double>(), C.c.as<double>(), (const double*)nullptr,
                          C.phi.as<double>(), C.K.as<double>(), P.uin.as<double>(), (double*)nullptr, C.J.as<T>(),
@@ -996,12 +1015,12 @@ struct Solver {
   }
 
   // Several passes of level k in one launch (henry_march.hpp).
-  template <int KIND>
-  void march(int k, const double* b, const double* xin, const double* e, double* x, double* bH) {
+  template <int KIND, typename T, typename TB>
+  void march(int k, const TB* b, const T* xin, const T* e, T* x, T* bH) {
     const MGLevel& L = *P.lv[k];
-    MarchArgs A{}, B{};
-    const long long cost = march_split<KIND, 32>(L.nx, L.ny, P.S, A);
-    const bool wide = march_split<KIND, 64>(L.nx, L.ny, P.S, B) < cost;
+    MarchArgs<T, TB> A{}, B{};
+    const long long c32 = march_split<KIND, 32>(L.nx, L.ny, P.S, A), c64 = march_split<KIND, 64>(L.nx, L.ny, P.S, B);
+    const bool wide = KIND == MARCH_PRE ? c64 <= c32 : c64 < c32;
     if (wide) A = B;
     A.P = phys_level(k);
     A.F = FreePhys(A.P);
@@ -1012,8 +1031,24 @@ struct Solver {
     A.x = x;
     A.bH = bH;
     const dim3 g(A.blocks());
-    if (wide) launch_timed((k_march<KIND, 64>), g, dim3(MARCH_NS * 64), march_lds<KIND, 64>(), st, A);
-    else launch_timed((k_march<KIND, 32>), g, dim3(MARCH_NS * 32), march_lds<KIND, 32>(), st, A);
+    if (wide) launch_timed((k_march<KIND, 64, T, TB>), g, dim3(MARCH_NS * 64), march_lds<KIND, 64, T>(), st, A);
+    else launch_timed((k_march<KIND, 32, T, TB>), g, dim3(MARCH_NS * 32), march_lds<KIND, 32, T>(), st, A);
+  }
+  // vcycle from x = 0 on a marched level.
+  template <typename T, typename TB>
+  void march_cycle(int k, const TB* b, T* x) {
+    MGLevel &L = *P.lv[k], &C = *P.lv[k + 1];
+    // the black half-way values go through the (unused) Jacobian's memory: a strip reads its
+    // neighbours' cells, so the second launch can't write what it reads
+    T* half = const_cast<T*>(level_J<T>(k));
+    auto pre = [&] { march<MARCH_PRE, T, TB>(k, b, nullptr, nullptr, half, C.b.as<T>()); };
+    auto post = [&] { march<MARCH_POST, T, TB>(k, b, half, C.x.as<T>(), x, nullptr); };
+    if (k == 0) timed(ctx, st, HENRY_PROF_RESTRICT, (long long)L.ncell * P.S, pre);
+    else pre();
+    const int visits = k + 2 < P.nlev ? o.mg_cycle : 1;
+    for (int v = 0; v < visits; ++v) vcycle<T, false>(k + 1, C.b.as<T>(), C.x.as<T>(), v == 0);
+    if (k == 0) timed(ctx, st, HENRY_PROF_PROLONG, (long long)L.ncell * P.S, post);
+    else post();
   }
 
   // One multigrid cycle x = M^{-1} b on level k (TR: the same cycle built from transposed
@@ -1057,22 +1092,8 @@ struct Solver {
     }
     const bool rows = free_rows<T, TR>();
     const T* J = level_J<T>(k);
-    if constexpr (sizeof(T) == 8) {
-      if (rows && zero && o.nu_pre == 1 && o.nu_post == 2 && o.fuse_prolong && march_takes(L.nx, L.ny, P.S)) {
-        // the black half-way values go through the (unused) Jacobian's memory: a strip reads its
-        // neighbours' cells, so the second launch can't write what it reads
-        MGLevel& C = *P.lv[k + 1];
-        double* half = k > 0 ? L.J.as<double>() : P.J.as<double>();
-        auto pre = [&] { march<MARCH_PRE>(k, b, nullptr, nullptr, half, C.b.as<double>()); };
-        auto post = [&] { march<MARCH_POST>(k, b, half, C.x.as<double>(), x, nullptr); };
-        if (k == 0) timed(ctx, st, HENRY_PROF_RESTRICT, (long long)L.ncell * P.S, pre);
-        else pre();
-        const int visits = k + 2 < P.nlev ? o.mg_cycle : 1;
-        for (int v = 0; v < visits; ++v) vcycle<T, TR>(k + 1, C.b.as<T>(), C.x.as<T>(), v == 0);
-        if (k == 0) timed(ctx, st, HENRY_PROF_PROLONG, (long long)L.ncell * P.S, post);
-        else post();
-        return;
-      }
+    if constexpr (!TR) {
+      if (zero && marched(k)) return march_cycle<T, T>(k, b, x);
     }
     const int half = (L.nx + 1) / 2;
     // fine-grid smoother passes that read neighbours are timed as one class
@@ -1170,6 +1191,9 @@ struct Solver {
   // which the SpMV and the x update read (widening them there is exact, so no FP64 copy).
   template <typename T, bool TR = false>
   void precond(const double* in, double* out) {
+    if constexpr (sizeof(T) == 4 && !TR) {
+      if (rows32()) return march_cycle<float, double>(0, in, reinterpret_cast<float*>(out));
+    }
     if (P.prec == 32) {
       MGLevel& L = *P.lv[0];
       const size_t n = 2 * P.N;
@@ -1269,10 +1293,10 @@ struct Solver {
   template <int NDOT, bool TR, typename TX>
   void spmv(const TX* x, double* y, const double* d0, const double* yb) {
     const Map& m = P.m;
-    if constexpr (sizeof(TX) == 8 && !TR) {
-      if (P.free_rows) {
-        launch_timed((k_spmv_free<NDOT>), grid_red(m), block_of(m), 0, st, m, P.G, phys, FreePhys(phys), free_op(0), x, y, d0,
-                           P.part.as<double>(), yb);
+    if constexpr (!TR) {
+      if (P.free_rows || rows32()) {
+        launch_timed((k_spmv_free<NDOT, TX>), grid_red(m), block_of(m), 0, st, m, P.G, phys, FreePhys(phys), free_op(0),
+                           x, y, d0, P.part.as<double>(), yb);
         return;
       }
     }
@@ -1320,7 +1344,7 @@ struct Solver {
     if (newton && P.h_ctrl[1] <= stop_at) return P.h_ctrl[1];
     const bool graphs = o.use_graphs && allow_graphs && !ctx->prof.on;
     if (graphs) {
-      const int key[5] = {o.nu_pre, o.nu_post, P.prec, o.mg_cycle, 1};
+      const int key[7] = {o.nu_pre, o.nu_post, P.prec, o.mg_cycle, o.fuse_prolong, spmv32(), 1};
       if (std::memcmp(key, P.gkey[TR], sizeof key) != 0 || P.grtol[TR] != rtol2) {
         P.drop_graphs(TR);
         std::memcpy(P.gkey[TR], key, sizeof key);
@@ -1464,7 +1488,7 @@ struct Solver {
   void launch_step_graph(int n) {
     const int order = guess_order(n);
     if (!P.step_exec || !same_phys(P.step_phys, phys) || std::memcmp(&P.step_opts, &o, sizeof o) != 0 ||
-        P.step_order != order) {
+        P.step_spmv32 != spmv32() ||        P.step_order != order) {
       P.drop_step_graph();
       P.step_exec = capture([&] {
         step_prologue(n, true);
@@ -1472,6 +1496,7 @@ struct Solver {
       });
       P.step_phys = phys;
       P.step_opts = o;
+      P.step_spmv32 = spmv32();
       P.step_order = order;
     }
     HIPCHK(hipGraphLaunch(P.step_exec, st));
@@ -1552,11 +1577,12 @@ struct Solver {
 
   // Compaction pays where the fine launches are bound by their cells: below COMPACT_MIN
   // cell-samples they are bound by launch and memory latency, which fewer samples do not
-  // shorten, and the gathers and scatters (some 20 launches) and the Jacobian assembled anew for
-  // the smaller batch are a loss.  With and without, ms a solve: 65 536 cell-samples 43.0 and
-  // 38.9 (level 0), 42.2 and 38.9 (level 1); 262 144: 56.0 and 51.2, 59.0 and 55.4, 71.7 and 67.3
-  // (level 2); 524 288: 76.4 and 73.8, 89.7 and 87.6 (level 3), 61.0 and 58.6 (FP32 cycle);
-  // 681 984: 108.9 and 112.1; 819 200: 105.1 and 107.1; 2 097 152: 158.9 and 172.3.
+  // shorten, and the gathers and scatters (some 20 launches) and the operator taken anew for the
+  // smaller batch are a loss.  With and without, ms a solve: 65 536 cell-samples 43.0 and 38.9
+  // (level 0), 262 144: 56.0 and 51.2, 71.7 and 67.3 (level 2); 614 400: 76.9 and 76.2; 1 048 576:
+  // 89.3 and 89.4 (level 3); 1 310 720: 80.1 and 80.0 (level 1), 82.4 and 82.0 (level 2); 2 048 000:
+  // 146.9 and 154.1; 2 097 152: 118.2 and 117.0 (level 3); 2 727 936: 171.3 and 179.9; 6 553 600:
+  // 305.5 and 329.4.
   bool allow_compact = true;
   bool may_compact() const { return allow_compact && P.N >= COMPACT_MIN; }
 

@@ -30,17 +30,19 @@ BYTES_PER_UNIT = {
 }
 # FP64 batches from 2^17 cell-samples form the rows from p, c, phi and K (32 bytes a cell), and from
 # 9 * 2^16 cell-samples the whole pre-smoothing with the restriction (restrict) and the whole
-# post-smoothing with the prolongation (prolong) of the fine grid are one launch each, per cell.
-ROWS_MIN, MARCH_MIN = 1 << 17, 9 << 16
+# post-smoothing with the prolongation (prolong) of the fine grid are one launch each, per cell; FP32
+# ones do so from 5 * 2^18 cell-samples, and form the products' rows.
+ROWS_MIN, MARCH_MIN, MARCH_MIN32 = 1 << 17, 9 << 16, 5 << 18
 BYTES_ROWS = dict(gs=112, spmv=88, assemble=56, restrict=44, prolong=120)
-BYTES_MARCH = dict(BYTES_ROWS, restrict=60, prolong=76)
+BYTES_MARCH = {64: dict(BYTES_ROWS, restrict=60, prolong=76),
+               32: dict(gs=104, spmv=80, assemble=56, restrict=54, prolong=62)}
 
 
 def bytes_per_unit(mg_precision: int, cell_samples: int) -> dict:
     """BYTES_PER_UNIT of the kernels that a batch of this many fine cell-samples runs."""
-    if mg_precision != 64 or cell_samples < ROWS_MIN:
-        return BYTES_PER_UNIT[mg_precision]
-    return BYTES_MARCH if cell_samples >= MARCH_MIN else BYTES_ROWS
+    if cell_samples >= (MARCH_MIN if mg_precision == 64 else MARCH_MIN32):
+        return BYTES_MARCH[mg_precision]
+    return BYTES_ROWS if mg_precision == 64 and cell_samples >= ROWS_MIN else BYTES_PER_UNIT[mg_precision]
 
 
 # The vertex-centred path (henry_vc_solve), per vertex-sample: the four-colour pass reads the

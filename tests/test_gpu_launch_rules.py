@@ -215,12 +215,15 @@ def test_pivoted_solvers_at_panel_edges(hx, nx, ny, S, solver):
     (144, 72, 57, dict()),                                      # several strips
     (128, 64, 73, dict(mg_cycle=2)),
     (512, 256, 5, dict()),                                      # many strips and segments, part of a block
+    (64, 32, 641, dict(mg_precision=32)),
+    (144, 72, 127, dict(mg_precision=32)),
+    (512, 256, 11, dict(mg_precision=32)),
     (64, 32, 129, dict(problem=dict(recharge_omega=2e-3, q_in_amp=0.3, right_c_dirichlet=1))),
 ])
 def test_rows_formed_from_the_state(hx, nx, ny, S, opts):
     """A batch of at least 2^17 cell-samples forms its operators' rows from the state, and one of at
-    least 9 * 2^16 marches through the grid with several passes a launch; the same samples alone
-    read stored Jacobians.  Both solve the same equations to the Newton tolerance
+    least 9 * 2^16 (FP32: 5 * 2^18) marches through the grid with several passes a launch; the same
+    samples alone read stored Jacobians.  Both solve the same equations to the Newton tolerance
     (1e-8 on the state, the workload's bound), with as strong a preconditioner: at most 5 % and
     one BiCGStab iteration a sample more."""
     import paper_2403_17018_amd as P
@@ -238,3 +241,26 @@ def test_rows_formed_from_the_state(hx, nx, ny, S, opts):
         assert ((u - v).abs().amax() / v.abs().amax()).item() <= 1e-8
     ia, ib = a.stats[pick, 1].cpu().numpy(), b.stats[:, 1].cpu().numpy()
     assert (ia <= 1.05 * ib + 1).all(), (ia, ib)
+
+
+def test_fp32_solve_and_adjoint_on_one_plan(hx):
+    """A solve (whose products read the FP32 Jacobian) and an adjoint (whose products read the FP64
+    one) of the same shape share a plan: each must come out as on a context of its own, in either
+    order, to the linear solves' tolerance (1e-8 on the state, the workload's bound)."""
+    import paper_2403_17018_amd as P
+    th = _cu(draw_theta(47, 40, level=0))
+    g, pr = P.grid(32, 16, 12), P.problem(T=9000.0)
+    o = P.solver_opts(mg_precision=32)
+
+    def close(u, v):
+        return ((u - v).abs().amax() / v.abs().amax()).item() <= 1e-8
+
+    h = P.Henry(0)
+    s0 = h.solve(th, g, pr, o, want_c=True).c_T.clone()
+    h.close()
+    h = P.Henry(0)
+    q0, g0 = [t.clone() for t in h.adjoint(th, g, pr, o)[:2]]
+    s1 = h.solve(th, g, pr, o, want_c=True).c_T.clone()
+    q1, g1 = [t.clone() for t in h.adjoint(th, g, pr, o)[:2]]
+    h.close()
+    assert close(s1, s0) and close(q1, q0) and close(g1, g0)
