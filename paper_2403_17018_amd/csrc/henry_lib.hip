@@ -34,6 +34,7 @@
 #include "henry_coarse.hpp"
 #include "henry_free.hpp"
 #include "henry_march.hpp"
+#include "henry_small.hpp"
 #include "henry_tail.hpp"
 #include "henry_plu.hpp"
 #include "henry_mlmc.hpp"
@@ -1502,6 +1503,59 @@ struct Solver {
     HIPCHK(hipGraphLaunch(P.step_exec, st));
   }
 
+  // Steps solved in one launch (henry_small.hpp): what the kernel's LDS takes, as a step graph's
+  // options allow.
+  bool small() const {
+    return P.prec == 64 && P.inverse && o.mg_cycle == 1 && o.nu_post >= 1 && o.step_graphs && allow_graphs &&
+           !ctx->prof.on && P.nlev - 1 <= SMALL_LEVELS && P.G.ncell <= SMALL_CELLS &&
+           P.lv[1]->ncell <= SMALL_THREADS;
+  }
+  void small_step() {
+    SmallArgs A{};
+    A.S = P.S;
+    A.nl = P.nlev - 1;
+    for (int l = 0; l <= A.nl; ++l) {
+      const MGLevel& L = *P.lv[l];
+      const FreeOp op = free_op(l);
+      const Phys ph = phys_level(l);
+      A.nx[l] = L.nx;
+      A.ny[l] = L.ny;
+      A.hy[l] = ph.hy;
+      A.F[l] = FreePhys(ph);
+      A.phi[l] = op.phi;
+      A.K[l] = op.K;
+    }
+    A.p = P.p.as<double>();
+    A.c = P.c.as<double>();
+    A.c_old = P.c_old.as<double>();
+    A.uin = P.uin.as<double>();
+    A.inv = P.LU.as<double>();
+    A.status = P.status.as<int>();
+    A.stats = P.stats.as<double>();
+    A.nu_pre = o.nu_pre;
+    A.nu_post = o.nu_post;
+    A.newton_maxit = o.newton_maxit;
+    A.krylov_maxit = o.krylov_maxit;
+    A.rtol2 = o.krylov_rtol * o.krylov_rtol;
+    A.breakdown = o.krylov_breakdown;
+    A.newton_tol = o.newton_tol;
+    A.pred_tol = o.newton_tol * o.newton_predict;
+    A.dc_max = o.newton_dc_max;
+    A.jac_reuse = o.newton_jac_reuse;
+    A.p_ref = pr.rho0 * pr.g * pr.Ly;
+    const uint32_t lds = (uint32_t)small_layout(A);
+    const dim3 g(8 * tail_chunk(P.S)), bl(SMALL_THREADS);
+    const bool one = P.G.ncell <= 2 * SMALL_THREADS, c32 = P.lv[A.nl]->ncell <= 32;
+    auto go = [&](auto kernel) {
+      lds_prepare(kernel, 160 * 1024);
+      hipLaunchKernelGGL(kernel, g, bl, lds, st, A, phys);
+    };
+    if (one && c32) go(&k_small_step<1, 2, 16>);
+    else if (one) go(&k_small_step<1, 4, 32>);
+    else if (c32) go(&k_small_step<2, 2, 16>);
+    else go(&k_small_step<2, 4, 32>);
+  }
+
   // one implicit-Euler step n -> n+1: damped Newton with multigrid-preconditioned BiCGStab
   template <typename T>
   void time_step(int n, int nsteps) {
@@ -1520,7 +1574,10 @@ struct Solver {
     // order (the first steps have less history).
     const int order = guess_order(n);
     const bool settled = order >= 0 && order == guess_order(n + 1);
-    if (o.step_graphs && allow_graphs && !ctx->prof.on && pr.recharge_omega == 0.0 && settled &&
+    if (small()) {
+      step_prologue(n, false);
+      small_step();
+    } else if (o.step_graphs && allow_graphs && !ctx->prof.on && pr.recharge_omega == 0.0 && settled &&
         o.newton_maxit > 1) {
       launch_step_graph<T>(n);
       const int remaining = read_ctrl(1);

@@ -326,16 +326,113 @@ __host__ inline size_t setup_lds(const TailSetup<T>& A) {
   return (a + b + 20 * nc + 2 * 4 * TAIL_NMAX) * sizeof(double);
 }
 
+// Inverse of an operator of ncc cells (rows of nxc) given by its blocks Jc [20][ncc] in LDS, by a
+// workgroup of SETUP_THREADS: Gauss-Jordan by 2x2 blocks without interchanges, as the banded LU
+// (the diagonal blocks of this operator are nonsingular and its pressure part is an M-matrix).
+// Each of 16 x TC threads holds RC row cells (tr, tr + 16, ..) of two column cells (tc, tc + TC) in
+// registers; a step's pivot rows and columns go through LDS (`pivots`, 8 TAIL_NMAX doubles), double
+// buffered, so the serial chain is ncc steps of one barrier, a 2x2 inverse and the multiply-adds.
+// RC = 2, TC = 16 take 32 cells, RC = 4, TC = 32 take 64.  With the pivots' register slots chosen
+// at run time k_tail_setup took 38 us instead of 27.  out(row, column, value).
+template <int RC, int TC, typename Out>
+__device__ __forceinline__ void tail_inverse(const double* Jc, double* pivots, int ncc, int nxc, Out&& out) {
+  struct alignas(16) Blk { double v[4]; };
+  Blk* prow = reinterpret_cast<Blk*>(pivots);          // [2][TAIL_NMAX / 2]: blocks of the pivot row
+  Blk* pcol = prow + TAIL_NMAX;                        // [2][TAIL_NMAX / 2]: blocks of the pivot column
+  const int t = threadIdx.x;
+  const bool worker = t < 16 * TC;
+  const int tr = t / TC, tc = t % TC;
+  double W[RC][2][4];
+#pragma unroll
+  for (int a = 0; a < RC; ++a)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int q = tr + 16 * a, c = tc + TC * h, d = c - q, qi = q % nxc;
+      int blk = -1;
+      if (d == 0) blk = 0;
+      else if (d == -1 && qi > 0) blk = 1;
+      else if (d == 1 && qi < nxc - 1) blk = 2;
+      else if (d == -nxc) blk = 3;
+      else if (d == nxc) blk = 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) W[a][h][e] = worker && blk >= 0 && q < ncc && c < ncc ? Jc[(blk * 4 + e) * ncc + q] : 0.0;
+    }
+#pragma unroll
+  for (int kh = 0; kh < RC; ++kh) {   // pivots 16 kh .. 16 kh + 15: row cell slot kh, column slot kc
+    constexpr int PER = TC / 16;
+    const int kc = kh / PER;
+    for (int kk = 0; kk < 16 && 16 * kh + kk < ncc; ++kk) {
+      const int k = 16 * kh + kk;
+      Blk* pr = prow + (kk & 1) * (TAIL_NMAX / 2);
+      Blk* pc = pcol + (kk & 1) * (TAIL_NMAX / 2);
+      const bool prw = worker && tr == kk, pcl = worker && tc == 16 * (kh % PER) + kk;
+      // publish the pivot row and the pivot column; the column becomes the identity's (in the
+      // pivot row) and zero, from which the update makes the inverse's
+      if (prw)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) pr[tc + TC * h].v[e] = W[kh][h][e];
+      if (pcl)
+#pragma unroll
+        for (int a = 0; a < RC; ++a)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            pc[tr + 16 * a].v[e] = W[a][kc][e];
+            W[a][kc][e] = 0.0;
+          }
+      lds_barrier();
+      if (!worker) continue;
+      const Blk d = pr[k];
+      Blk p[2] = {pr[tc], pr[tc + TC]};
+      if (pcl) {
+        p[kc].v[0] = p[kc].v[3] = 1.0;
+        p[kc].v[1] = p[kc].v[2] = 0.0;
+      }
+      const double rdet = 1.0 / (d.v[0] * d.v[3] - d.v[1] * d.v[2]);
+      const double i00 = d.v[3] * rdet, i01 = -d.v[1] * rdet, i10 = -d.v[2] * rdet, i11 = d.v[0] * rdet;
+      double g[2][4];   // D^{-1} times the pivot row's blocks
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        g[h][0] = i00 * p[h].v[0] + i01 * p[h].v[2];
+        g[h][1] = i00 * p[h].v[1] + i01 * p[h].v[3];
+        g[h][2] = i10 * p[h].v[0] + i11 * p[h].v[2];
+        g[h][3] = i10 * p[h].v[1] + i11 * p[h].v[3];
+      }
+#pragma unroll
+      for (int a = 0; a < RC; ++a) {
+        const Blk l = pc[tr + 16 * a];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            W[a][h][e] -= l.v[2 * (e >> 1)] * g[h][e & 1];
+            W[a][h][e] -= l.v[2 * (e >> 1) + 1] * g[h][2 + (e & 1)];
+          }
+      }
+      if (prw)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) W[kh][h][e] = g[h][e];
+    }
+  }
+  if (!worker) return;
+#pragma unroll
+  for (int a = 0; a < RC; ++a)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int q = tr + 16 * a, c = tc + TC * h;
+      if (q >= ncc || c >= ncc) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out(2 * q + (e >> 1), 2 * c + (e & 1), W[a][h][e]);
+    }
+}
+
 // Restricted states (means of the four children), rediscretised Jacobians of the grids of A (the
 // assembly's formulas), and the inverse of the coarsest operator (of its transpose when
-// `transposed`): Gauss-Jordan by 2x2 blocks without interchanges, as the banded LU (the diagonal
-// blocks of this operator are nonsingular and its pressure part is an M-matrix).  Each of
-// 16 x TC threads holds RC row cells (tr, tr + 16, ..) of two column cells (tc, tc + TC) in
-// registers; a step's pivot rows and columns go through LDS, double buffered, so the serial
-// chain is nc steps of one barrier, a 2x2 inverse and the multiply-adds.  RC = 2, TC = 16 take
-// 32 cells, RC = 4, TC = 32 take 64.  That chain bounds the launch: 27 us for 16 samples from a
-// 16x8 grid down, where the banded factorisation alone took 56 us and the assemblies four
-// launches more; with the pivots' register slots chosen at run time it was 38 us.
+// `transposed`).  The inversion's serial chain bounds the launch: 27 us for 16 samples from a 16x8
+// grid down, where the banded factorisation alone took 56 us and the assemblies four launches more.
 template <typename T, int RC, int TC>
 __global__ void __launch_bounds__(SETUP_THREADS) k_tail_setup(TailSetup<T> A, Phys P) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -425,102 +522,10 @@ __global__ void __launch_bounds__(SETUP_THREADS) k_tail_setup(TailSetup<T> A, Ph
     Jg += 20 * n;
   }
   lds_barrier();
-  // the inversion
-  struct alignas(16) Blk { double v[4]; };
-  Blk* prow = reinterpret_cast<Blk*>(Jc + 20 * ncc);   // [2][TAIL_NMAX / 2]: blocks of the pivot row
-  Blk* pcol = prow + TAIL_NMAX;                        // [2][TAIL_NMAX / 2]: blocks of the pivot column
-  const int nxc = A.nx[A.nl];
-  const bool worker = t < 16 * TC;
-  const int tr = t / TC, tc = t % TC;
-  double W[RC][2][4];
-#pragma unroll
-  for (int a = 0; a < RC; ++a)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int q = tr + 16 * a, c = tc + TC * h, d = c - q, qi = q % nxc;
-      int blk = -1;
-      if (d == 0) blk = 0;
-      else if (d == -1 && qi > 0) blk = 1;
-      else if (d == 1 && qi < nxc - 1) blk = 2;
-      else if (d == -nxc) blk = 3;
-      else if (d == nxc) blk = 4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) W[a][h][e] = worker && blk >= 0 && q < ncc && c < ncc ? Jc[(blk * 4 + e) * ncc + q] : 0.0;
-    }
-#pragma unroll
-  for (int kh = 0; kh < RC; ++kh) {   // pivots 16 kh .. 16 kh + 15: row cell slot kh, column slot kc
-    constexpr int PER = TC / 16;
-    const int kc = kh / PER;
-    for (int kk = 0; kk < 16 && 16 * kh + kk < ncc; ++kk) {
-      const int k = 16 * kh + kk;
-      Blk* pr = prow + (kk & 1) * (TAIL_NMAX / 2);
-      Blk* pc = pcol + (kk & 1) * (TAIL_NMAX / 2);
-      const bool prw = worker && tr == kk, pcl = worker && tc == 16 * (kh % PER) + kk;
-      // publish the pivot row and the pivot column; the column becomes the identity's (in the
-      // pivot row) and zero, from which the update makes the inverse's
-      if (prw)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) pr[tc + TC * h].v[e] = W[kh][h][e];
-      if (pcl)
-#pragma unroll
-        for (int a = 0; a < RC; ++a)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            pc[tr + 16 * a].v[e] = W[a][kc][e];
-            W[a][kc][e] = 0.0;
-          }
-      lds_barrier();
-      if (!worker) continue;
-      const Blk d = pr[k];
-      Blk p[2] = {pr[tc], pr[tc + TC]};
-      if (pcl) {
-        p[kc].v[0] = p[kc].v[3] = 1.0;
-        p[kc].v[1] = p[kc].v[2] = 0.0;
-      }
-      const double rdet = 1.0 / (d.v[0] * d.v[3] - d.v[1] * d.v[2]);
-      const double i00 = d.v[3] * rdet, i01 = -d.v[1] * rdet, i10 = -d.v[2] * rdet, i11 = d.v[0] * rdet;
-      double g[2][4];   // D^{-1} times the pivot row's blocks
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        g[h][0] = i00 * p[h].v[0] + i01 * p[h].v[2];
-        g[h][1] = i00 * p[h].v[1] + i01 * p[h].v[3];
-        g[h][2] = i10 * p[h].v[0] + i11 * p[h].v[2];
-        g[h][3] = i10 * p[h].v[1] + i11 * p[h].v[3];
-      }
-#pragma unroll
-      for (int a = 0; a < RC; ++a) {
-        const Blk l = pc[tr + 16 * a];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            W[a][h][e] -= l.v[2 * (e >> 1)] * g[h][e & 1];
-            W[a][h][e] -= l.v[2 * (e >> 1) + 1] * g[h][2 + (e & 1)];
-          }
-      }
-      if (prw)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) W[kh][h][e] = g[h][e];
-    }
-  }
-  if (!worker) return;
   double* out = A.inv + (size_t)s * nu * nu;
-#pragma unroll
-  for (int a = 0; a < RC; ++a)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int q = tr + 16 * a, c = tc + TC * h;
-      if (q >= ncc || c >= ncc) continue;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 2 * q + (e >> 1), k = 2 * c + (e & 1);
-        out[A.transposed ? (size_t)k * nu + r : (size_t)r * nu + k] = W[a][h][e];
-      }
-    }
+  tail_inverse<RC, TC>(Jc, Jc + 20 * ncc, ncc, A.nx[A.nl], [&](int r, int k, double v) {
+    out[A.transposed ? (size_t)k * nu + r : (size_t)r * nu + k] = v;
+  });
 }
 
 }  // namespace henry
