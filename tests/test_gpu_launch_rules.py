@@ -279,7 +279,7 @@ def test_fp32_solve_and_adjoint_on_one_plan(hx):
     (64, 32, 300, dict()),                                      # more samples than workgroups at once
     (64, 32, 5, dict(coarse_nx=4, coarse_ny=2)),                # four smoothed grids
     (32, 16, 12, dict(newton_predict=0.0, newton_jac_reuse=0.0)),
-    (32, 16, 12, dict(newton_dc_max=0.02)),                     # damped updates
+    (32, 16, 12, dict(newton_dc_max=0.05)),                     # damped updates
     (32, 16, 12, dict(newton_maxit=1)),                         # not converged: status 1
     (32, 16, 12, dict(krylov_maxit=1)),
     (64, 32, 12, dict(problem=dict(recharge_omega=2e-3, q_in_amp=0.3, right_c_dirichlet=1))),
