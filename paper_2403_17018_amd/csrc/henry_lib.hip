@@ -1403,6 +1403,29 @@ struct Solver {
     return n == 0 ? 0 : 1;
   }
 
+  // Newton starts from a polynomial extrapolation of the last steps (u^0 itself on the first
+  // step); the fixed point of the step does not depend on the guess.  kind: 0 none, 1 k_extrapolate
+  // with factors gp, gc, 2 k_extrapolate_poly of this order.
+  struct Guess {
+    int kind, order;
+    double gp, gc;
+  };
+  Guess guess(int n) const {
+    if (!o.newton_extrapolate) return {0, 0, 0.0, 0.0};
+    const int order = guess_order(n);
+    if (order >= 0 && o.newton_extrapolate >= 3) return {2, order, 0.0, 0.0};
+    double gp = n == 0 ? 0.0 : 1.0, gc = gp;
+    if (n > 0 && order < 0) {
+      // pressure follows the inflow almost instantly: scale its last increment by the
+      // change of the inflow factor (linear in the forcing), bounded
+      auto f = [&](int k) { return 1.0 + std::sin(pr.recharge_omega * k * phys.tau); };
+      const double d0 = f(n) - f(n - 1), d1 = f(n + 1) - f(n);
+      gp = std::fabs(d0) > 1e-3 ? std::max(-3.0, std::min(3.0, d1 / d0)) : 1.0;
+      gc = 0.0;   // c starts from c^n: its increments do not follow the inflow factor
+    }
+    return {1, order, gp, gc};
+  }
+
   // Start of step n: c_old = c, Newton flags cleared, first guess extrapolated.  Inside a
   // captured graph the flags are cleared by a fill kernel, not a memset node.
   void step_prologue(int n, bool in_graph) {
@@ -1415,31 +1438,20 @@ struct Solver {
       HIPCHK(hipMemsetAsync(P.ndone.p, 0, S * sizeof(int), st));
       HIPCHK(hipMemsetAsync(P.nhist.p, 0, (size_t)S * 2 * sizeof(double), st));
     }
-    if (!o.newton_extrapolate) return;
-    // Newton starts from a polynomial extrapolation of the last steps (u^0 itself on the
-    // first step); the fixed point of the step does not depend on the guess
+    const Guess u = guess(n);
+    if (u.kind == 0) return;
     const size_t n2 = P.N;
     const dim3 g((unsigned)((n2 + 255) / 256));
-    const int order = guess_order(n);
-    if (order >= 0 && o.newton_extrapolate >= 3) {
+    if (u.kind == 2) {
       const bool h3 = o.newton_extrapolate == 4;
-      hipLaunchKernelGGL(k_extrapolate_poly, g, dim3(256), 0, st, n2, order, P.p.as<double>(), P.p_prev.as<double>(),
+      hipLaunchKernelGGL(k_extrapolate_poly, g, dim3(256), 0, st, n2, u.order, P.p.as<double>(), P.p_prev.as<double>(),
                          P.p_prev2.as<double>(), h3 ? P.p_prev3.as<double>() : nullptr);
-      hipLaunchKernelGGL(k_extrapolate_poly, g, dim3(256), 0, st, n2, order, P.c.as<double>(), P.c_prev.as<double>(),
+      hipLaunchKernelGGL(k_extrapolate_poly, g, dim3(256), 0, st, n2, u.order, P.c.as<double>(), P.c_prev.as<double>(),
                          P.c_prev2.as<double>(), h3 ? P.c_prev3.as<double>() : nullptr);
       return;
     }
-    double gp = n == 0 ? 0.0 : 1.0, gc = gp;
-    if (n > 0 && order < 0) {
-      // pressure follows the inflow almost instantly: scale its last increment by the
-      // change of the inflow factor (linear in the forcing), bounded
-      auto f = [&](int k) { return 1.0 + std::sin(pr.recharge_omega * k * phys.tau); };
-      const double d0 = f(n) - f(n - 1), d1 = f(n + 1) - f(n);
-      gp = std::fabs(d0) > 1e-3 ? std::max(-3.0, std::min(3.0, d1 / d0)) : 1.0;
-      gc = 0.0;   // c starts from c^n: its increments do not follow the inflow factor
-    }
-    hipLaunchKernelGGL(k_extrapolate, g, dim3(256), 0, st, n2, gp, P.p.as<double>(), P.p_prev.as<double>());
-    hipLaunchKernelGGL(k_extrapolate, g, dim3(256), 0, st, n2, gc, P.c.as<double>(), P.c_prev.as<double>());
+    hipLaunchKernelGGL(k_extrapolate, g, dim3(256), 0, st, n2, u.gp, P.p.as<double>(), P.p_prev.as<double>());
+    hipLaunchKernelGGL(k_extrapolate, g, dim3(256), 0, st, n2, u.gc, P.c.as<double>(), P.c_prev.as<double>());
   }
 
   // Newton update from vx: per-sample damping, convergence flags and statistics (ctrl[1]:
@@ -1510,7 +1522,7 @@ struct Solver {
            !ctx->prof.on && P.nlev - 1 <= SMALL_LEVELS && P.G.ncell <= SMALL_CELLS &&
            P.lv[1]->ncell <= SMALL_THREADS;
   }
-  void small_step() {
+  void small_step(int n) {
     SmallArgs A{};
     A.S = P.S;
     A.nl = P.nlev - 1;
@@ -1528,6 +1540,19 @@ struct Solver {
     A.p = P.p.as<double>();
     A.c = P.c.as<double>();
     A.c_old = P.c_old.as<double>();
+    const Guess u = guess(n);
+    const bool h3 = o.newton_extrapolate == 4;
+    A.guess = u.kind;
+    A.order = u.order;
+    A.gp = u.gp;
+    A.gc = u.gc;
+    A.hp[0] = P.p_prev.as<double>();
+    A.hp[1] = P.p_prev2.as<double>();
+    A.hp[2] = h3 ? P.p_prev3.as<double>() : nullptr;
+    A.hc[0] = P.c_prev.as<double>();
+    A.hc[1] = P.c_prev2.as<double>();
+    A.hc[2] = h3 ? P.c_prev3.as<double>() : nullptr;
+    A.c_range_tol = o.c_range_tol;
     A.uin = P.uin.as<double>();
     A.inv = P.LU.as<double>();
     A.status = P.status.as<int>();
@@ -1545,13 +1570,13 @@ struct Solver {
     A.p_ref = pr.rho0 * pr.g * pr.Ly;
     const uint32_t lds = (uint32_t)small_layout(A);
     const dim3 g(8 * tail_chunk(P.S)), bl(SMALL_THREADS);
-    const bool one = P.G.ncell <= 2 * SMALL_THREADS, c32 = P.lv[A.nl]->ncell <= 32;
+    const bool one = P.G.ncell <= SMALL_THREADS, c32 = P.lv[A.nl]->ncell <= 32;
     auto go = [&](auto kernel) {
       lds_prepare(kernel, 160 * 1024);
       hipLaunchKernelGGL(kernel, g, bl, lds, st, A, phys);
     };
-    if (one && c32) go(&k_small_step<1, 2, 16>);
-    else if (one) go(&k_small_step<1, 4, 32>);
+    if (one && c32) go(&k_small_step<0, 2, 16>);
+    else if (one) go(&k_small_step<0, 4, 32>);
     else if (c32) go(&k_small_step<2, 2, 16>);
     else go(&k_small_step<2, 4, 32>);
   }
@@ -1575,9 +1600,10 @@ struct Solver {
     const int order = guess_order(n);
     const bool settled = order >= 0 && order == guess_order(n + 1);
     if (small()) {
-      step_prologue(n, false);
-      small_step();
-    } else if (o.step_graphs && allow_graphs && !ctx->prof.on && pr.recharge_omega == 0.0 && settled &&
+      small_step(n);
+      return;
+    }
+    if (o.step_graphs && allow_graphs && !ctx->prof.on && pr.recharge_omega == 0.0 && settled &&
         o.newton_maxit > 1) {
       launch_step_graph<T>(n);
       const int remaining = read_ctrl(1);

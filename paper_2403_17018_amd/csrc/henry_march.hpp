@@ -67,10 +67,11 @@ __host__ __device__ constexpr int march_lds() {
 struct Face {
   double a, b, ac, dL, dH;
 };
-// km: 2 / mu, qd: half of F.qd; both 0 for a face that is not there.
+// km: 2 / mu, qd: half of F.qd; both 0 for a face that is not there.  flow, salt: the fluid and salt
+// mass fluxes L -> H.
 template <bool NORTH>
-__device__ __forceinline__ Face face_terms(const Phys& P, const FreePhys& F, double km, double qd, const CellState& L,
-                                           const CellState& H) {
+__device__ __forceinline__ Face face_flows(const Phys& P, const FreePhys& F, double km, double qd, const CellState& L,
+                                           const CellState& H, double& flow, double& salt) {
   const double kf = L.K * H.K * rcp_normal(L.K + H.K) * km;
   const double q = (L.phi + H.phi) * qd;
   const double rf = P.rho0 + F.hd * (L.c + H.c);
@@ -83,6 +84,8 @@ __device__ __forceinline__ Face face_terms(const Phys& P, const FreePhys& F, dou
   const double flux = rf * uA;
   const double cup = flux >= 0.0 ? L.c : H.c;
   const double dif = rf * q;
+  flow = flux;
+  salt = flux * cup - dif * (H.c - L.c);
   Face f;
   f.b = F.hd * (uA - grav);
   const double g = f.b * cup - F.hd * q * (H.c - L.c);
@@ -91,6 +94,12 @@ __device__ __forceinline__ Face face_terms(const Phys& P, const FreePhys& F, dou
   f.a = rk * F.w[NORTH];
   f.ac = f.a * cup;
   return f;
+}
+template <bool NORTH>
+__device__ __forceinline__ Face face_terms(const Phys& P, const FreePhys& F, double km, double qd, const CellState& L,
+                                           const CellState& H) {
+  double flow, salt;
+  return face_flows<NORTH>(P, F, km, qd, L, H, flow, salt);
 }
 
 // A row's coefficients as kept: FaceRow's of the west and east neighbours, its north face's both

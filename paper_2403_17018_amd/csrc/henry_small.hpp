@@ -6,12 +6,16 @@
 //
 // Launch by launch a step of these grids is some 110 launches of 3 to 5 us and four host reads,
 // however few the samples, and a batch iterates until its hardest sample is done.  Milliseconds a
-// solve, before and with this kernel: 32x16 cells, 48 steps, 16 samples 31.0 and 9.9, 256 samples
-// 40.5 and 11.6; 64x32 cells, 48 steps, 64 samples 42.6 and 22.5, 333 samples 88 and 45; 24 steps,
-// 1000 samples 147 and 59; 12 steps, 4096 samples 574 and 144 (32x16: 83 and 63): it is taken for
-// every batch size.  What bounds it is the chain of a cycle's passes, each a barrier, a few LDS
-// reads and some 200 dependent FP64 operations, and of the coarsest operator's inversion; one
-// workgroup (LDS, registers) fits a compute unit.
+// solve, before and with this kernel: 32x16 cells, 48 steps, 16 samples 31.0 and 8.1, 256 samples
+// 40.5 and 9.3; 64x32 cells, 48 steps, 64 samples 42.6 and 19.4, 333 samples 88 and 39; 24 steps,
+// 1000 samples 147 and 51; 12 steps, 4096 samples 574 and 144 (32x16: 83 and 63): it is taken for
+// every batch size.  What bounds it is latency: one workgroup (LDS, registers) fits a compute unit
+// and a step is a chain of passes, each a barrier, a few LDS reads and a row.  Of a step's 150 us at
+// 32x16 (3 Newton, 3 BiCGStab iterations) the fine passes take 19, the coarser grids 26, the
+// coarsest operator's inversion 24 (or twice), residuals and rows 45, the Krylov part 18.  Rows
+// formed from the state in every pass instead of kept made 10.8 ms of the 9.4 then; with two cells
+// of each colour a thread keeping them spills (64x32x64: 20.7 ms with one coarser grid's kept, 22.5
+// with two).  The step's start and its balance as launches of their own took 0.5 ms of 9.4.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,14 +32,17 @@ struct SmallArgs {
   int at[SMALL_LEVELS + 2];                     // the grids' places in LDS (small_layout), the rest's
   double hy[SMALL_LEVELS + 1];
   FreePhys F[SMALL_LEVELS + 1];
-  double *p, *c;                                // state [cell][S]: the first guess in, the solution out
-  const double *c_old, *uin;
+  double *p, *c, *c_old;                        // state [cell][S], the step before's in, the new one out; its c
+  double *hp[3], *hc[3];                        // the states of the steps before that, newest first
+  int guess, order;                             // Newton's first guess: 0 the state, 1 linear, 2 a polynomial
+  double gp, gc;                                // (k_extrapolate's factors)
+  const double* uin;
   const double *phi[SMALL_LEVELS + 1], *K[SMALL_LEVELS + 1];
   double* inv;                                  // [S][n][n]: the coarsest operators' inverses
   int* status;
-  double* stats;                                // [S][4]: Newton, BiCGStab iterations
+  double* stats;                                // [S][4]: Newton, BiCGStab iterations, balance defects
   int nu_pre, nu_post, newton_maxit, krylov_maxit;
-  double rtol2, breakdown, newton_tol, pred_tol, dc_max, jac_reuse, p_ref;
+  double rtol2, breakdown, newton_tol, pred_tol, dc_max, jac_reuse, p_ref, c_range_tol;
 };
 
 // LDS in units of 16 bytes: per grid its state (p c, phi K), iterate and (but for the finest)
@@ -85,6 +92,47 @@ __device__ __forceinline__ int small_at(int i, int j, int nx, int ny) {
   return ((i + j) & 1) * hx * ny + j * hx + (i >> 1);
 }
 
+// Folds the values of a wavefront's lanes into lane 63's (0 where there is no lane to the left).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lanes_left(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <typename Op>
+__device__ __forceinline__ void wave_fold(double& a, double& b, Op&& op) {
+  auto step = [&](auto ctrl, auto rows) {
+    a = op(a, lanes_left<decltype(ctrl)::value, decltype(rows)::value>(a));
+    b = op(b, lanes_left<decltype(ctrl)::value, decltype(rows)::value>(b));
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // 1, 2, 4, 8 lanes in rows of 16
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // the rows' last lanes on
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+}
+
+// k_extrapolate and k_extrapolate_poly for one value; the history h moves on by one.
+__device__ __forceinline__ double small_guess(const SmallArgs& A, double un, double gamma, double* const (&h)[3], size_t q) {
+  if (A.guess == 0) return un;
+  if (A.guess == 1) {
+    const double v = gamma != 0.0 ? un + gamma * (un - h[0][q]) : un;
+    h[0][q] = un;
+    return v;
+  }
+  const double a = A.order > 0 ? h[0][q] : un, b = A.order > 1 ? h[1][q] : a;
+  const double v = A.order == 3   ? 4.0 * (un + b) - 6.0 * a - h[2][q]
+                   : A.order == 2 ? 3.0 * (un - a) + b
+                   : A.order == 1 ? 2.0 * un - a
+                                  : un;
+  if (h[2]) h[2][q] = b;
+  h[1][q] = a;
+  h[0][q] = un;
+  return v;
+}
+
 struct SmallGrid {
   int nx, ny, n;
   Two *pc, *fk, *x, *b;
@@ -94,21 +142,35 @@ struct SmallGrid {
   }
 };
 
-// The four faces' terms of a cell; f(side, face, the neighbour's place), sides 0 W, 1 E, 2 S, 3 N.
+// The four faces' terms of a cell; f(side, face, the neighbour's place, the fluxes through it L -> H),
+// sides 0 W, 1 E, 2 S, 3 N.
 template <typename Fn>
 __device__ __forceinline__ void small_faces(const SmallGrid& G, const Phys& P, const FreePhys& F, const SmallCell& c,
                                             const CellState& own, Fn&& f) {
   const double km = 2.0 * F.inv_mu, qx = 0.5 * F.qd[0], qy = 0.5 * F.qd[1];
   const bool w = c.i > 0, e = c.i < G.nx - 1, s = c.j > 0, n = c.j < G.ny - 1;
-  f(0, face_terms<false>(P, F, w ? km : 0.0, w ? qx : 0.0, G.state(c.w), own), c.w);
-  f(1, face_terms<false>(P, F, e ? km : 0.0, e ? qx : 0.0, own, G.state(c.e)), c.e);
-  f(2, face_terms<true>(P, F, s ? km : 0.0, s ? qy : 0.0, G.state(c.s), own), c.s);
-  f(3, face_terms<true>(P, F, n ? km : 0.0, n ? qy : 0.0, own, G.state(c.n)), c.n);
+  double flow, salt;
+  {
+    const Face a = face_flows<false>(P, F, w ? km : 0.0, w ? qx : 0.0, G.state(c.w), own, flow, salt);
+    f(0, a, c.w, flow, salt);
+  }
+  {
+    const Face a = face_flows<false>(P, F, e ? km : 0.0, e ? qx : 0.0, own, G.state(c.e), flow, salt);
+    f(1, a, c.e, flow, salt);
+  }
+  {
+    const Face a = face_flows<true>(P, F, s ? km : 0.0, s ? qy : 0.0, G.state(c.s), own, flow, salt);
+    f(2, a, c.s, flow, salt);
+  }
+  {
+    const Face a = face_flows<true>(P, F, n ? km : 0.0, n ? qy : 0.0, own, G.state(c.n), flow, salt);
+    f(3, a, c.n, flow, salt);
+  }
 }
 // the neighbours' part of the row times x
 __device__ __forceinline__ Two small_off(const SmallGrid& G, const Phys& P, const FreePhys& F, const SmallCell& c) {
   Two y{0.0, 0.0};
-  small_faces(G, P, F, c, G.state(c.at), [&](int side, const Face& f, int q) {
+  small_faces(G, P, F, c, G.state(c.at), [&](int side, const Face& f, int q, double, double) {
     const Two v = G.x[q];
     const bool high = (side & 1) == 0;   // the cell is the high side of its west and south faces
     y[0] += (high ? -f.b : f.b) * v[1] - f.a * v[0];
@@ -133,7 +195,7 @@ __device__ __forceinline__ void small_centre(const SmallGrid& G, const Phys& P, 
   D[0] = D[2] = 0.0;
   D[1] = v * P.drho;
   D[3] = v * (P.rho0 + 2.0 * P.drho * own.c);
-  small_faces(G, P, F, c, own, [&](int side, const Face& f, int) {
+  small_faces(G, P, F, c, own, [&](int side, const Face& f, int, double, double) {
     const bool high = (side & 1) == 0;
     D[0] += f.a;
     D[1] += high ? -f.b : f.b;
@@ -144,50 +206,29 @@ __device__ __forceinline__ void small_centre(const SmallGrid& G, const Phys& P, 
   side_terms(P, F, G.nx, c.i, c.j, own, D);
 }
 
-// D^{-1} (b - the neighbours' part), or D^{-1} b from x = 0
-__device__ __forceinline__ Two small_solve(const SmallGrid& G, const Phys& P, const FreePhys& F, const SmallCell& c,
-                                           bool zero) {
-  const CellState own = G.state(c.at);
-  const double v = F.vt * own.phi;
-  double D[4] = {0.0, v * P.drho, 0.0, v * (P.rho0 + 2.0 * P.drho * own.c)};
-  Two r = G.b[c.at];
-  small_faces(G, P, F, c, own, [&](int side, const Face& f, int q) {
-    const bool high = (side & 1) == 0;
-    D[0] += f.a;
-    D[1] += high ? -f.b : f.b;
-    D[2] += f.ac;
-    D[3] += high ? -f.dH : f.dL;
-    if (zero) return;
-    const Two x = G.x[q];
-    r[0] -= (high ? -f.b : f.b) * x[1] - f.a * x[0];
-    r[1] -= (high ? -f.dL : f.dH) * x[1] - f.ac * x[0];
-  });
-  side_terms(P, F, G.nx, c.i, c.j, own, D);
-  return small_inverse(D)(r);
-}
-// b - A x of a row
-__device__ __forceinline__ Two small_residual(const SmallGrid& G, const Phys& P, const FreePhys& F, const SmallCell& c) {
-  const CellState own = G.state(c.at);
-  const double v = F.vt * own.phi;
-  double D[4] = {0.0, v * P.drho, 0.0, v * (P.rho0 + 2.0 * P.drho * own.c)};
-  Two r = G.b[c.at];
-  small_faces(G, P, F, c, own, [&](int side, const Face& f, int q) {
-    const bool high = (side & 1) == 0;
-    D[0] += f.a;
-    D[1] += high ? -f.b : f.b;
-    D[2] += f.ac;
-    D[3] += high ? -f.dH : f.dL;
-    const Two x = G.x[q];
-    r[0] -= (high ? -f.b : f.b) * x[1] - f.a * x[0];
-    r[1] -= (high ? -f.dL : f.dH) * x[1] - f.ac * x[0];
-  });
-  side_terms(P, F, G.nx, c.i, c.j, own, D);
-  const Two x = G.x[c.at];
-  return r - Two{D[0] * x[0] + D[1] * x[1], D[2] * x[0] + D[3] * x[1]};
-}
+// The neighbours' blocks of a row, kept in registers.
+struct SmallRow {
+  double o[4][4];
+  __device__ __forceinline__ void set(int side, double b0, double b1, double b2, double b3) {
+    o[side][0] = b0;
+    o[side][1] = b1;
+    o[side][2] = b2;
+    o[side][3] = b3;
+  }
+  __device__ __forceinline__ Two off(const SmallGrid& G, const SmallCell& c) const {
+    Two y{0.0, 0.0};
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const Two v = G.x[n == 0 ? c.w : n == 1 ? c.e : n == 2 ? c.s : c.n];
+      y += Two{o[n][0] * v[0] + o[n][1] * v[1], o[n][2] * v[0] + o[n][3] * v[1]};
+    }
+    return y;
+  }
+};
 
-// H: cells of each colour of the finest grid per thread (1 up to 1024 cells, 2 up to 2048); RC, TC:
-// the inversion's shape (tail_inverse).
+// H: cells of each colour of the finest grid per thread (2 up to 2048 cells), or 0: one cell a thread
+// (up to 512), whose rows of the operator and of the first two coarser grids' are kept in registers.
+// RC, TC: the inversion's shape (tail_inverse).
 template <int H, int RC, int TC>
 __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Phys P) {
   extern __shared__ Two ssh[];
@@ -208,21 +249,43 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
   Two* const scratch = ssh + A.at[nl + 1];
   double* const red = reinterpret_cast<double*>(scratch + small_scratch(A));   // [2][2][8]
   const int half = G.n >> 1, nu = 2 * C.n;
-  // this thread's cells: H red, then H black (i and j kept packed: the rest is found anew, which
-  // takes fewer registers)
-  int ij[2 * H];
+  // this thread's cells: H red, then H black (their i and j packed: the rest is found anew each time,
+  // which takes fewer registers), or one
+  constexpr int NC = H ? 2 * H : 1, NR = H ? H : 1;   // cells, of them red (H = 0: or black)
+  int ij[NC];
+  SmallCell mine{};
+  if constexpr (H > 0) {
 #pragma unroll
-  for (int m = 0; m < 2 * H; ++m) {
-    const int u = t + SMALL_THREADS * (m % H);
-    const SmallCell c = small_cell(m / H, u, G.nx, G.ny);
-    ij[m] = u < half ? c.j << 16 | c.i : -1;
+    for (int m = 0; m < NC; ++m) {
+      const int u = t + SMALL_THREADS * (m % NR);
+      const SmallCell c = small_cell(m / NR, u, G.nx, G.ny);
+      ij[m] = u < half ? c.j << 16 | c.i : -1;
+    }
+  } else if (t < G.n) {
+    mine = t < half ? small_cell(0, t, G.nx, G.ny) : small_cell(1, t - half, G.nx, G.ny);
   }
   auto cell = [&](int m, SmallCell& c) {
-    int k = ij[m];
-    asm volatile("" : "+v"(k));
-    if (k < 0) return false;
-    c = small_cell(m / H, t + SMALL_THREADS * (m % H), k & 0xffff, k >> 16, G.nx, G.ny);
-    return true;
+    if constexpr (H > 0) {
+      int k = ij[m];
+      asm volatile("" : "+v"(k));
+      if (k < 0) return false;
+      c = small_cell(m / NR, t + SMALL_THREADS * (m % NR), k & 0xffff, k >> 16, G.nx, G.ny);
+      return true;
+    } else {
+      c = mine;
+      return t < G.n;
+    }
+  };
+  // its m-th cell of a colour; k: which of its cells that is
+  auto cell_in = [&](int colour, int m, SmallCell& c, int& k) {
+    if constexpr (H > 0) {
+      k = colour * H + m;
+      return cell(k, c);
+    } else {
+      k = 0;
+      c = mine;
+      return colour == 0 ? t < half : t >= half && t < G.n;
+    }
   };
   auto global = [&](const SmallCell& c) { return ((size_t)c.j * G.nx + c.i) * S + s; };
   // its cell of a coarser smoothed grid
@@ -232,15 +295,13 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     c = t < h ? small_cell(0, t, g.nx, g.ny) : small_cell(1, t - h, g.nx, g.ny);
     return true;
   };
+  // over the workgroup, for every thread; two buffers by turns, so one barrier each
   int flip = 0;
-  auto sum2 = [&](double& a, double& b) {
-    for (int k = 32; k > 0; k >>= 1) {
-      a += __shfl_xor(a, k);
-      b += __shfl_xor(b, k);
-    }
+  auto fold2 = [&](double& a, double& b, auto&& op) {
+    wave_fold(a, b, op);
     double* q = red + 16 * flip;
     flip ^= 1;
-    if ((t & 63) == 0) {
+    if ((t & 63) == 63) {
       q[t >> 6] = a;
       q[8 + (t >> 6)] = b;
     }
@@ -248,38 +309,24 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     a = b = 0.0;
 #pragma unroll
     for (int k = 0; k < SMALL_THREADS / 64; ++k) {
-      a += q[k];
-      b += q[8 + k];
+      a = op(a, q[k]);
+      b = op(b, q[8 + k]);
     }
   };
-  auto larger = [](double a, double b) { return b > a || b != b ? b : a; };   // a NaN stays
-  auto max2 = [&](double& a, double& b) {
-    for (int k = 32; k > 0; k >>= 1) {
-      a = larger(a, __shfl_xor(a, k));
-      b = larger(b, __shfl_xor(b, k));
-    }
-    double* q = red + 16 * flip;
-    flip ^= 1;
-    if ((t & 63) == 0) {
-      q[t >> 6] = a;
-      q[8 + (t >> 6)] = b;
-    }
-    lds_barrier();
-    a = b = 0.0;
-#pragma unroll
-    for (int k = 0; k < SMALL_THREADS / 64; ++k) {
-      a = larger(a, q[k]);
-      b = larger(b, q[8 + k]);
-    }
-  };
+  auto larger = [](double a, double b) { return b > a || b != b ? b : a; };   // (of values >= 0; a NaN stays)
+  auto sum2 = [&](double& a, double& b) { fold2(a, b, [](double u, double v) { return u + v; }); };
+  auto max2 = [&](double& a, double& b) { fold2(a, b, larger); };
 
   // state and coefficients into LDS
+  double co[NC] = {};   // the step before's c
 #pragma unroll
-  for (int m = 0; m < 2 * H; ++m) {
+  for (int m = 0; m < NC; ++m) {
     SmallCell c;
     if (!cell(m, c)) continue;
     const size_t q = global(c);
-    G.pc[c.at] = Two{A.p[q], A.c[q]};
+    const double pn = A.p[q], cn = A.c[q];
+    A.c_old[q] = co[m] = cn;
+    G.pc[c.at] = Two{small_guess(A, pn, A.gp, A.hp, q), small_guess(A, cn, A.gc, A.hc, q)};
     G.fk[c.at] = Two{A.phi[0][q], A.K[0][q]};
   }
   for (int l = 1; l <= nl; ++l) {
@@ -291,26 +338,125 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
   }
   lds_barrier();
 
-  Inv2 Di[2 * H];   // inverse centre blocks of the fine cells
+  constexpr int KC = H ? 0 : 2;   // coarser grids whose rows are kept
+  Inv2 Di[NC], Dc[2];             // inverse centre blocks
+  SmallRow row, rc[2];
+  SmallCell cc[2] = {};
+  if constexpr (KC > 0) {
+    for (int l = 1; l < nl && l <= KC; ++l) (void)coarse(grid(l), l == 1 ? cc[0] : cc[1]);
+  }
   double iv[8];                                // the first eight terms of this thread's row of the inverse
   double* const inv = A.inv + (size_t)s * nu * nu;
+  const double inflow = -(P.rho0 + P.drho * P.c_left) * A.uin[s] * P.uin_fac * P.hy;
   const int part = t & 7;
   double last = 0.0, r2prev = 0.0, newtons = 0.0, kits = 0.0;
   int status = 0;
   bool done = false, fresh = true;
 
-  // ---- x = M^{-1} b: b of this thread's fine cells in, x in G.x; rd: the last red right-hand sides
-  // less their neighbours' part (D x of the red cells)
-  auto cycle = [&](const Two (&b)[2 * H], Two (&rd)[H]) {
-    const Phys P0 = phys(0);
+  // ---- the coarser grids' part of a cycle: one copy of each kind of pass (the kernel's code is
+  // read through by every wavefront, and what exceeds the instruction cache is fetched each time)
+  auto gather = [&](const SmallGrid& f, int I, int J) {   // the two red children's residuals
+    const int hx = f.nx >> 1;
+    return scratch[2 * J * hx + I] + scratch[(2 * J + 1) * hx + I];
+  };
+  // the correction of the grid below prolonged onto a black cell of grid l
+  auto prolong = [&](const SmallGrid& g, int l, const SmallCell& c) {
+    const SmallGrid e = grid(l + 1);
+    const int I = c.i >> 1, J = c.j >> 1;
+    const int I2 = min(max(I + ((c.i & 1) ? 1 : -1), 0), e.nx - 1), J2 = min(max(J + ((c.j & 1) ? 1 : -1), 0), e.ny - 1);
+    auto v = [&](int i, int j) { return e.x[l + 1 == nl ? j * e.nx + i : small_at(i, j, e.nx, e.ny)]; };
+    g.x[c.at] += 0.5625 * v(I, J) + 0.1875 * (v(I2, J) + v(I, J2)) + 0.0625 * v(I2, J2);
+  };
+  const int cJ = t / C.nx, cI = t - cJ * C.nx;
+  auto coarse_cycle = [&] {
+#pragma unroll 1
+    for (int q = 1; q < 2 * nl; ++q) {   // grids 1 .. nl - 1 down, nl, nl - 1 .. 1 up
+      if (q == nl) {
+        if (t < C.n) C.b[t] = gather(grid(nl - 1), cI, cJ);
+        lds_barrier();
+        const double* v = reinterpret_cast<const double*>(C.b);
+        double* y = reinterpret_cast<double*>(C.x);
+        for (int row = t >> 3, k = 0; row < nu; row += SMALL_THREADS / 8, ++k) {
+          double acc = 0.0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int w = part + 8 * e;
+            if (w < nu) acc += (k == 0 ? iv[e] : inv[(size_t)row * nu + w]) * v[w];
+          }
+          for (int w = part + 64; w < nu; w += 8) acc += inv[(size_t)row * nu + w] * v[w];
+#pragma unroll
+          for (int o = 1; o < 8; o <<= 1) acc += __shfl_xor(acc, o);
+          if (part == 0) y[row] = acc;
+        }
+        lds_barrier();
+        continue;
+      }
+      const bool down = q < nl;
+      const int l = down ? q : 2 * nl - q;
+      const SmallGrid g = grid(l);
+      const Phys Pl = phys(l);
+      SmallCell c;
+      const bool own = t < g.n;
+      if (KC >= 1 && l == 1) c = cc[0];
+      else if (KC >= 2 && l == 2) c = cc[1];
+      else (void)coarse(g, c);
+      const int colour = own ? t >= (g.n >> 1) : 2;
+      if (down && own) {
+        g.b[c.at] = gather(grid(l - 1), c.i, c.j);
+      } else if (!down && colour == 1) {
+        prolong(g, l, c);
+      }
+      if (!down) lds_barrier();
+      const int passes = 2 * (down ? A.nu_pre : A.nu_post) + (down ? 1 : 0);   // the last one down: the residual
+      auto sweep = [&](auto&& offd, const Inv2& D) {
+        Two rd{0.0, 0.0};
+#pragma unroll 1
+        for (int k = 0; k < passes; ++k) {
+          if (colour == (k & 1)) {
+            Two r = g.b[c.at];
+            if (!down || k > 0) r -= offd();
+            if (down && k == 2 * A.nu_pre) {
+              scratch[c.at] = r - rd;
+            } else {
+              rd = r;
+              g.x[c.at] = D(r);
+            }
+          }
+          lds_barrier();
+        }
+      };
+      if (KC >= 1 && l == 1) {
+        sweep([&] { return rc[0].off(g, c); }, Dc[0]);
+      } else if (KC >= 2 && l == 2) {
+        sweep([&] { return rc[1].off(g, c); }, Dc[1]);
+      } else {
+        Inv2 D{};
+        if (own) {
+          double d[4];
+          small_centre(g, Pl, A.F[l], c, d, [](int, double, double, double, double) {});
+          D = small_inverse(d);
+        }
+        sweep([&] { return small_off(g, Pl, A.F[l], c); }, D);
+      }
+    }
+  };
+  // ---- y = A M^{-1} b: b of this thread's fine cells in, the cycle's iterate in G.x.  D x of a red
+  // cell is its right-hand side less the neighbours' part when it was last passed over (rd), so a
+  // residual or product there is the neighbours' change; the last black pass leaves A x = b there.
+  auto off = [&](const SmallCell& c) {
+    if constexpr (H > 0) return small_off(G, P, A.F[0], c);
+    else return row.off(G, c);
+  };
+  auto cycle = [&](const Two (&b)[NC], Two (&y)[NC]) {
+    Two rd[NR];
     auto pass = [&](int colour, bool zero) {
 #pragma unroll
-      for (int m = 0; m < H; ++m) {
-        const int k = colour * H + m;
+      for (int m = 0; m < NR; ++m) {
         SmallCell c;
-        if (!cell(k, c)) continue;
+        int k;
+        if (!cell_in(colour, m, c, k)) continue;
         Two r = b[k];
-        if (!zero) r -= small_off(G, P0, A.F[0], c);
+        if (!zero) r -= off(c);
         if (colour == 0) rd[m] = r;
         G.x[c.at] = Di[k](r);
       }
@@ -318,84 +464,24 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     };
     pass(0, true);
     pass(1, false);
+#pragma unroll 1
     for (int sw = 1; sw < A.nu_pre; ++sw) {
       pass(0, false);
       pass(1, false);
     }
 #pragma unroll
-    for (int m = 0; m < H; ++m) {   // D x = rd of the last red pass: what is left is the neighbours' change
+    for (int m = 0; m < NR; ++m) {
       SmallCell c;
-      if (!cell(m, c)) continue;
-      scratch[c.at] = b[m] - rd[m] - small_off(G, P0, A.F[0], c);
+      int k;
+      if (cell_in(0, m, c, k)) scratch[c.at] = b[k] - rd[m] - off(c);
     }
     lds_barrier();
-    auto gather = [&](const SmallGrid& f, int I, int J) {   // the two red children's residuals
-      const int hx = f.nx >> 1;
-      return scratch[2 * J * hx + I] + scratch[(2 * J + 1) * hx + I];
-    };
-#pragma unroll 1
-    for (int l = 1; l < nl; ++l) {
-      const SmallGrid g = grid(l);
-      const Phys Pl = phys(l);
-      SmallCell c;
-      const bool own = coarse(g, c), is_red = own && t < (g.n >> 1), black = own && !is_red;
-      if (own) g.b[c.at] = gather(grid(l - 1), c.i, c.j);
-#pragma unroll 1
-      for (int sw = 0; sw < A.nu_pre; ++sw) {
-        if (is_red) g.x[c.at] = small_solve(g, Pl, A.F[l], c, sw == 0);
-        lds_barrier();
-        if (black) g.x[c.at] = small_solve(g, Pl, A.F[l], c, false);
-        lds_barrier();
-      }
-      if (is_red) scratch[c.at] = small_residual(g, Pl, A.F[l], c);
-      lds_barrier();
-    }
-    if (t < C.n) C.b[t] = gather(grid(nl - 1), t % C.nx, t / C.nx);
-    lds_barrier();
-    {
-      const double* v = reinterpret_cast<const double*>(C.b);
-      double* y = reinterpret_cast<double*>(C.x);
-      for (int row = t >> 3, k = 0; row < nu; row += SMALL_THREADS / 8, ++k) {
-        double acc = 0.0;
+    coarse_cycle();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int q = part + 8 * e;
-          if (q < nu) acc += (k == 0 ? iv[e] : inv[(size_t)row * nu + q]) * v[q];
-        }
-        for (int q = part + 64; q < nu; q += 8) acc += inv[(size_t)row * nu + q] * v[q];
-#pragma unroll
-        for (int o = 1; o < 8; o <<= 1) acc += __shfl_xor(acc, o);
-        if (part == 0) y[row] = acc;
-      }
-    }
-    lds_barrier();
-    // the correction prolonged onto a black cell
-    auto prolong = [&](const SmallGrid& g, const SmallGrid& e, bool coarsest, const SmallCell& c) {
-      const int I = c.i >> 1, J = c.j >> 1;
-      const int I2 = min(max(I + ((c.i & 1) ? 1 : -1), 0), e.nx - 1), J2 = min(max(J + ((c.j & 1) ? 1 : -1), 0), e.ny - 1);
-      auto v = [&](int i, int j) { return e.x[coarsest ? j * e.nx + i : small_at(i, j, e.nx, e.ny)]; };
-      g.x[c.at] += 0.5625 * v(I, J) + 0.1875 * (v(I2, J) + v(I, J2)) + 0.0625 * v(I2, J2);
-    };
-#pragma unroll 1
-    for (int l = nl - 1; l >= 1; --l) {
-      const SmallGrid g = grid(l);
-      const Phys Pl = phys(l);
+    for (int m = 0; m < NR; ++m) {
       SmallCell c;
-      const bool own = coarse(g, c), is_red = own && t < (g.n >> 1), black = own && !is_red;
-      if (black) prolong(g, grid(l + 1), l + 1 == nl, c);
-      lds_barrier();
-#pragma unroll 1
-      for (int sw = 0; sw < A.nu_post; ++sw) {
-        if (is_red) g.x[c.at] = small_solve(g, Pl, A.F[l], c, false);
-        lds_barrier();
-        if (black) g.x[c.at] = small_solve(g, Pl, A.F[l], c, false);
-        lds_barrier();
-      }
-    }
-#pragma unroll
-    for (int m = H; m < 2 * H; ++m) {
-      SmallCell c;
-      if (cell(m, c)) prolong(G, grid(1), nl == 1, c);
+      int k;
+      if (cell_in(1, m, c, k)) prolong(G, 0, c);
     }
     lds_barrier();
 #pragma unroll 1
@@ -403,52 +489,53 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
       pass(0, false);
       pass(1, false);
     }
-  };
-  // A x after a cycle: its black pass left A x = b on the black cells
-  auto apply = [&](const Two (&b)[2 * H], const Two (&rd)[H], Two (&y)[2 * H]) {
-    const Phys P0 = phys(0);
 #pragma unroll
-    for (int m = 0; m < H; ++m) {
+    for (int k = 0; k < NC; ++k) y[k] = b[k];   // (black cells; b is 0 where the thread has no cell)
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
       SmallCell c;
-      y[m] = y[H + m] = Two{0.0, 0.0};
-      if (cell(m, c)) y[m] = rd[m] + small_off(G, P0, A.F[0], c);
-      if (cell(H + m, c)) y[H + m] = b[H + m];
+      int k;
+      if (cell_in(0, m, c, k)) y[k] = rd[m] + off(c);
     }
   };
 
   for (int it = 0; it < A.newton_maxit && !done; ++it) {
-    // ---- residual and inverse centre blocks at the state (the assembly's formulas)
-    Two R[2 * H];
-    const Phys& P0 = P;   // of the finest grid
+    // ---- residual, inverse centre blocks and kept rows at the state
+    Two R[NC];
     double r2 = 0.0, zero = 0.0;
 #pragma unroll
-    for (int m = 0; m < 2 * H; ++m) {
+    for (int m = 0; m < NC; ++m) {
       R[m] = Two{0.0, 0.0};
       SmallCell c;
       if (!cell(m, c)) continue;
       const CellState o = G.state(c.at);
-      const double co = A.c_old[global(c)];
-      const double rP = P0.rho0 + P0.drho * o.c, ro = P0.rho0 + P0.drho * co;
-      double Rp = P0.vol * o.phi * (rP - ro) / P0.tau, Rc = P0.vol * o.phi * (rP * o.c - ro * co) / P0.tau;
-      double D[4] = {0.0, P0.vol * o.phi * P0.drho / P0.tau, 0.0,
-                     P0.vol * o.phi * (P0.rho0 + 2.0 * P0.drho * o.c) / P0.tau};
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const bool north = d >= 2, high = (d & 1) == 0;
-        if (!(d == 0 ? c.i > 0 : d == 1 ? c.i < G.nx - 1 : d == 2 ? c.j > 0 : c.j < G.ny - 1)) continue;
-        const CellState q = G.state(d == 0 ? c.w : d == 1 ? c.e : d == 2 ? c.s : c.n);
-        FaceFlux f;
-        if (high) face_flux(P0, north, q.p, q.c, q.phi, q.K, o.p, o.c, o.phi, o.K, f);
-        else face_flux(P0, north, o.p, o.c, o.phi, o.K, q.p, q.c, q.phi, q.K, f);
-        const double sg = high ? -1.0 : 1.0;
-        Rp += sg * f.F;
-        Rc += sg * f.G;
+      const double v = A.F[0].vt * o.phi;
+      const double rP = P.rho0 + P.drho * o.c;
+      double Rp = v * (P.drho * (o.c - co[m])), Rc = v * (rP * o.c - (P.rho0 + P.drho * co[m]) * co[m]);
+      double D[4] = {0.0, v * P.drho, 0.0, v * (P.rho0 + 2.0 * P.drho * o.c)};
+      small_faces(G, P, A.F[0], c, o, [&](int side, const Face& f, int, double flow, double salt) {
+        const bool high = (side & 1) == 0;
+        Rp += high ? -flow : flow;
+        Rc += high ? -salt : salt;
         D[0] += f.a;
-        D[1] += sg * f.bF;
-        D[2] += f.a * f.cup;
-        D[3] += sg * (high ? f.dGH : f.dGL);
+        D[1] += high ? -f.b : f.b;
+        D[2] += f.ac;
+        D[3] += high ? -f.dH : f.dL;
+        if (H == 0) row.set(side, -f.a, high ? -f.b : f.b, -f.ac, high ? -f.dL : f.dH);
+      });
+      const double dif = o.phi * A.F[0].side_dif;
+      if (c.i == 0) {   // the inflow, and diffusion to c_left
+        Rp += inflow;
+        Rc += inflow * P.c_left + dif * rP * (o.c - P.c_left);
       }
-      boundary_terms(P0, G.nx, c.i, c.j, o.p, o.c, o.phi, o.K, c.i == 0 ? A.uin[s] : 0.0, Rp, Rc, D);
+      if (c.i == G.nx - 1) {   // the sea: what flows in has its density and concentration
+        const double u = o.K * A.F[0].side_k * (o.p + P.rho1 * P.g * (-P.Ly + (c.j + 0.5) * P.hy));
+        const double flow = (u < 0.0 ? P.rho1 : rP) * u;
+        Rp += flow;
+        Rc += flow * (u < 0.0 ? 1.0 : o.c);
+        if (P.right_dir) Rc += dif * rP * (o.c - 1.0);
+      }
+      side_terms(P, A.F[0], G.nx, c.i, c.j, o, D);
       R[m] = Two{Rp, Rc};
       Di[m] = small_inverse(D);
       r2 += Rp * Rp + Rc * Rc;
@@ -474,6 +561,15 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
           g.pc[l < nl ? small_at(I, J, g.nx, g.ny) : q] = 0.25 * v;
         }
         lds_barrier();
+      }
+#pragma unroll
+      for (int l = 1; l <= KC; ++l) {
+        if (l >= nl || t >= A.nx[l] * A.ny[l]) continue;
+        double D[4];
+        small_centre(grid(l), phys(l), A.F[l], cc[l - 1], D, [&](int side, double b0, double b1, double b2, double b3) {
+          rc[l - 1].set(side, b0, b1, b2, b3);
+        });
+        Dc[l - 1] = small_inverse(D);
       }
       double* const Jc = reinterpret_cast<double*>(scratch);   // [20][cells]
       if (t < C.n) {
@@ -502,86 +598,77 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
 #pragma unroll
       for (int e = 0; e < 8; ++e) iv[e] = (t >> 3) < nu && part + 8 * e < nu ? inv[(size_t)(t >> 3) * nu + part + 8 * e] : 0.0;
     }
-    // ---- BiCGStab: A dx = -R with the shadow residual R
-    Two x[2 * H], r[2 * H], p[2 * H], v[2 * H];
+    // ---- BiCGStab: A dx = -R with the shadow residual R.  Each iteration is two half-steps, p
+    // (half 0) and then s (half 1), through one copy of the cycle.
+    Two x[NC], r[NC], p[NC], v[NC];
 #pragma unroll
-    for (int m = 0; m < 2 * H; ++m) {
+    for (int m = 0; m < NC; ++m) {
       x[m] = Two{0.0, 0.0};
       r[m] = p[m] = -R[m];
       v[m] = Two{0.0, 0.0};
     }
-    double rho = -r2, al = 0.0, om = 0.0, beta = 0.0;
-    for (int k = 0; k < A.krylov_maxit && act; ++k) {
-      Two rd[H];
-      if (k > 0) {
+    double rho = -r2, al = 0.0, om = 0.0;
+    for (int k = 0; k < 2 * A.krylov_maxit && act; ++k) {
+      const bool second = k & 1;
+      Two in[NC], y[NC];
 #pragma unroll
-        for (int m = 0; m < 2 * H; ++m) p[m] = r[m] + beta * (p[m] - om * v[m]);
+      for (int m = 0; m < NC; ++m) in[m] = second ? r[m] : p[m];
+      cycle(in, y);
+      double a = 0.0, b = 0.0;   // half 0: (R, v); half 1: (t, s), (t, t)
+#pragma unroll
+      for (int m = 0; m < NC; ++m) {
+        const Two w = second ? r[m] : R[m];
+        a += w[0] * y[m][0] + w[1] * y[m][1];
+        b += y[m][0] * y[m][0] + y[m][1] * y[m][1];
       }
-      cycle(p, rd);
-      apply(p, rd, v);
-      double rv = 0.0, ss = 0.0, d = 0.0;
+      sum2(a, b);
+      double step;
+      if (!second) {
+        if (!(a != 0.0 && isfinite(a) && !(fabs(a) <= A.breakdown * fabs(rho)))) {
+          status = 2;   // (near) breakdown
+          break;
+        }
+        step = al = rho / a;
 #pragma unroll
-      for (int m = 0; m < 2 * H; ++m) rv += R[m][0] * v[m][0] + R[m][1] * v[m][1];
-      sum2(rv, d);
-      al = 0.0;
-      if (rv != 0.0 && isfinite(rv) && !(fabs(rv) <= A.breakdown * fabs(rho))) {
-        al = rho / rv;
+        for (int m = 0; m < NC; ++m) v[m] = y[m];
       } else {
-        status = 2;   // (near) breakdown
-        break;
-      }
-#pragma unroll
-      for (int m = 0; m < 2 * H; ++m) {
-        r[m] -= al * v[m];   // s
-        ss += r[m][0] * r[m][0] + r[m][1] * r[m][1];
-        SmallCell c;
-        if (cell(m, c)) x[m] += al * G.x[c.at];
-      }
-      d = 0.0;
-      sum2(ss, d);
-      const bool at_half = ss <= A.rtol2 * r2;
-      om = 0.0;
-      if (!at_half) {
-        Two y[2 * H];
-        cycle(r, rd);
-        apply(r, rd, y);
-        double ts = 0.0, tt = 0.0;
-#pragma unroll
-        for (int m = 0; m < 2 * H; ++m) {
-          ts += y[m][0] * r[m][0] + y[m][1] * r[m][1];
-          tt += y[m][0] * y[m][0] + y[m][1] * y[m][1];
-        }
-        sum2(ts, tt);
-        if (tt > 0.0) om = ts / tt;
-        if (om != 0.0) {
-#pragma unroll
-          for (int m = 0; m < 2 * H; ++m) {
-            SmallCell c;
-            if (cell(m, c)) x[m] += om * G.x[c.at];
-            r[m] -= om * y[m];
-          }
-        }
+        step = om = b > 0.0 ? a / b : 0.0;
       }
       double rn = 0.0, rr = 0.0;
+      if (step != 0.0) {
 #pragma unroll
-      for (int m = 0; m < 2 * H; ++m) {
+        for (int m = 0; m < NC; ++m) {
+          SmallCell c;
+          if (cell(m, c)) x[m] += step * G.x[c.at];
+          r[m] -= step * y[m];
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < NC; ++m) {
         rn += R[m][0] * r[m][0] + R[m][1] * r[m][1];
         rr += r[m][0] * r[m][0] + r[m][1] * r[m][1];
       }
       sum2(rn, rr);
+      if (!second) {
+        if (!(rr <= A.rtol2 * r2)) continue;
+        kits += 1.0;
+        break;
+      }
       kits += 1.0;
-      if (at_half || rr <= A.rtol2 * r2) break;
+      if (rr <= A.rtol2 * r2) break;
       if (om == 0.0 || rn == 0.0 || !isfinite(rn)) {
         status = 2;   // breakdown before convergence
         break;
       }
-      beta = (rn / rho) * (al / om);
+      const double beta = (rn / rho) * (al / om);
       rho = rn;
+#pragma unroll
+      for (int m = 0; m < NC; ++m) p[m] = r[m] + beta * (p[m] - om * v[m]);
     }
     // ---- damped update and convergence
     double mp = 0.0, mc = 0.0;
 #pragma unroll
-    for (int m = 0; m < 2 * H; ++m) {
+    for (int m = 0; m < NC; ++m) {
       mp = larger(mp, fabs(x[m][0]));
       mc = larger(mc, fabs(x[m][1]));
     }
@@ -596,7 +683,7 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     const double size = fmax(mc, mp / A.p_ref);
     last = mc > A.dc_max ? 0.0 : size;
 #pragma unroll
-    for (int m = 0; m < 2 * H; ++m) {
+    for (int m = 0; m < NC; ++m) {
       SmallCell c;
       if (cell(m, c)) G.pc[c.at] += lam * x[m];
     }
@@ -605,20 +692,48 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     else fresh = !(size <= A.jac_reuse);
   }
 
+  // ---- the new state out; mass balance and range (k_balance, k_fin_balance)
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0, low = 0.0, high = 0.0;
 #pragma unroll
-  for (int m = 0; m < 2 * H; ++m) {
+  for (int m = 0; m < NC; ++m) {
     SmallCell c;
     if (!cell(m, c)) continue;
     const size_t q = global(c);
-    const Two v = G.pc[c.at];
-    A.p[q] = v[0];
-    A.c[q] = v[1];
+    const CellState o = G.state(c.at);
+    A.p[q] = o.p;
+    A.c[q] = o.c;
+    const double r = P.rho0 + P.drho * o.c, ro = P.rho0 + P.drho * co[m], dif = o.phi * A.F[0].side_dif;
+    a0 += P.vol * o.phi * (r - ro);
+    a1 += P.vol * o.phi * (r * o.c - ro * co[m]);
+    if (c.i == 0) {
+      a2 += P.tau * inflow;
+      a3 += P.tau * (inflow * P.c_left + dif * r * (o.c - P.c_left));
+    }
+    if (c.i == G.nx - 1) {
+      const double u = o.K * A.F[0].side_k * (o.p + P.rho1 * P.g * (-P.Ly + (c.j + 0.5) * P.hy));
+      const double flow = (u < 0.0 ? P.rho1 : r) * u;
+      double salt = flow * (u < 0.0 ? 1.0 : o.c);
+      if (P.right_dir) salt += dif * r * (o.c - 1.0);
+      a2 += P.tau * flow;
+      a3 += P.tau * salt;
+    }
+    low = larger(low, -o.c);
+    high = larger(high, o.c);
   }
+  sum2(a0, a1);
+  sum2(a2, a3);
+  max2(low, high);
   if (t == 0) {
-    A.stats[(size_t)s * 4] += newtons;
-    A.stats[(size_t)s * 4 + 1] += kits;
-    if (status != 0) A.status[s] = status;
-    if (!done && A.status[s] == 0) A.status[s] = 1;
+    const double scale = P.tau * P.rho0 * A.uin[s] * P.Ly;
+    double* st = A.stats + (size_t)s * 4;
+    st[0] += newtons;
+    st[1] += kits;
+    st[2] = fmax(st[2], fabs(a0 + a2) / scale);
+    st[3] = fmax(st[3], fabs(a1 + a3) / scale);
+    int v = status ? status : A.status[s];
+    if (!done && v == 0) v = 1;
+    if (v == 0 && (!(low <= A.c_range_tol) || !(high <= 1.0 + A.c_range_tol))) v = 4;
+    A.status[s] = v;
   }
 }
 
