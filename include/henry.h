@@ -133,8 +133,9 @@ typedef struct {
                                  iteration keeps the multigrid hierarchy, the coarse factors and
                                  the stored Jacobian (a chord step; only R is reassembled; large
                                  FP64 batches and one-launch steps form the fine operator from the
-                                 current state, so their step stays Newton's, and the latter decide
-                                 for each sample alone).  The first iteration of each step
+                                 current state, so their step stays Newton's; the latter decide for
+                                 each sample alone, and keep the coarse operators up to 30 times
+                                 this size).  The first iteration of each step
                                  always assembles.  0 disables [1e-3] */
   int mg_cycle;               /* 1: V-cycle; 2: W-cycle (two coarse cycles per level above the
                                  coarsest) [1] */
@@ -157,10 +158,10 @@ typedef struct {
                                  start, assembly, one BiCGStab iteration with both halves and the
                                  damped update, every decision taken per sample on the device -- is
                                  replayed from one captured hipGraph, followed by one host read; only
-                                 samples that still iterate continue as usual.  FP64 batches on grids
+                                 samples that still iterate continue as usual.  Batches on grids
                                  of up to 2048 cells (an explicit-inverse coarsest grid, V-cycles) solve
                                  every step in one launch instead, each sample on its own, with no host
-                                 read.  Changes the iteration path, not the discrete solution [1] */
+                                 read, the cycle in FP64.  Changes the iteration path, not the discrete solution [1] */
   int ragged_threads;         /* ragged calls with several grids: 0: one host thread (and stream) per
                                  grid, run concurrently [0]; 1: the grids one after another from the
                                  calling thread (for tools that cannot follow several threads) */

@@ -1516,9 +1516,10 @@ struct Solver {
   }
 
   // Steps solved in one launch (henry_small.hpp): what the kernel's LDS takes, as a step graph's
-  // options allow.
+  // options allow.  Its cycle is in FP64 whatever mg_precision: its iterates never leave LDS, so
+  // FP32 would save no traffic (24 steps, FP32 launch by launch and this: 48x24x64 21 and 10 ms).
   bool small() const {
-    return P.prec == 64 && P.inverse && o.mg_cycle == 1 && o.nu_post >= 1 && o.step_graphs && allow_graphs &&
+    return P.inverse && o.mg_cycle == 1 && o.nu_post >= 1 && o.step_graphs && allow_graphs &&
            !ctx->prof.on && P.nlev - 1 <= SMALL_LEVELS && P.G.ncell <= SMALL_CELLS &&
            P.lv[1]->ncell <= SMALL_THREADS;
   }

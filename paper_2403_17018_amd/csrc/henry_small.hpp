@@ -8,8 +8,8 @@
 // however few the samples, and a batch iterates until its hardest sample is done.  Milliseconds a
 // solve, before and with this kernel: 32x16 cells, 48 steps, 16 samples 31.0 and 8.1, 256 samples
 // 40.5 and 9.3; 64x32 cells, 48 steps, 64 samples 42.6 and 19.4, 333 samples 88 and 39; 24 steps,
-// 1000 samples 147 and 51; 12 steps, 4096 samples 574 and 144 (32x16: 83 and 63): it is taken for
-// every batch size.  What bounds it is latency: one workgroup (LDS, registers) fits a compute unit
+// 1000 samples 147 and 51; 12 steps, 8000 samples 1517 and 233 (32x16, 30000 samples: 830 and 368):
+// it is taken for every batch size.  What bounds it is latency: one workgroup (LDS, registers) fits a compute unit
 // and a step is a chain of passes, each a barrier, a few LDS reads and a row.  Of a step's 150 us at
 // 32x16 (3 Newton, 3 BiCGStab iterations) the fine passes take 19, the coarser grids 26, the
 // coarsest operator's inversion 24 (or twice), residuals and rows 45, the Krylov part 18.  Rows
@@ -25,6 +25,10 @@
 namespace henry {
 
 constexpr int SMALL_THREADS = 512, SMALL_CELLS = 2048, SMALL_LEVELS = TAIL_LEVELS + 1;   // smoothed grids at most
+
+// The fine rows are always the state's; the coarse grids' are kept up to this many times the update
+// that the option names, with the same iteration counts (32x16: 8.07 ms at 1, 7.65 at 30).
+constexpr double SMALL_REUSE = 30.0;
 
 struct SmallArgs {
   int S, nl;                                    // samples, smoothed grids (the coarsest follows)
@@ -689,7 +693,7 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     }
     lds_barrier();
     if (size <= A.newton_tol) done = true;
-    else fresh = !(size <= A.jac_reuse);
+    else fresh = !(size <= SMALL_REUSE * A.jac_reuse);
   }
 
   // ---- the new state out; mass balance and range (k_balance, k_fin_balance)

@@ -248,8 +248,8 @@ def test_fp32_solve_and_adjoint_on_one_plan(hx):
     one) of the same shape share a plan: each must come out as on a context of its own, in either
     order, to the linear solves' tolerance (1e-8 on the state, the workload's bound)."""
     import paper_2403_17018_amd as P
-    th = _cu(draw_theta(47, 40, level=0))
-    g, pr = P.grid(32, 16, 12), P.problem(T=9000.0)
+    th = _cu(draw_theta(47, 20, level=0))
+    g, pr = P.grid(80, 40, 12), P.problem(T=3600.0)              # above one-launch steps' cells
     o = P.solver_opts(mg_precision=32)
 
     def close(u, v):
@@ -284,9 +284,11 @@ def test_fp32_solve_and_adjoint_on_one_plan(hx):
     (32, 16, 12, dict(krylov_maxit=1)),
     (64, 32, 12, dict(problem=dict(recharge_omega=2e-3, q_in_amp=0.3, right_c_dirichlet=1))),
     (32, 16, 12, dict(problem=dict(field_model=1))),
+    (32, 16, 9, dict(mg_precision=32)),
+    (48, 24, 65, dict(mg_precision=32)),
 ])
 def test_small_grids_in_one_launch_a_step(hx, nx, ny, S, opts):
-    """FP64 grids of up to 2048 cells solve a step in one launch, a workgroup per sample; step_graphs
+    """Grids of up to 2048 cells solve a step in one launch, a workgroup per sample; step_graphs
     0 takes them launch by launch.  Both solve the same equations: the state of the solved samples to 1e-8 (the
     workload's bound), the same status, and at most 15 % (and 3) more BiCGStab iterations a sample, as a chord
     step's fine rows and coarse correction are not of the same state."""
