@@ -334,7 +334,8 @@ def bench_adaptive(args):
 def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
     """Time `steps` whole-batch solves (plus the estimator over the batch) after `warmup`
     untimed ones; the dominant kernel class and its roofline from HIP events on the library's
-    stream during the timed region."""
+    stream during the timed region.  Grids whose time steps are single launches go launch by
+    launch while the events are on: there they are taken from one more, untimed solve."""
     import torch
     prec = opts.mg_precision
     S = theta.shape[0]
@@ -347,12 +348,17 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
     for _ in range(warmup):
         step()
     torch.cuda.synchronize()
-    hx.profile(True)
+    one_launch = g.nx * g.ny <= ONE_LAUNCH_CELLS
+    hx.profile(not one_launch)
     t0 = time.perf_counter()
     for _ in range(steps):
         r, est = step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
+    if one_launch:
+        hx.profile(True)
+        step()
+        torch.cuda.synchronize()
     prof = hx.profile_read()
     hx.profile(False)
     dt = (t1 - t0) / steps
@@ -370,7 +376,8 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
     return dict(value=S * g.nsteps / dt, ms_per_step=dt * 1e3,
                 roofline={"bound": "hbm", "kernel": name[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
                           "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                          "traffic": pmc_traffic(name[cls], prec, workload, model),
+                          "traffic": pmc_traffic(name[cls], prec, workload, model,
+                                                 "henry_march.hpp" if name[cls] == "k_march" else "henry_kernels.hpp"),
                           "avg_launch_us": ms / n * 1e3, "launches": n,
                           "algorithmic_bytes_per_launch": per_launch_bytes},
                 kernel_classes_ms={k: round(v[2], 3) for k, v in prof.items()},
@@ -380,6 +387,7 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
                 _prof=prof)
 
 
+ONE_LAUNCH_CELLS = 2048
 VC_KERNEL_NAME = dict(gs="k_vc_gs", spmv="k_vc_spmv", assemble="k_vc_assemble")
 VC_SAMPLES = 512
 # one pre- and one post-smoothing sweep: the fastest of 1+1, 1+2, 2+1, 2+2 and 1+3 on this
@@ -435,9 +443,9 @@ def bench_vc(hx, P, S=VC_SAMPLES, graphs=1, prec=64):
                     + ("; FP32 multigrid and Jacobian" if prec == 32 else "")
                     + ("; BiCGStab iterations replayed from a hipGraph" if graphs else ""),
         "unit": "sample-timesteps/s", "value": S * g.nsteps / dt, "ms_per_step": dt * 1e3,
-        "roofline": {"bound": "hbm", "kernel": VC_name[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": VC_KERNEL_NAME[cls], "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": pmc_traffic(VC_name[cls], prec, "f3_vc_level1_paper", "paper", "henry_vc.hpp"),
+                     "traffic": pmc_traffic(VC_KERNEL_NAME[cls], prec, "f3_vc_level1_paper", "paper", "henry_vc.hpp"),
                      "avg_launch_us": ms / n * 1e3, "launches": n, "algorithmic_bytes_per_launch": per_launch,
                      "timed_in": "a stream-launched repeat of the run" if graphs else "the timed run"},
         "kernel_classes_ms": {k: round(prof_k[k][2], 3) for k in table},
