@@ -131,7 +131,7 @@ def solver_config(o):
     """The solver settings that ran, for the config label."""
     return {"coarse_grid": f"{o.coarse_nx}x{o.coarse_ny}",
             "coarse_solver": {1: "LU with partial pivoting", 2: "LU with partial pivoting (any size, short bands)"}.get(
-                getattr(o, "coarse_solver", 0), "block-banded LU without pivoting"),
+                getattr(o, "coarse_solver", 0), "elimination by 2x2 blocks without pivoting"),
             "smoother": f"red-black 2x2-block Gauss-Seidel, {o.nu_pre} pre + {o.nu_post} post sweeps",
             "cycle": "V" if o.mg_cycle == 1 else "W",
             "krylov": f"right-preconditioned BiCGStab, forcing term {o.krylov_rtol:g}",

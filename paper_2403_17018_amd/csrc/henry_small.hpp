@@ -7,8 +7,8 @@
 // Launch by launch a step of these grids is some 110 launches of 3 to 5 us and four host reads,
 // however few the samples, and a batch iterates until its hardest sample is done.  Milliseconds a
 // solve, before and with this kernel: 32x16 cells, 48 steps, 16 samples 31.0 and 6.7, 256 samples
-// 40.5 and 9.3; 64x32 cells, 48 steps, 64 samples 42.6 and 18.8, 333 samples 88 and 37; 24 steps,
-// 1000 samples 147 and 51; 12 steps, 8000 samples 1517 and 233 (32x16, 30000 samples: 830 and 368):
+// 40.5 and 8.9; 64x32 cells, 48 steps, 64 samples 42.6 and 18.8, 333 samples 88 and 37; 24 steps,
+// 1000 samples 147 and 50; 12 steps, 8000 samples 1517 and 233 (32x16, 30000 samples: 830 and 368):
 // it is taken for every batch size.  What bounds it is latency: one workgroup (LDS, registers) fits a compute unit
 // and a step is a chain of passes, each a barrier, a few LDS reads and a row.  Of a step's 150 us at
 // 32x16 (3 Newton, 3 BiCGStab iterations) the fine passes take 19, the coarser grids 26, the
