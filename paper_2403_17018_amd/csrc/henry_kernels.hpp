@@ -154,31 +154,39 @@ __device__ __forceinline__ double kl_1d(double w, int odd, double nrm, double t)
   return (odd ? sin(a) : cos(a)) / nrm;
 }
 
-// One block takes FIELDS_CPT * CY consecutive cells of one sample block.  The modes (KL) or
+// One block takes `cpb` consecutive cells of one sample block.  The modes (KL) or
 // the sines and cosines of the paper's porosity depend on the cell alone, so the block
 // evaluates them once per cell into LDS and every sample combines them with its own
 // coefficients, held in registers: 16 / SX FP64 sine or cosine evaluations per cell-sample
 // instead of 16, which bounded the kernel; what remains is one exp and the two stores.
 // 256 x 128 cells x 512 samples: 651 -> 125 us a call (268 MB written).
-constexpr int FIELDS_CPT = 4;
-__host__ inline size_t fields_lds(int CY) { return (size_t)FIELDS_CPT * CY * 8 * sizeof(double); }
-__global__ void __launch_bounds__(256) k_fields(Map m, Grid2 G, Phys P, KLModes kl, FieldParams fp,
+// Four cells a thread row, but of few samples (whose blocks have many rows) only so many that 512
+// blocks remain, down to 32 cells, one mode evaluation a thread: 4 CY cells took an assembly of
+// 256 x 128 cells x 2 samples from 88 to 98 us, 87 this way.
+__host__ inline int fields_cells(const Map& m, int ncell) {
+  int cpb = 4 * m.CY;
+  while (cpb > 32 && (size_t)m.nsb * ((ncell + cpb - 1) / cpb) < 512) cpb = (cpb + 1) / 2;
+  return cpb;
+}
+__host__ inline size_t fields_lds(int cpb) { return (size_t)cpb * 8 * sizeof(double); }
+__global__ void __launch_bounds__(256) k_fields(Map m, Grid2 G, int cpb, Phys P, KLModes kl, FieldParams fp,
                                                 const double* __restrict__ theta, double* __restrict__ phi,
                                                 double* __restrict__ K, double* __restrict__ uin) {
-  extern __shared__ double fields_sh[];   // [FIELDS_CPT * CY cells][8]
+  extern __shared__ double fields_sh[];   // [cpb cells][8]
   double (*e)[8] = reinterpret_cast<double (*)[8]>(fields_sh);
   const int sblk = blockIdx.x % m.nsb, cblk = blockIdx.x / m.nsb;
-  const int cell0 = cblk * FIELDS_CPT * m.CY, nc = min(FIELDS_CPT * m.CY, G.ncell - cell0);
+  const int cell0 = cblk * cpb, nc = min(cpb, G.ncell - cell0);
   const int nt = m.SX * m.CY, t = threadIdx.y * m.SX + threadIdx.x;
   if (fp.model == 1) {
-    // section 4, eq. poro_2levels: the periodic factors of a cell
-    for (int w = t; w < nc * 5; w += nt) {
-      const int q = w / 5, k = w - q * 5, cell = cell0 + q;
-      const int j = cell / G.nx, i = cell - j * G.nx;
-      const double x = (i + 0.5) * P.hx, y = -P.Ly + (j + 0.5) * P.hy;
-      e[q][k] = k == 0 ? cospi(0.5 * x) : k == 1 ? sinpi(2.0 * y) : k == 2 ? cospi(2.0 * x)
-                : k == 3 ? sinpi(64.0 * x) : sinpi(32.0 * y);
-    }
+    // section 4, eq. poro_2levels: the periodic factors of a cell, one function a wavefront
+    const int nw = nt >> 6;   // (whole wavefronts; at least two)
+    for (int k = t >> 6; k < 5 && t < 64 * nw; k += nw)
+      for (int q = t & 63; q < nc; q += 64) {
+        const int cell = cell0 + q, j = cell / G.nx, i = cell - j * G.nx;
+        const double x = (i + 0.5) * P.hx, y = -P.Ly + (j + 0.5) * P.hy;
+        e[q][k] = k == 0 ? cospi(0.5 * x) : k == 1 ? sinpi(2.0 * y) : k == 2 ? cospi(2.0 * x)
+                  : k == 3 ? sinpi(64.0 * x) : sinpi(32.0 * y);
+      }
   } else {
     for (int w = t; w < nc * kl.n; w += nt) {
       const int q = w / kl.n, k = w - q * kl.n, cell = cell0 + q;

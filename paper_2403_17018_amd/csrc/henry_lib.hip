@@ -233,12 +233,14 @@ static dim3 grid_cells(const Map& m, int ncell) {
   const long long nb = (long long)m.nsb * ((ncell + m.CY - 1) / m.CY);
   return dim3((unsigned)nb);
 }
-static dim3 grid_fields(const Map& m, int ncell) {
-  const int per = FIELDS_CPT * m.CY;
-  return dim3((unsigned)((long long)m.nsb * ((ncell + per - 1) / per)));
-}
 static dim3 grid_red(const Map& m) { return dim3((unsigned)((long long)m.nsb * m.ncb)); }
 static dim3 block_of(const Map& m) { return dim3(m.SX, m.CY); }
+static void launch_fields(hipStream_t st, const Map& m, const Grid2& G, const Phys& P, const KLModes& kl,
+                          const FieldParams& fp, const double* theta, double* phi, double* K, double* uin) {
+  const int cpb = fields_cells(m, G.ncell);
+  hipLaunchKernelGGL(k_fields, dim3((unsigned)((long long)m.nsb * ((G.ncell + cpb - 1) / cpb))), block_of(m),
+                     fields_lds(cpb), st, m, G, cpb, P, kl, fp, theta, phi, K, uin);
+}
 // the assembly's tiles: one workgroup per (sample block, ASM_TX x ASM_TY cells)
 static dim3 asm_grid(const Map& m, const Grid2& G) { return dim3((unsigned)((long long)m.nsb * asm_tiles(G.nx, G.ny))); }
 static dim3 asm_block(const Map& m) { return dim3(m.SX, ASM_T); }
@@ -845,8 +847,7 @@ struct Solver {
 
   void fields(const double* theta) {
     const Map& m = P.m;
-    hipLaunchKernelGGL(k_fields, grid_fields(m, P.G.ncell), block_of(m), fields_lds(m.CY), st, m, P.G, phys, kl, fp, theta,
-                       P.phi.as<double>(), P.K.as<double>(), P.uin.as<double>());
+    launch_fields(st, m, P.G, phys, kl, fp, theta, P.phi.as<double>(), P.K.as<double>(), P.uin.as<double>());
     for (int k = 1; k < P.nlev; ++k) {
       MGLevel& F = *P.lv[k - 1];
       MGLevel& C = *P.lv[k];
@@ -2228,8 +2229,7 @@ int henry_sample_fields(henry_ctx* ctx, const henry_problem* prob, henry_grid gr
     const Phys P = make_phys(*prob, grid.nx, grid.ny, grid.nsteps);
     const KLModes kl = make_kl(*prob);
     const FieldParams fp = make_fp(*prob);
-    hipLaunchKernelGGL(k_fields, grid_fields(m, G.ncell), block_of(m), fields_lds(m.CY), ctx->stream, m, G, P, kl, fp, theta, phi, K,
-                       q_in);
+    launch_fields(ctx->stream, m, G, P, kl, fp, theta, phi, K, q_in);
     HIPCHK(hipGetLastError());
     return HENRY_OK;
   });
@@ -2534,8 +2534,7 @@ int henry_assemble(henry_ctx* ctx, const henry_problem* prob, henry_grid grid, i
     double* phi = ctx->kws.as<double>();
     double* K = phi + N;
     double* uin = K + N;
-    hipLaunchKernelGGL(k_fields, grid_fields(m, G.ncell), block_of(m), fields_lds(m.CY), ctx->stream, m, G, P, make_kl(*prob),
-                       make_fp(*prob), theta, phi, K, uin);
+    launch_fields(ctx->stream, m, G, P, make_kl(*prob), make_fp(*prob), theta, phi, K, uin);
     hipLaunchKernelGGL((k_assemble<true, double, false, true>), asm_grid(m, G), asm_block(m), asm_lds(m.SX), ctx->stream, m,
                        G, P, p, c, c_old, (const double*)phi, (const double*)K, (const double*)uin, R, J,
                        (float*)nullptr);
@@ -2923,8 +2922,7 @@ struct VCSolver {
   }
 
   void fields(const double* theta) {
-    hipLaunchKernelGGL(k_fields, grid_fields(me, ne), block_of(me), fields_lds(me.CY), st, me, E, P, make_kl(pr), make_fp(pr), theta,
-                       phi.as<double>(), K.as<double>(), uin.as<double>());
+    launch_fields(st, me, E, P, make_kl(pr), make_fp(pr), theta, phi.as<double>(), K.as<double>(), uin.as<double>());
     const double* pf = phi.as<double>();
     const double* kf = K.as<double>();
     Grid2 Ef = E;
