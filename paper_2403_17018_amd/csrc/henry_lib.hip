@@ -358,6 +358,7 @@ struct Plan {
   // per operator: nu_pre, nu_post, precision, cycle, fuse_prolong, FP32 Jacobian in the products, valid
   int gkey[2][7] = {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}};
   double grtol[2] = {0.0, 0.0};
+  Phys gphys{};            // constants in the arguments of the untransposed ones' kernels (rows formed from the state)
   // captured first Newton iteration of a time step (step_graphs) and what it was captured for
   hipGraphExec_t step_exec = nullptr;
   Phys step_phys{};
@@ -1347,10 +1348,15 @@ struct Solver {
     const bool graphs = o.use_graphs && allow_graphs && !ctx->prof.on;
     if (graphs) {
       const int key[7] = {o.nu_pre, o.nu_post, P.prec, o.mg_cycle, o.fuse_prolong, spmv32(), 1};
-      if (std::memcmp(key, P.gkey[TR], sizeof key) != 0 || P.grtol[TR] != rtol2) {
+      // Plans outlive a problem.  Where the kernels read a stored Jacobian it brings the problem's constants;
+      // where they form their rows they hold them.
+      const bool formed = !TR && (P.free_rows || rows32());
+      if (std::memcmp(key, P.gkey[TR], sizeof key) != 0 || P.grtol[TR] != rtol2 ||
+          (formed && !same_operator(P.gphys, phys))) {
         P.drop_graphs(TR);
         std::memcpy(P.gkey[TR], key, sizeof key);
         P.grtol[TR] = rtol2;
+        if (!TR) P.gphys = phys;
       }
       for (int part = 0; part < 5; ++part) {
         if (P.gexec[TR][part]) continue;
@@ -1490,10 +1496,15 @@ struct Solver {
     newton_update();
   }
 
-  static bool same_phys(const Phys& a, const Phys& b) {
+  // What the operator's rows are formed from: all but the inflow's factor of the step (a periodic
+  // recharge changes it every step) and the QoI's region.
+  static bool same_operator(const Phys& a, const Phys& b) {
     return a.rho0 == b.rho0 && a.drho == b.drho && a.rho1 == b.rho1 && a.mu == b.mu && a.g == b.g && a.Dm == b.Dm &&
            a.c_left == b.c_left && a.hx == b.hx && a.hy == b.hy && a.vol == b.vol && a.tau == b.tau && a.Ly == b.Ly &&
-           a.Lx == b.Lx && a.uin_fac == b.uin_fac && a.qoi_xmin == b.qoi_xmin && a.right_dir == b.right_dir;
+           a.Lx == b.Lx && a.right_dir == b.right_dir;
+  }
+  static bool same_phys(const Phys& a, const Phys& b) {
+    return same_operator(a, b) && a.uin_fac == b.uin_fac && a.qoi_xmin == b.qoi_xmin;
   }
 
   // Replay (capturing first when the plan has none for these settings) the step graph:

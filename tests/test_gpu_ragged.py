@@ -70,6 +70,33 @@ def test_graph_replay_is_bitwise_equal_to_eager(hx):
             assert torch.equal(e.c_T, r.c_T) and torch.equal(e.p_T, r.p_T) and torch.equal(e.stats, r.stats)
 
 
+@pytest.mark.parametrize("step_graphs", [0, 1])
+@pytest.mark.parametrize("nx,ny,S,prec", [
+    (80, 40, 8, 64),      # rows of a stored Jacobian
+    (80, 40, 64, 64),     # formed from the state
+    (128, 64, 73, 64),    # and marched through
+    (144, 72, 127, 32),   # so with the FP32 cycle
+])
+def test_graphs_follow_the_problem(nx, ny, S, prec, step_graphs):
+    """A plan, and the BiCGStab iterations captured in it, outlives a call: calls of one shape with
+    another step length, viscosity, boundary condition or recharge, on one context with graphs,
+    each give bitwise the state and the iteration counts of a context of their own."""
+    import paper_2403_17018_amd as P
+    th = _cu(draw_theta(71, S, level=1))
+    T = 6 * 36000.0 / (3 * ny)
+    o = P.solver_opts(use_graphs=1, step_graphs=step_graphs, mg_precision=prec)
+    one = P.Henry(0)
+    for n, kw in ((6, {}), (9, {}), (9, dict(mu=2e-3)), (9, dict(right_c_dirichlet=1)),
+                  (9, dict(recharge_omega=2e-3, q_in_amp=0.3)), (6, {})):
+        g, pr = P.grid(nx, ny, n), P.problem(T=T, **kw)
+        own = P.Henry(0)
+        a, b = [h.solve(th, g, pr, o, want_p=True) for h in (one, own)]
+        own.close()
+        assert torch.equal(a.stats, b.stats), (n, kw, a.stats.sum(0), b.stats.sum(0))
+        assert torch.equal(a.c_T, b.c_T) and torch.equal(a.p_T, b.p_T) and torch.equal(a.status, b.status), (n, kw)
+    one.close()
+
+
 def test_ragged_with_graphs_matches_oracle(hx):
     import paper_2403_17018_amd as P
     T = 6000.0
