@@ -357,7 +357,7 @@ struct Plan {
                                 {nullptr, nullptr, nullptr, nullptr, nullptr}};
   // per operator: nu_pre, nu_post, precision, cycle, fuse_prolong, FP32 Jacobian in the products, valid
   int gkey[2][7] = {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}};
-  double grtol[2] = {0.0, 0.0};
+  double grtol[2] = {0.0, 0.0}, gbreakdown[2] = {0.0, 0.0};
   Phys gphys{};            // constants in the arguments of the untransposed ones' kernels (rows formed from the state)
   // captured first Newton iteration of a time step (step_graphs) and what it was captured for
   hipGraphExec_t step_exec = nullptr;
@@ -1352,10 +1352,11 @@ struct Solver {
       // where they form their rows they hold them.
       const bool formed = !TR && (P.free_rows || rows32());
       if (std::memcmp(key, P.gkey[TR], sizeof key) != 0 || P.grtol[TR] != rtol2 ||
-          (formed && !same_operator(P.gphys, phys))) {
+          P.gbreakdown[TR] != o.krylov_breakdown || (formed && !same_operator(P.gphys, phys))) {
         P.drop_graphs(TR);
         std::memcpy(P.gkey[TR], key, sizeof key);
         P.grtol[TR] = rtol2;
+        P.gbreakdown[TR] = o.krylov_breakdown;
         if (!TR) P.gphys = phys;
       }
       for (int part = 0; part < 5; ++part) {

@@ -97,6 +97,17 @@ def test_graphs_follow_the_problem(nx, ny, S, prec, step_graphs):
     one.close()
 
 
+def test_graphs_follow_the_breakdown_option(hx):
+    """krylov_breakdown is an argument of a captured kernel: a later call's value holds.  At 1e6 the
+    first step of every sample counts as a breakdown (status 2)."""
+    import paper_2403_17018_amd as P
+    th = _cu(draw_theta(72, 6, level=1))
+    g, pr = P.grid(80, 40, 4), P.problem(T=1200.0)
+    for breakdown, status in ((0.0, 0), (1e6, 2), (0.0, 0)):
+        r = hx.solve(th, g, pr, P.solver_opts(use_graphs=1, step_graphs=0, krylov_breakdown=breakdown))
+        assert (r.status == status).all(), (breakdown, r.status)
+
+
 def test_ragged_with_graphs_matches_oracle(hx):
     import paper_2403_17018_amd as P
     T = 6000.0
