@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(PLU_THREADS) k_plu_factor(int S, int nx, int n
           }
           u[c] = lane_value(w, pl);
         }
-        const double rp = u[j] != 0.0 ? 1.0 / u[j] : 0.0;   // an exactly singular column leaves L = 0
+        const double rp = u[j] != 0.0 ? 1.0 / u[j] : 0.0;   // an exactly singular column leaves L = 0 (and 1 / 0 in U)
 #pragma unroll
         for (int a = 0; a < RPL; ++a) {
           if (a == pa && lane == pl) {
@@ -229,7 +229,8 @@ __global__ void __launch_bounds__(PLU_THREADS) k_plu_factor(int S, int nx, int n
       const int r = e / PLU_NB, c = e - r * PLU_NB;
       const double x = P[r * (PLU_NB + 1) + c];
       Lg[e] = x;
-      if (r < PLU_NB) Ug[(size_t)r * C + c] = r == c ? (x != 0.0 ? 1.0 / x : 0.0) : x;   // U's diagonal as its reciprocal
+      // U's diagonal as its reciprocal: infinite for a singular operator, whose solves are not finite
+      if (r < PLU_NB) Ug[(size_t)r * C + c] = r == c ? 1.0 / x : x;
     }
     for (int r = t; r < m; r += PLU_THREADS) ps[(size_t)(k0 / PLU_NB) * m + r] = src[r];
     lds_barrier();

@@ -201,6 +201,30 @@ def test_pivoted_solvers_at_panel_edges(hx, nx, ny, S, solver):
                 assert np.abs(xs - ref).max() <= 1000 * eps * np.linalg.cond(A, np.inf) * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("what", ["row", "column"])
+@pytest.mark.parametrize("nx,ny,solver", [(8, 4, 1), (8, 4, 2), (3, 3, 2), (32, 16, 1)])
+def test_pivoted_solvers_of_a_singular_operator(hx, nx, ny, solver, what):
+    """One sample's operator has an unknown without an equation, or without an entry in any: its
+    solution is not finite, the others' are."""
+    import paper_2403_17018_amd as P
+    rng = np.random.default_rng(9)
+    J = rng.normal(size=(20, ny, nx, 3))
+    J[4:8, :, 0] = J[8:12, :, -1] = 0.0
+    J[12:16, 0] = J[16:20, -1] = 0.0
+    i, j = nx // 2, ny // 2
+    for k, (di, dj) in enumerate(((0, 0), (1, 0), (-1, 0), (0, 1), (0, -1))):
+        if what == "row":
+            J[4 * k:4 * k + 2, j, i, 1] = 0.0
+        elif 0 <= i + di < nx and 0 <= j + dj < ny:   # the rows of which (i, j) is neighbour k
+            J[[4 * k, 4 * k + 2], j + dj, i + di, 1] = 0.0
+    b = _cu(rng.normal(size=(2, ny, nx, 3)))
+    for prec in (64, 32):
+        for tr in (False, True):
+            x = hx.coarse_solve(_cu(J), b, P.grid(nx, ny, 1), solver, prec, tr)
+            assert torch.isfinite(x[..., [0, 2]]).all(), (prec, tr)
+            assert not torch.isfinite(x[..., 1]).all(), (prec, tr)
+
+
 @pytest.mark.parametrize("nx,ny,S,opts", [
     (64, 32, 64, dict()),
     (64, 32, 129, dict(nu_pre=2, nu_post=1)),
