@@ -134,9 +134,8 @@ typedef struct {
                                  the stored Jacobian (a chord step; only R is reassembled; large
                                  FP64 batches and one-launch steps form the fine operator from the
                                  current state, so their step stays Newton's; the latter decide for
-                                 each sample alone, and keep the coarse operators up to 30 times
-                                 this size).  The first iteration of each step
-                                 always assembles.  0 disables [1e-3] */
+                                 each sample alone).  The first iteration of each step always
+                                 assembles.  0 disables [1e-3] */
   int mg_cycle;               /* 1: V-cycle; 2: W-cycle (two coarse cycles per level above the
                                  coarsest) [1] */
   int adjoint_guess;          /* first guess of each transposed solve of the reverse sweep.

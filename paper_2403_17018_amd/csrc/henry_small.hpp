@@ -26,10 +26,6 @@ namespace henry {
 
 constexpr int SMALL_THREADS = 512, SMALL_CELLS = 2048, SMALL_LEVELS = TAIL_LEVELS + 1;   // smoothed grids at most
 
-// The fine rows are always the state's; the coarse grids' are kept up to this many times the update
-// that the option names, with the same iteration counts (32x16: 8.07 ms at 1, 7.65 at 30).
-constexpr double SMALL_REUSE = 30.0;
-
 struct SmallArgs {
   int S, nl;                                    // samples, smoothed grids (the coarsest follows)
   int nx[SMALL_LEVELS + 1], ny[SMALL_LEVELS + 1];
@@ -693,7 +689,7 @@ __global__ void __launch_bounds__(SMALL_THREADS, 2) k_small_step(SmallArgs A, Ph
     }
     lds_barrier();
     if (size <= A.newton_tol) done = true;
-    else fresh = !(size <= SMALL_REUSE * A.jac_reuse);
+    else fresh = !(size <= A.jac_reuse);   // the coarse operators'; the fine rows are always the state's
   }
 
   // ---- the new state out; mass balance and range (k_balance, k_fin_balance)

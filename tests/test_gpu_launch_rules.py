@@ -331,3 +331,15 @@ def test_small_grids_in_one_launch_a_step(hx, nx, ny, S, opts):
         assert u.numel() == 0 or ((u - v).abs().amax() / v.abs().amax()).item() <= 1e-8
     ia, ib = a.stats[:, 1].sum().item(), b.stats[:, 1].sum().item()
     assert ia <= 1.15 * ib + 3 * S, (ia, ib)
+
+
+@pytest.mark.parametrize("tol", [1e-9, 1e-6, 1e-4])
+def test_one_launch_steps_keep_operators_up_to_the_option(hx, tol):
+    """newton_jac_reuse means its value in one-launch steps too: at the Newton tolerance no iteration
+    follows an update of that size, so every operator is fresh, as with 0."""
+    import paper_2403_17018_amd as P
+    th = _cu(draw_theta(73, 40, level=0))
+    g, pr = P.grid(32, 16, 6), P.problem(T=4500.0)
+    a, b = [hx.solve(th, g, pr, P.solver_opts(newton_tol=tol, newton_predict=0.0, newton_jac_reuse=r), want_p=True)
+            for r in (tol, 0.0)]
+    assert torch.equal(a.stats, b.stats) and torch.equal(a.c_T, b.c_T) and torch.equal(a.p_T, b.p_T)
