@@ -779,20 +779,33 @@ static size_t part_bytes_max(int nx, int ny, int S, int red_blocks, int sample_b
   return mx;
 }
 
-// The plan of a batch shape, with its compacted sub-plan (see Solver::compact_newton) created
-// and sized for every effective batch size up front: the solve itself then allocates and frees
-// no device or pinned memory, so concurrent solves on worker threads never call the allocator
-// while another thread captures or synchronises a stream.
+// Steps solved in one launch (henry_small.hpp): what the kernel's LDS takes, as a step graph's
+// options allow.  Its cycle is in FP64 whatever mg_precision: its iterates never leave LDS, so
+// FP32 would save no traffic (24 steps, FP32 launch by launch and this: 48x24x64 21 and 10 ms).
+static bool one_launch_steps(const henry_ctx* ctx, const Plan& P, const henry_solver_opts& o) {
+  return P.inverse && o.mg_cycle == 1 && o.nu_post >= 1 && o.step_graphs && !ctx->prof.on &&
+         P.nlev - 1 <= SMALL_LEVELS && P.G.ncell <= SMALL_CELLS && P.lv[1]->ncell <= SMALL_THREADS;
+}
+
+constexpr size_t COMPACT_MIN = 3 << 19;   // see Solver::may_compact
+
+// The plan of a batch shape, with its compacted sub-plan (see Solver::compact_newton), where steps
+// with these options may use it, created and sized for every effective batch size up front: the
+// solve itself then allocates and frees no device or pinned memory, so concurrent solves on worker
+// threads never call the allocator while another thread captures or synchronises a stream.
 static Plan* get_plan(henry_ctx* ctx, int nx, int ny, int S, const henry_solver_opts& o, int inst = 0) {
   const PlanKey key = plan_key(nx, ny, S, o, inst);
-  auto it = ctx->plans.find(key);
-  if (it != ctx->plans.end()) return it->second.get();
-  auto P = make_plan(nx, ny, S, o);
-  P->compact = make_plan(nx, ny, S, o);
-  P->compact->part.alloc(part_bytes_max(nx, ny, S, o.red_blocks, o.sample_block));
-  Plan* raw = P.get();
-  ctx->plans[key] = std::move(P);
-  return raw;
+  const auto it = ctx->plans.find(key);
+  std::unique_ptr<Plan> made;   // (released again if the sub-plan does not fit)
+  if (it == ctx->plans.end()) made = make_plan(nx, ny, S, o);
+  Plan* P = made ? made.get() : it->second.get();
+  if (!P->compact && P->N >= COMPACT_MIN && !one_launch_steps(ctx, *P, o)) {
+    auto Q = make_plan(nx, ny, S, o);
+    Q->part.alloc(part_bytes_max(nx, ny, S, o.red_blocks, o.sample_block));
+    P->compact = std::move(Q);
+  }
+  if (made) ctx->plans[key] = std::move(made);
+  return P;
 }
 
 // Use plan Q (capacity >= Sa samples) for an effective batch of Sa samples.  Allocates
@@ -809,8 +822,6 @@ static void plan_set_samples(Plan& Q, int Sa, int red_blocks, int sample_block) 
 // ---------------------------------------------------------------------------
 // solver
 // ---------------------------------------------------------------------------
-constexpr size_t COMPACT_MIN = 3 << 19;   // see Solver::may_compact
-
 struct Solver {
   henry_ctx* ctx;
   const henry_problem& pr;
@@ -1528,14 +1539,6 @@ struct Solver {
     HIPCHK(hipGraphLaunch(P.step_exec, st));
   }
 
-  // Steps solved in one launch (henry_small.hpp): what the kernel's LDS takes, as a step graph's
-  // options allow.  Its cycle is in FP64 whatever mg_precision: its iterates never leave LDS, so
-  // FP32 would save no traffic (24 steps, FP32 launch by launch and this: 48x24x64 21 and 10 ms).
-  bool small() const {
-    return P.inverse && o.mg_cycle == 1 && o.nu_post >= 1 && o.step_graphs && allow_graphs &&
-           !ctx->prof.on && P.nlev - 1 <= SMALL_LEVELS && P.G.ncell <= SMALL_CELLS &&
-           P.lv[1]->ncell <= SMALL_THREADS;
-  }
   void small_step(int n) {
     SmallArgs A{};
     A.S = P.S;
@@ -1613,7 +1616,7 @@ struct Solver {
     // order (the first steps have less history).
     const int order = guess_order(n);
     const bool settled = order >= 0 && order == guess_order(n + 1);
-    if (small()) {
+    if (allow_graphs && one_launch_steps(ctx, P, o)) {
       small_step(n);
       return;
     }

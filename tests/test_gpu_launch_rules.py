@@ -333,6 +333,30 @@ def test_small_grids_in_one_launch_a_step(hx, nx, ny, S, opts):
     assert ia <= 1.15 * ib + 3 * S, (ia, ib)
 
 
+def test_memory_for_compaction_only_where_it_can_happen():
+    """A shape whose steps never move samples to a smaller batch (fewer than 3 * 2^19 cell-samples, or
+    one launch a step) holds one plan, not two; a later call that may (launch by launch) gets its
+    second then.  700 samples of 64x32 cells are below that number, 800 above."""
+    import paper_2403_17018_amd as P
+    g, pr = P.grid(64, 32, 1), P.problem(T=375.0)
+    used = {}
+    for S, graphs in ((700, (0,)), (800, (0,)), (800, (1,)), (800, (1, 0))):
+        th = _cu(draw_theta(74, S, level=0))
+        h = P.Henry(0)
+        for sg in (0, 1):   # the kernels' own memory (scratch of their queue)
+            h.solve(th[:2].contiguous(), g, pr, P.solver_opts(step_graphs=sg), want_c=False)
+        torch.cuda.synchronize()
+        m0 = torch.cuda.mem_get_info()[0]
+        for sg in graphs:
+            assert h.solve(th, g, pr, P.solver_opts(step_graphs=sg), want_c=False).nfailed == 0
+        torch.cuda.synchronize()
+        used[S, graphs] = m0 - torch.cuda.mem_get_info()[0]
+        h.close()
+    assert used[700, (0,)] < 0.6 * used[800, (0,)], used
+    assert used[800, (1,)] < 0.6 * used[800, (0,)], used
+    assert used[800, (1, 0)] > 0.9 * used[800, (0,)], used
+
+
 @pytest.mark.parametrize("tol", [1e-9, 1e-6, 1e-4])
 def test_one_launch_steps_keep_operators_up_to_the_option(hx, tol):
     """newton_jac_reuse means its value in one-launch steps too: at the Newton tolerance no iteration
