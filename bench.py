@@ -28,8 +28,8 @@ sys.path.insert(0, ROOT)
 from henry_inputs import WORKLOADS, draw_theta, level_grid  # noqa: E402
 
 # HBM peak and the algorithmic bytes per unit of each kernel class (FP64 / FP32 multigrid)
-from paper_2403_17018_amd.metrics import (BYTES_MARCH, BYTES_ROWS, HBM_PEAK_GBS, VC_BYTES_PER_UNIT,  # noqa: E402
-                                          MetricsLog, batch_record, bytes_per_unit)
+from paper_2403_17018_amd.metrics import (HBM_PEAK_GBS, VC_BYTES_PER_UNIT, MetricsLog, batch_record,  # noqa: E402
+                                          bytes_per_unit, kernel_path)
 
 METRICS = None   # MetricsLog of --metrics: one JSON line per measured batch
 KERNEL_NAME = dict(gs="k_gs_colour", spmv="k_spmv_dot", assemble="k_assemble", restrict="k_residual_restrict",
@@ -363,12 +363,13 @@ def measure_batch(hx, theta, g, prob, opts, warmup, steps, workload, model):
     hx.profile(False)
     dt = (t1 - t0) / steps
     if METRICS is not None:
-        METRICS.write(batch_record(workload, g, r, seconds=dt, prof=prof, mg_precision=prec, timed_runs=steps,
-                                   coarse=f"{opts.coarse_nx}x{opts.coarse_ny}", coarse_solver=opts.coarse_solver))
+        METRICS.write(batch_record(workload, g, r, seconds=dt, prof=prof, mg_precision=prec, opts=opts,
+                                   timed_runs=steps, coarse=f"{opts.coarse_nx}x{opts.coarse_ny}",
+                                   coarse_solver=opts.coarse_solver))
     st = r.stats.cpu()
-    table = bytes_per_unit(prec, g.nx * g.ny * S)
-    name = (KERNEL_NAME_MARCH if table is BYTES_MARCH[prec] else
-            KERNEL_NAME_ROWS if table is BYTES_ROWS else KERNEL_NAME)
+    n_cells = g.nx * g.ny * S
+    table = bytes_per_unit(prec, n_cells, opts)
+    name = dict(march=KERNEL_NAME_MARCH, rows=KERNEL_NAME_ROWS, stored=KERNEL_NAME)[kernel_path(prec, n_cells, opts)]
     cls = max(table, key=lambda k: prof[k][2])            # dominant kernel class by summed time
     n, units, ms = prof[cls]
     per_launch_bytes = units / n * table[cls]

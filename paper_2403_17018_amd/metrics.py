@@ -29,20 +29,48 @@ BYTES_PER_UNIT = {
     32: dict(gs=104, spmv=96, assemble=136, restrict=38, prolong=108),
 }
 # FP64 batches from 2^17 cell-samples form the rows from p, c, phi and K (32 bytes a cell), and from
-# 9 * 2^16 cell-samples the whole pre-smoothing with the restriction (restrict) and the whole
-# post-smoothing with the prolongation (prolong) of the fine grid are one launch each, per cell; FP32
-# ones do so from 5 * 2^18 cell-samples, and form the products' rows.
+# 9 * 2^16 cell-samples, with 1 + 2 sweeps and the prolongation fused, the whole pre-smoothing with
+# the restriction (restrict) and the whole post-smoothing with the prolongation (prolong) of the fine
+# grid are one launch each, per cell; FP32 ones do so from 5 * 2^18 cell-samples, in V-cycles, and
+# form the products' rows.
 ROWS_MIN, MARCH_MIN, MARCH_MIN32 = 1 << 17, 9 << 16, 5 << 18
 BYTES_ROWS = dict(gs=112, spmv=88, assemble=56, restrict=44, prolong=120)
 BYTES_MARCH = {64: dict(BYTES_ROWS, restrict=60, prolong=76),
                32: dict(gs=104, spmv=80, assemble=56, restrict=54, prolong=62)}
 
 
-def bytes_per_unit(mg_precision: int, cell_samples: int) -> dict:
-    """BYTES_PER_UNIT of the kernels that a batch of this many fine cell-samples runs."""
-    if cell_samples >= (MARCH_MIN if mg_precision == 64 else MARCH_MIN32):
-        return BYTES_MARCH[mg_precision]
-    return BYTES_ROWS if mg_precision == 64 and cell_samples >= ROWS_MIN else BYTES_PER_UNIT[mg_precision]
+def kernel_path(mg_precision: int, cell_samples: int, opts=None) -> str:
+    """Which kernels the untransposed cycle of a batch of this many fine cell-samples runs on the fine
+    grid: "march", "rows" (formed from the state, a launch per pass) or "stored" (Jacobian).
+    opts: henry_solver_opts (None: the defaults)."""
+    fused = opts is None or (opts.nu_pre == 1 and opts.nu_post == 2 and bool(opts.fuse_prolong))
+    v_cycle = opts is None or opts.mg_cycle == 1
+    if mg_precision == 32:
+        return "march" if fused and v_cycle and cell_samples >= MARCH_MIN32 else "stored"
+    if fused and cell_samples >= MARCH_MIN:
+        return "march"
+    return "rows" if cell_samples >= ROWS_MIN else "stored"
+
+
+def bytes_per_unit(mg_precision: int, cell_samples: int, opts=None, adjoint: bool = False) -> dict:
+    """Bytes per unit of the kernel classes of a batch of this many fine cell-samples, without those
+    for which they are not one number: classes whose kernel these options change (the restriction's
+    after other than one sweep, the product's after a cycle that does not end in a sweep, the
+    prolongation's on its own), and an adjoint's, whose transposed solves read the FP64 Jacobian
+    where the forward solves form rows or read an FP32 one."""
+    path = kernel_path(mg_precision, cell_samples, opts)
+    if adjoint and (mg_precision == 32 or path != "stored"):
+        return {}
+    table = {"march": BYTES_MARCH[mg_precision], "rows": BYTES_ROWS, "stored": BYTES_PER_UNIT[mg_precision]}[path]
+    drop = set()
+    if opts is not None:
+        if opts.nu_pre != 1 or opts.nu_post == 0:
+            drop.add("restrict")
+        if opts.nu_post == 0:
+            drop.add("spmv")
+        if opts.nu_post == 0 or not opts.fuse_prolong:
+            drop.add("prolong")
+    return {k: v for k, v in table.items() if k not in drop}
 
 
 # The vertex-centred path (henry_vc_solve), per vertex-sample: the four-colour pass reads the
@@ -69,10 +97,11 @@ def _hist(x: np.ndarray, width: float) -> dict:
                 min=float(x.min()), mean=float(x.mean()), max=float(x.max()))
 
 
-def kernel_classes(prof: dict, mg_precision: int = 64, cell_samples: int = 0) -> dict:
-    """{class: {launches, units, ms[, avg_launch_us, gbs, frac_of_peak]}} from Henry.profile_read()."""
+def kernel_classes(prof: dict, mg_precision: int = 64, cell_samples: int = 0, opts=None, adjoint: bool = False) -> dict:
+    """{class: {launches, units, ms[, avg_launch_us, gbs, frac_of_peak]}} from Henry.profile_read();
+    opts and adjoint: of the profiled calls (bytes_per_unit)."""
     out = {}
-    table = bytes_per_unit(mg_precision, cell_samples)
+    table = bytes_per_unit(mg_precision, cell_samples, opts, adjoint)
     for name, (n, units, ms) in prof.items():
         if n == 0:
             continue
@@ -85,8 +114,9 @@ def kernel_classes(prof: dict, mg_precision: int = 64, cell_samples: int = 0) ->
 
 
 def batch_record(label: str, grid, result, seconds: float | None = None, prof: dict | None = None,
-                 mg_precision: int = 64, **extra) -> dict:
-    """One JSON-ready record for a SolveResult on henry_grid `grid`."""
+                 mg_precision: int = 64, opts=None, **extra) -> dict:
+    """One JSON-ready record for a SolveResult on henry_grid `grid`; opts: the profiled solves'
+    henry_solver_opts (None: the defaults)."""
     st = result.stats.detach().cpu().numpy().astype(np.float64)       # [S, 4] (or [S, 2])
     status = result.status.detach().cpu().numpy()
     S = st.shape[0]
@@ -102,7 +132,7 @@ def batch_record(label: str, grid, result, seconds: float | None = None, prof: d
     if seconds is not None and seconds > 0:
         rec.update(seconds=float(seconds), sample_timesteps_per_s=S * grid.nsteps / seconds)
     if prof is not None:
-        rec["kernel_classes"] = kernel_classes(prof, mg_precision, int(grid.nx) * int(grid.ny) * S)
+        rec["kernel_classes"] = kernel_classes(prof, mg_precision, int(grid.nx) * int(grid.ny) * S, opts)
     rec.update(extra)
     return rec
 

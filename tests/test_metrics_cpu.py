@@ -5,7 +5,8 @@ import numpy as np
 import torch
 
 import paper_2403_17018_amd as P
-from paper_2403_17018_amd.metrics import BYTES_PER_UNIT, MetricsLog, batch_record, kernel_classes
+from paper_2403_17018_amd.metrics import (BYTES_MARCH, BYTES_PER_UNIT, BYTES_ROWS, MetricsLog, batch_record,
+                                          bytes_per_unit, kernel_classes, kernel_path)
 
 
 def _result(stats, status):
@@ -37,6 +38,27 @@ def test_kernel_classes_bandwidth():
     assert "spmv" not in kc and "gbs" not in kc["band_factor"]
     want = 10_000_000 * BYTES_PER_UNIT[64]["gs"] / 1e-3 / 1e9
     assert abs(kc["gs"]["gbs"] - round(want, 2)) < 1e-9 and kc["gs"]["avg_launch_us"] == 100.0
+
+
+def test_bytes_follow_the_kernels_that_run():
+    """The byte table is that of the solver's dispatch on size, precision and options; classes
+    without one number are left out."""
+    big, rows, small = 1 << 24, 1 << 18, 1 << 16
+    o = P.solver_opts
+    assert [kernel_path(64, n, o()) for n in (big, rows, small)] == ["march", "rows", "stored"]
+    assert [kernel_path(32, n, o(mg_precision=32)) for n in (big, 1 << 20, small)] == ["march", "stored", "stored"]
+    for kw in (dict(nu_pre=2), dict(nu_post=1), dict(fuse_prolong=0)):
+        assert kernel_path(64, big, o(**kw)) == "rows" and kernel_path(32, big, o(**kw)) == "stored"
+    assert kernel_path(64, big, o(mg_cycle=2)) == "march" and kernel_path(32, big, o(mg_cycle=2)) == "stored"
+    assert bytes_per_unit(64, big) == BYTES_MARCH[64] and bytes_per_unit(64, big, o()) == BYTES_MARCH[64]
+    assert bytes_per_unit(64, big, o(nu_post=1)) == BYTES_ROWS
+    assert "restrict" not in bytes_per_unit(64, big, o(nu_pre=2))
+    assert "prolong" not in bytes_per_unit(64, small, o(fuse_prolong=0))
+    assert bytes_per_unit(64, big, adjoint=True) == {} == bytes_per_unit(32, small, adjoint=True)
+    assert bytes_per_unit(64, small, adjoint=True) == BYTES_PER_UNIT[64]
+    prof = {"prolong": (10, 10_000_000, 1.0)}
+    assert "gbs" in kernel_classes(prof, 64, big)["prolong"]
+    assert "gbs" not in kernel_classes(prof, 64, big, o(fuse_prolong=0))["prolong"]
 
 
 def test_metrics_log_appends_lines(tmp_path):
