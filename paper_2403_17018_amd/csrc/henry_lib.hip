@@ -311,11 +311,13 @@ static FieldParams make_fp(const henry_problem& pr) {
 // ---------------------------------------------------------------------------
 // From this many cell-samples on the FP64 forward solves read no stored Jacobian: their passes are
 // bound by memory there, and by launches below, of which a cycle has one more (a stored diagonal
-// block lets the pre-smoothing pass form the red half on the fly).  Stored and formed, ms a solve:
-// 8192 cell-samples 30.8 and 33.1, 51 200: 35.9 and 36.9, 131 072: 42.7 and 40.5 (32x16 cells),
-// 42.2 and 43.1 (64x32), 55.5 and 56.2 (128x64), and these three in concurrent streams 142 and
-// 130; 512 000: 54.7 and 47.4, 524 288: 60.4 and 53.8 (128x64), 74.1 and 63.5 (256x128), 681 984:
-// 108.5 and 90.3, 2 097 152: 169.4 and 130.2.
+// block lets the pre-smoothing pass form the red half on the fly).  Stored and formed, ms a solve
+// (median of three runs): 16 384 cell-samples 27.7 and 30.2, 65 536: 33.9 and 34.5; 131 072: 36.6
+// and 37.6 (128x64 cells), 31.7 and 31.4 (256x128), 27.1 and 26.1 (512x256), 128.8 and 127.6 (as level
+// 2 of an estimate, beside levels 0 and 1); 133 632: 40.7 and 39.7 (96x48); 163 840: 43.6 and 41.6
+// (128x64); 204 800: 43.0 and 42.7 (80x40); 262 144: 42.9 and 41.9 (128x64), 38.9 and 35.5 (256x128),
+// 32.7 and 30.7 (512x256); 320 000: 56.3 and 50.8 (80x40); 393 216: 55.3 and 51.7 (128x64), 54.6 and
+// 48.9 (256x128); 524 288: 61.4 and 53.2, 50.9 and 43.2.
 constexpr size_t FREE_MIN = 1 << 17;
 struct MGLevel {
   int nx, ny, ncell;
