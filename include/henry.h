@@ -149,9 +149,9 @@ typedef struct {
                                  pivoting of the 2*cells x 2*cells matrix, trailing updates on the
                                  matrix cores; needs 2*cells divisible by 16 and a 16-column panel of
                                  all rows within the LDS (32x16 cells at most in FP64).  2: the same for
-                                 any number of cells with coarse_ny <= 19.  1 and 2 work on the
-                                 operator's band only (cells numbered along the shorter side first),
-                                 in FP64, one workgroup per sample */
+                                 coarse_ny <= 19 and 2*cells + 32*(4*coarse_ny + 3) <= 8176 (in FP32
+                                 16352).  1 and 2 work on the operator's band only (cells numbered
+                                 along the shorter side first), in FP64, one workgroup per sample */
   int step_graphs;            /* 1: once a step's kernel arguments are settled (constant inflow, full
                                  extrapolation history), its first Newton iteration -- the step's
                                  start, assembly, one BiCGStab iteration with both halves and the

@@ -611,21 +611,23 @@ static size_t max_lds_per_block() {
   return (size_t)std::max(v, o);
 }
 
-// Sizes the pivoted solvers take: `solver` 1 (stated as a dense LU) whole 16-column panels of
-// all n rows in LDS, 2 (stated as a band LU) bands of up to 39 diagonals a side.  Both run
-// k_plu_factor, whose window is smaller than either.
+// Sizes the pivoted solvers take, as henry.h states them (coarse_solver): `solver` 1 whole 16-column
+// panels of all n rows within the LDS in its precision, 2 bands of up to 39 diagonals a side in
+// the same.  Both run k_plu_factor, whose FP64 window of the band is smaller than either: these
+// limits are the entry points', not the kernel's.
 static void check_plu_size(int solver, int nx, int ny, int prec) {
   const size_t n = 2 * (size_t)nx * ny, tsz = prec == 32 ? 4 : 8;
   if (solver == 1) {
     const size_t need = n * 16 * tsz + 16 * 64 * tsz + 1024 * (tsz + sizeof(int)) + n * sizeof(int);
-    if (n % 16) fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d: the dense LU needs 2 * cells divisible by 16", nx, ny);
+    if (n % 16) fail(HENRY_EUNSUPPORTED, "grid %dx%d: coarse_solver 1 needs 2 * cells divisible by 16", nx, ny);
     if (need > max_lds_per_block())
-      fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d too large for the dense LU's LDS panel (%zu bytes)", nx, ny, need);
+      fail(HENRY_EUNSUPPORTED, "grid %dx%d: beyond coarse_solver 1's limit, 16 columns of all rows in LDS (%zu bytes)",
+           nx, ny, need);
   } else {
     const size_t kl = 2 * (size_t)ny + 1, cols = 2 * kl + 1;
     const size_t factor = ((kl + 2) * (cols + 1) + 16 * cols + cols) * tsz + 16, solve = (n + 2 * 16 * cols) * tsz + 128;
     if (kl * 2 * kl > 3072 || factor > 64 * 1024 || solve > 64 * 1024)
-      fail(HENRY_EUNSUPPORTED, "coarsest grid %dx%d too large for the pivoted band LU (ny <= 19 and the LDS limit)", nx,
+      fail(HENRY_EUNSUPPORTED, "grid %dx%d: beyond coarse_solver 2's limit, ny <= 19 and its band's rows in 64 KB", nx,
            ny);
   }
 }
