@@ -121,13 +121,16 @@ def test_adjoint_level3_full_batch():
     h.close()
 
 
-def test_adjoint_with_graphs_equals_eager(hx):
+@pytest.mark.parametrize("nx,ny,S,T", [(64, 32, 8, 6000.0),      # forward steps a launch each
+                                       (80, 40, 8, 2400.0),      # of captured iterations
+                                       (80, 40, 48, 2400.0)])    # whose rows are formed from the state
+def test_adjoint_with_graphs_equals_eager(hx, nx, ny, S, T):
     """Forward and transposed BiCGStab iterations replayed from hipGraphs (alternating in the
     reverse sweep) give bitwise the eager gradient."""
     import paper_2403_17018_amd as P
-    th = draw_theta(23, 8)
-    g = P.grid(64, 32, 8)
-    prob = P.problem(T=6000.0)
+    th = draw_theta(23, S)
+    g = P.grid(nx, ny, 8)
+    prob = P.problem(T=T)
     a = hx.adjoint(_cu(th), g, prob, P.solver_opts(use_graphs=0), checkpoint_every=3)
     b = hx.adjoint(_cu(th), g, prob, P.solver_opts(use_graphs=1), checkpoint_every=3)
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])

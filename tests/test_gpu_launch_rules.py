@@ -50,12 +50,16 @@ def test_moments_at_every_row_width(hx, m):
     assert np.abs(out["var_field"].cpu().numpy() - vf).max() <= 8 * eps * 3 * 2
 
 
-@pytest.mark.parametrize("S", [1, 3, 16, 37, 64, 130])
+@pytest.mark.parametrize("nx,ny,S", [
+    *[(nx, ny, S) for nx, ny in ((6, 3), (34, 17), (64, 32)) for S in (1, 3, 16, 37, 64, 130)],
+    (1030, 515, 1), (1030, 515, 3), (260, 130, 16),    # 1024, 340 and 64 cells a block
+    (400, 200, 1), (300, 150, 3),                      # 128 and 85
+])
 @pytest.mark.parametrize("model", ["kl", "paper"])
-@pytest.mark.parametrize("nx,ny", [(6, 3), (34, 17), (64, 32)])
-def test_fields_at_block_edges(hx, S, model, nx, ny):
-    """Cells per block 4 * (256 / min(S, 64)), with remainders: phi, K and u_in against the
-    oracle.  Bound: 8 + 8 products and sums, and exp's argument (about 21) carried to K."""
+def test_fields_at_block_edges(hx, nx, ny, S, model):
+    """4 * (256 / min(S, 64)) cells a block, of few samples halved towards 32 while fewer than 512
+    blocks are left, with remainders: phi, K and u_in against the oracle.  Bound: 8 + 8 products and
+    sums, and exp's argument (about 21) carried to K."""
     import paper_2403_17018_amd as P
     from oracle import henry as H
     th = draw_theta(31, S, level=1)
@@ -297,7 +301,8 @@ def test_fp32_solve_and_adjoint_on_one_plan(hx):
     (32, 16, 130, dict(nu_pre=2, nu_post=1)),
     (32, 16, 17, dict(coarse_nx=4, coarse_ny=2)),               # three smoothed grids
     (40, 20, 20, dict()),                                       # a coarsest grid of 50 cells, idle threads
-    (44, 22, 33, dict(coarse_nx=11, coarse_ny=11)),             # not a multiple of the threads
+    (24, 12, 33, dict()),                                       # a coarsest grid of 18 cells, half the threads idle
+    (20, 10, 33, dict()),                                       # the coarsest grid alone below the fine one, 50 cells
     (48, 24, 7, dict(nu_pre=3, nu_post=1)),                     # two cells of a colour a thread
     (64, 32, 40, dict()),
     (64, 32, 300, dict()),                                      # more samples than workgroups at once
@@ -321,8 +326,12 @@ def test_small_grids_in_one_launch_a_step(hx, nx, ny, S, opts):
     kw = dict(opts.pop("problem", {}), T=36000.0 * 6 / (3 * max(ny, 8)))
     th = _cu(draw_theta(51, S, level=0))
     g = P.grid(nx, ny, 6)
+    reads = [hx.profile_read()["host_sync"][0]]
     a = hx.solve(th, g, P.problem(**kw), P.solver_opts(**opts), want_c=True, want_p=True)
+    reads.append(hx.profile_read()["host_sync"][0])
     b = hx.solve(th, g, P.problem(**kw), P.solver_opts(step_graphs=0, **opts), want_c=True, want_p=True)
+    reads.append(hx.profile_read()["host_sync"][0])
+    assert reads[1] - reads[0] <= 1 and reads[2] - reads[1] > 6, reads   # no read within steps but launch by launch
     assert torch.equal(a.status, b.status)
     ok = b.status == 0
     assert ok.any() or opts.get("newton_maxit") == 1

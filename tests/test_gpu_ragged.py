@@ -41,14 +41,17 @@ def test_ragged_call_matches_separate_calls(hx):
         assert np.allclose(r.qoi.cpu().numpy(), s.qoi.cpu().numpy(), rtol=1e-9, atol=0)
 
 
-def test_same_grid_and_size_with_other_step_counts(hx):
+@pytest.mark.parametrize("nx,ny,S,T", [(32, 16, 16, 7200.0),     # a step a launch
+                                       (80, 40, 16, 2400.0),     # captured iterations, stored Jacobians
+                                       (80, 40, 48, 2400.0)])    # and rows formed from the state
+def test_same_grid_and_size_with_other_step_counts(hx, nx, ny, S, T):
     """Two batches on one grid with the same sample count but different step counts are solved
     concurrently in one call (one stream each): each must equal its own separate solve.  They
     share a workspace shape, so the library gives each its own instance."""
     import paper_2403_17018_amd as P
-    prob = P.problem(T=7200.0)
-    a, b = draw_theta(61, 16), draw_theta(62, 16)
-    ga, gb = P.grid(32, 16, 8), P.grid(32, 16, 12)
+    prob = P.problem(T=T)
+    a, b = draw_theta(61, S), draw_theta(62, S)
+    ga, gb = P.grid(nx, ny, 8), P.grid(nx, ny, 12)
     rr = hx.solve_ragged([(_cu(a), ga), (_cu(b), gb)], prob, P.solver_opts(use_graphs=1), want_p=True)
     for th, g, r in ((a, ga, rr[0]), (b, gb, rr[1])):
         s = hx.solve(_cu(th), g, prob, P.solver_opts(use_graphs=1), want_p=True)
@@ -60,14 +63,19 @@ def test_same_grid_and_size_with_other_step_counts(hx):
 
 def test_graph_replay_is_bitwise_equal_to_eager(hx):
     """Each BiCGStab iteration replayed from a captured hipGraph, many replays with eager
-    Newton/assembly work in between, against the eager launch sequence."""
+    Newton/assembly work in between, against the eager launch sequence: grids of single-launch
+    steps, of a stored Jacobian, of rows formed from the state, marched through (FP64, FP32)."""
     import paper_2403_17018_amd as P
-    th = _cu(draw_theta(0, 16))
     for prec in (64, 32):
-        for g in (P.level_grid(0), P.grid(64, 32, 12)):
-            e = hx.solve(th, g, opts=P.solver_opts(mg_precision=prec, use_graphs=0), want_p=True)
-            r = hx.solve(th, g, opts=P.solver_opts(mg_precision=prec, use_graphs=1), want_p=True)
-            assert torch.equal(e.c_T, r.c_T) and torch.equal(e.p_T, r.p_T) and torch.equal(e.stats, r.stats)
+        for S, g in ((16, P.level_grid(0)), (16, P.grid(64, 32, 12)), (16, P.grid(80, 40, 12)),
+                     (48, P.grid(80, 40, 12)), (73, P.grid(128, 64, 8)), (161, P.grid(128, 64, 4))):
+            th = _cu(draw_theta(0, S))
+            prob = P.problem() if g.ny <= 32 else P.problem(T=36000.0 * g.nsteps / (3 * g.ny))
+            e = hx.solve(th, g, prob, opts=P.solver_opts(mg_precision=prec, use_graphs=0), want_p=True)
+            r = hx.solve(th, g, prob, opts=P.solver_opts(mg_precision=prec, use_graphs=1), want_p=True)
+            assert e.nfailed == 0 or g.ny <= 32, (prec, S, g.ny)
+            assert torch.equal(e.stats, r.stats), (prec, S, g.ny)
+            assert torch.equal(e.c_T, r.c_T) and torch.equal(e.p_T, r.p_T), (prec, S, g.ny)
 
 
 @pytest.mark.parametrize("step_graphs", [0, 1])
@@ -172,20 +180,22 @@ def _host_syncs(hx):
 
 
 @pytest.mark.parametrize("prec", [64, 32])
-def test_step_graphs_match_oracle_and_eager_series(hx, prec):
+@pytest.mark.parametrize("nx,ny,nsteps,S", [(32, 16, 48, 16),    # a step a launch
+                                            (80, 40, 12, 6)])    # a captured graph a step
+def test_step_graphs_match_oracle_and_eager_series(hx, prec, nx, ny, nsteps, S):
     """Steps whose first Newton iteration is replayed from one captured graph (device-side
     control, one host read per step): c and p at T against the oracle (1e-8), and the salt
     masses after every step against the eager solve, so each of the replays -- with eager
     continuation iterations, balance kernels and host reads between them -- is checked; the
     replayed path needs fewer host round trips."""
     import paper_2403_17018_amd as P
-    th = draw_theta(0, 16)
-    g = P.level_grid(0)
-    ref = oracle_batch(th, g.nx, g.ny, g.nsteps)
+    th = draw_theta(0, S)
+    g, kw = P.grid(nx, ny, nsteps), dict(T=36000.0 * nsteps / (3 * ny))
+    ref = oracle_batch(th, g.nx, g.ny, g.nsteps, kw)
     out = {}
     for sg in (0, 1):
         n0 = _host_syncs(hx)
-        r = hx.solve(_cu(th), g, opts=P.solver_opts(mg_precision=prec, step_graphs=sg), want_p=True,
+        r = hx.solve(_cu(th), g, P.problem(**kw), opts=P.solver_opts(mg_precision=prec, step_graphs=sg), want_p=True,
                      want_series=True)
         torch.cuda.synchronize()
         out[sg] = (r, _host_syncs(hx) - n0)
