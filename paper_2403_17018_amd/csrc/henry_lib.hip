@@ -785,7 +785,7 @@ static size_t part_bytes_max(int nx, int ny, int S, int red_blocks, int sample_b
 
 // Steps solved in one launch (henry_small.hpp): what the kernel's LDS takes, as a step graph's
 // options allow.  Its cycle is in FP64 whatever mg_precision: its iterates never leave LDS, so
-// FP32 would save no traffic (24 steps, FP32 launch by launch and this: 48x24x64 21 and 10 ms).
+// FP32 would save no traffic (24 steps, FP32 launch by launch and this: 48x24x64 27 and 10 ms).
 static bool one_launch_steps(const henry_ctx* ctx, const Plan& P, const henry_solver_opts& o) {
   return P.inverse && o.mg_cycle == 1 && o.nu_post >= 1 && o.step_graphs && !ctx->prof.on &&
          P.nlev - 1 <= SMALL_LEVELS && P.G.ncell <= SMALL_CELLS && P.lv[1]->ncell <= SMALL_THREADS;
@@ -1529,7 +1529,7 @@ struct Solver {
   void launch_step_graph(int n) {
     const int order = guess_order(n);
     if (!P.step_exec || !same_phys(P.step_phys, phys) || std::memcmp(&P.step_opts, &o, sizeof o) != 0 ||
-        P.step_spmv32 != spmv32() ||        P.step_order != order) {
+        P.step_spmv32 != spmv32() || P.step_order != order) {
       P.drop_step_graph();
       P.step_exec = capture([&] {
         step_prologue(n, true);

@@ -5,8 +5,9 @@
 //
 // 256x128 cells, 512 samples: the pre-smoothing sweep with the restriction takes 333 us (three
 // launches of a pass each 562), two post-smoothing sweeps with the prolongation 498 us (four
-// launches 961); in FP32 (rows formed in FP64, kept rounded) 319 and 444 us.  They move 1.01 and 1.28 GB at least, 210 and 270 us at the 4.7 TB/s of a copy;
-// counters show 1.1 and 1.5 GB and the vector units busy a third of the time.  What bounds them is
+// launches 961); in FP32 (rows formed in FP64, kept rounded) 319 and 444 us.  They move 1.01 and
+// 1.28 GB at least, 210 and 270 us at the 4.7 TB/s of a copy; counters show 1.15 and 1.75 GB (FP32
+// 1.12 and 1.62) and the vector units busy a third of the time.  What bounds them is
 // the issue of two wavefronts a SIMD, all that the registers of a column's rows leave (182 and 243),
 // each waiting for its own LDS reads, barrier and instructions most of the time.  Keeping the rows'
 // coefficients in registers costs that residency but a third of the arithmetic of forming them in

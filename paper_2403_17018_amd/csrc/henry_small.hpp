@@ -6,16 +6,17 @@
 //
 // Launch by launch a step of these grids is some 110 launches of 3 to 5 us and four host reads,
 // however few the samples, and a batch iterates until its hardest sample is done.  Milliseconds a
-// solve, before and with this kernel: 32x16 cells, 48 steps, 16 samples 31.0 and 6.7, 256 samples
-// 40.5 and 8.9; 64x32 cells, 48 steps, 64 samples 42.6 and 18.8, 333 samples 88 and 37; 24 steps,
-// 1000 samples 147 and 50; 12 steps, 8000 samples 1517 and 233 (32x16, 30000 samples: 830 and 368):
-// it is taken for every batch size.  What bounds it is latency: one workgroup (LDS, registers) fits a compute unit
-// and a step is a chain of passes, each a barrier, a few LDS reads and a row.  Of a step's 150 us at
-// 32x16 (3 Newton, 3 BiCGStab iterations) the fine passes take 19, the coarser grids 26, the
-// coarsest operator's inversion 24 (or twice), residuals and rows 45, the Krylov part 18.  Rows
-// formed from the state in every pass instead of kept made 10.8 ms of the 9.4 then; with two cells
-// of each colour a thread keeping them spills (64x32x64: 20.7 ms with one coarser grid's kept, 22.5
-// with two).  The step's start and its balance as launches of their own took 0.5 ms of 9.4.
+// solve, launch by launch (step_graphs 0) and with this kernel: 32x16 cells, 48 steps, 16 samples
+// 40.3 and 7.2, 256 samples 49.0 and 9.5; 64x32 cells, 48 steps, 64 samples 44.7 and 19.6, 333
+// samples 99 and 38.9; 24 steps, 1000 samples 133 and 51; 12 steps, 8000 samples 1518 and 250
+// (32x16, 30000 samples: 869 and 426): it is taken for every batch size.  What bounds it is latency:
+// one workgroup (LDS, registers) fits a compute unit and a step is a chain of passes, each a
+// barrier, a few LDS reads and a row.  Of a step's 150 us at 32x16 (3 Newton, 3 BiCGStab iterations)
+// the fine passes take 19, the coarser grids 26, the coarsest operator's inversion 24 (or
+// twice), residuals and rows 45, the Krylov part 18.  Rows formed from the state in every pass
+// instead of kept took 15 % more; with two cells of each colour a thread keeping them spills
+// (64x32x64: 20.7 ms with one coarser grid's kept, 22.5 with two).  The step's start and its
+// balance as launches of their own took 5 %.
 #pragma once
 
 #include <hip/hip_runtime.h>
